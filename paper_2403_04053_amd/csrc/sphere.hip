@@ -176,49 +176,58 @@ __global__ void shell_flush_kernel(const int64_t* __restrict__ ctr, int count, c
 }
 
 // node values: separable interpolation of (sum + comp) * scale - inc (scale
-// complex: one over the incident phasor)
-__global__ void node_kernel(int n_nodes, const int* __restrict__ start, const double* __restrict__ lw,
-                            const double3* __restrict__ normal, const int* __restrict__ slot, int nx, int ny,
-                            const double2* __restrict__ sum, const double2* __restrict__ comp,
-                            const double2* __restrict__ inc, double2 scale, double2* __restrict__ out) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n_nodes) return;
-    const int ix = start[3 * q], iy = start[3 * q + 1], iz = start[3 * q + 2];
+// complex: one over the incident phasor).  One wave per node: lane 8 b + a
+// holds the (x, y) stencil column (a, b) and walks the eight z planes, so a
+// wave's gathers are eight runs of eight consecutive shell slots each and a
+// lane's eight loads are independent; the z sums with the values' and the
+// derivative's weights are all it keeps, the x and y weights multiply them
+// once.  The work is the gathers' latency: one thread per node (512 dependent
+// gathers each on 64 workgroups) took 309 us for 8192 nodes, this 20 us.
+constexpr int kNodeWaves = 4;
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+__global__ __launch_bounds__(64 * kNodeWaves) void node_kernel(
+    int n_nodes, const int* __restrict__ start, const double* __restrict__ lw, const double3* __restrict__ normal,
+    const int* __restrict__ slot, int nx, int ny, const double2* __restrict__ sum, const double2* __restrict__ comp,
+    const double2* __restrict__ inc, double2 scale, double2* __restrict__ out) {
+    static_assert(kStencil == 8, "a wave is an 8 x 8 stencil plane");
+    const int lane = threadIdx.x & 63;
+    const int q = blockIdx.x * kNodeWaves + (threadIdx.x >> 6);
+    if (q >= n_nodes) return;  // whole wave
+    const int a = lane & 7, b = lane >> 3;
     const double* W = lw + (int64_t)q * 3 * 2 * kStencil;
-    const double* Lx = W;
-    const double* dLx = W + kStencil;
-    const double* Ly = W + 2 * kStencil;
-    const double* dLy = W + 3 * kStencil;
     const double* Lz = W + 4 * kStencil;
     const double* dLz = W + 5 * kStencil;
-    double vr = 0, vi = 0, gxr = 0, gxi = 0, gyr = 0, gyi = 0, gzr = 0, gzi = 0;
+    const int64_t plane = (int64_t)nx * ny;
+    const int64_t lin = (start[3 * q] + a) + (int64_t)nx * (start[3 * q + 1] + b) + plane * start[3 * q + 2];
+    int sl[kStencil];
+#pragma unroll
+    for (int c = 0; c < kStencil; ++c) sl[c] = slot[lin + c * plane];
+    double vr = 0, vi = 0, dr = 0, di = 0;
+#pragma unroll
     for (int c = 0; c < kStencil; ++c) {
-        for (int b = 0; b < kStencil; ++b) {
-            const double wyz = Ly[b] * Lz[c], wdy = dLy[b] * Lz[c], wdz = Ly[b] * dLz[c];
-            for (int a = 0; a < kStencil; ++a) {
-                const int64_t lin = (ix + a) + (int64_t)nx * ((iy + b) + (int64_t)ny * (iz + c));
-                const int sl = slot[lin];
-                const double2 sv = sum[sl], cv = comp[sl], iv = inc[sl];
-                const double ar = sv.x + cv.x, ai = sv.y + cv.y;
-                const double pr = ar * scale.x - ai * scale.y - iv.x, pi = ar * scale.y + ai * scale.x - iv.y;
-                const double w0 = Lx[a] * wyz;
-                vr += w0 * pr;
-                vi += w0 * pi;
-                const double wx = dLx[a] * wyz;
-                gxr += wx * pr;
-                gxi += wx * pi;
-                const double wy = Lx[a] * wdy;
-                gyr += wy * pr;
-                gyi += wy * pi;
-                const double wz = Lx[a] * wdz;
-                gzr += wz * pr;
-                gzi += wz * pi;
-            }
-        }
+        const double2 sv = sum[sl[c]], cv = comp[sl[c]], iv = inc[sl[c]];
+        const double ar = sv.x + cv.x, ai = sv.y + cv.y;
+        const double pr = ar * scale.x - ai * scale.y - iv.x, pi = ar * scale.y + ai * scale.x - iv.y;
+        vr += Lz[c] * pr;
+        vi += Lz[c] * pi;
+        dr += dLz[c] * pr;
+        di += dLz[c] * pi;
     }
     const double3 nq = normal[q];
-    out[q] = make_double2(vr, vi);
-    out[n_nodes + q] = make_double2(nq.x * gxr + nq.y * gyr + nq.z * gzr, nq.x * gxi + nq.y * gyi + nq.z * gzi);
+    const double lx = W[a], dlx = W[kStencil + a], ly = W[2 * kStencil + b], dly = W[3 * kStencil + b];
+    const double wv = lx * ly, wg = nq.x * (dlx * ly) + nq.y * (lx * dly), wz = nq.z * wv;
+    const double orr = wave_sum(wv * vr), oi = wave_sum(wv * vi);
+    const double gr = wave_sum(wg * vr + wz * dr), gi = wave_sum(wg * vi + wz * di);
+    if (lane == 0) {
+        out[q] = make_double2(orr, oi);
+        out[n_nodes + q] = make_double2(gr, gi);
+    }
 }
 
 constexpr int kNodeChunk = 256;
@@ -521,7 +530,8 @@ hipError_t sphere_phasors(pstd_solver* s, const SphereOut& o, double2* out, hipS
     SphereState* sp = s->sphere;
     if (o.ik < 0 || o.ik >= sp->nk) return hipErrorInvalidValue;
     const int64_t off = (int64_t)o.ik * sp->n_shell;
-    hipLaunchKernelGGL(node_kernel, dim3((unsigned)((sp->n_nodes + 127) / 128)), dim3(128), 0, stream, sp->n_nodes,
+    hipLaunchKernelGGL(node_kernel, dim3((unsigned)((sp->n_nodes + kNodeWaves - 1) / kNodeWaves)),
+                       dim3(64 * kNodeWaves), 0, stream, sp->n_nodes,
                        sp->start, sp->lw, sp->normal, sp->slot, s->prob.n[0], s->prob.n[1], sp->sum + off,
                        sp->comp + off, sp->inc, o.scale, sp->phasor);
     hipError_t e = hipGetLastError();
