@@ -683,13 +683,15 @@ pstd_status solver_create(const pstd_problem* p, hipStream_t stream, int64_t* ex
             (e = hipMemcpy(s->v2full, full.data(), full.size() * sizeof(float), hipMemcpyHostToDevice)))
             return cleanup(hip_fail(s, e, "potential"));
     }
-    // where the potential term is taken: in the x pass (re-reading psi^n from
-    // the cache on the rows that cross V's box) when the box covers under a
-    // quarter of the rows, else in the z pass (psi^n held in registers); the
-    // complex absorber's real part (every cell) and segmented x pencils take
-    // the z pass (batch instances follow the same rule, grouped by it)
-    const double box_rows = (double)s->pot.n[1] * s->pot.n[2] / ((double)p->n[1] * p->n[2]);
-    s->potx = (p->abc_UR == 0.0 && p->sub_core[0] == 0 && box_rows < 0.25) ? 1 : 0;
+    // where the potential term is taken: in the x pass (V's rows are contiguous
+    // there, and psi^n is read again from the cache on the rows that cross V's
+    // box or, with a complex absorber, on all), which spares the z pass a copy
+    // of psi^n held in registers; with V on most of the grid, z pass and x pass:
+    // 160^3 25.0 + 13.0 -> 22.3 + 14.0 us, 288^3 213 + 78 -> 175 + 96,
+    // 150 x 108 x 180 with a complex absorber 32.0 + 14.0 -> 19.8 + 17.7.
+    // Segmented x or z pencils take the z pass (segments of 48 + 2 8 points re-read
+    // a third more than they update: 72.3 against 69.9 Gcell/s)
+    s->potx = p->sub_core[0] == 0 && p->sub_core[2] == 0 ? 1 : 0;
     // fields (psi pair and L, 24 B per cell) beyond the Infinity Cache: the z
     // pass's last-use loads bypass it, which leaves it to the lines the next
     // pass reads (measured: 256^3 +6 %, 288^3 +1 %; within the cache the

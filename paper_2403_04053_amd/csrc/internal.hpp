@@ -40,8 +40,8 @@ struct PassArgs {
     float2* buf[2];            // psi ping-pong
     float2* L;                 // kinetic accumulator (scaled by 2 eta dtau)
     PotentialArgs pot;
-    int potx;                  // 1: the x pass takes the potential term (V's box covers few rows,
-                               // no absorber real part, x unsegmented), else the z pass
+    int potx;                  // 1: the x pass takes the potential term (x and z unsegmented), else
+                               // the z pass
     int nt;                    // 1: the fields outgrow the Infinity Cache; the z pass reads its
                                // last-use operands (psi^n, L, psi^{n-1}) with non-temporal loads
     int nx, ny, nz;

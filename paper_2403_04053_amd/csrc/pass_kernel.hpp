@@ -28,7 +28,7 @@
 // with the field); z pass adds its term and applies the leapfrog update with
 // the potential (V read only on the pencils that cross the box where it may
 // be non-zero), TF/SF source and absorber, writing psi^{n+1} over psi^{n-1}.
-// When that box covers few rows (PassArgs::potx), the x pass takes the
+// Where x and z are whole pencils (PassArgs::potx) the x pass takes the
 // potential term instead, on the rows that cross the box, and the z pass
 // holds no copy of psi^n through its transforms.
 // Inside the DFT window each pass also accumulates, in FP64 with Neumaier
@@ -240,18 +240,36 @@ __device__ __forceinline__ TileGeo tile_geo(const Fields& f, int tile, int pA, b
     return g;
 }
 
-// raw pencil values of one tile (zero outside the grid and for idle lanes)
+// Element n1 of a thread's pencil lies n1 * step bytes after its element 0,
+// step uniform over the grid: one 64-bit pointer per thread and array, and
+// one add of a scalar per access (a product per element cost a quarter-rate
+// 64-bit multiply-add each, a tenth of the z pass's VALU time).
+template <class T>
+__device__ __forceinline__ GMEM T* at_step(GMEM T* p, int n1, int64_t step) {
+    return (GMEM T*)((GMEM char*)p + (int64_t)n1 * step);
+}
+template <class T>
+__device__ __forceinline__ GMEM const T* at_step(GMEM const T* p, int n1, int64_t step) {
+    return (GMEM const T*)((GMEM const char*)p + (int64_t)n1 * step);
+}
+
+// raw pencil values of one tile (zero outside the grid and for idle lanes);
+// p: the thread's element 0.  Whole-axis pencils lie inside the grid as a
+// whole, so one branch covers a thread's loads.
 template <int N, int N1, int N2, bool SEG, bool NTL = false>
-__device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ psi, const TileGeo& g, int n2,
+__device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ p, int64_t step, const TileGeo& g, int n2,
                                           float2 (&x)[N1]) {
-    unroll<N1>([&](auto i) {
-        constexpr int n1 = decltype(i)::value;
-        const int e = n2 + N2 * n1;
-        const bool in = g.valid && (e < N) && (!SEG || (g.g0 + e >= 0 && g.g0 + e < g.Ng));
-        float2 val = make_float2(0.f, 0.f);
-        if (in) val = load_last<NTL>(psi + g.base + (int64_t)e * g.estride);
-        x[n1] = val;
-    });
+    static_assert(N == N1 * N2, "pencil factors");
+    unroll<N1>([&](auto i) { x[decltype(i)::value] = make_float2(0.f, 0.f); });
+    if constexpr (!SEG) {
+        if (g.valid) unroll<N1>([&](auto i) { x[decltype(i)::value] = load_last<NTL>(at_step(p, decltype(i)::value, step)); });
+    } else {
+        unroll<N1>([&](auto i) {
+            constexpr int n1 = decltype(i)::value;
+            const int e = g.g0 + n2 + N2 * n1;
+            if (g.valid && e >= 0 && e < g.Ng) x[n1] = load_last<NTL>(at_step(p, n1, step));
+        });
+    }
 }
 
 // One workgroup per tile of P pencils; MULTI launches find their instance
@@ -331,8 +349,10 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
 
     {
         const TileGeo geo = tile_geo<N, P, AXIS, SEG>(f, tile, pA, activeA);
+        const int64_t first = geo.base + (int64_t)n2 * geo.estride;        // this thread's element 0
+        const int64_t step = (int64_t)(N2 * sizeof(float2)) * geo.estride;  // bytes between its elements
         float2 raw[N1];
-        load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi, geo, n2, raw);
+        load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi + first, step, geo, n2, raw);
         // the y pass's epilogue operand (L from the x pass), the same elements
         // the epilogue writes, read by the thread that writes them.  Issued
         // once stage A is done, the field loads have the memory system to
@@ -343,15 +363,18 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
         float2 Lin[N1];
         auto load_L = [&]() {
             if constexpr (AXIS == 1) {
-                const int C = SEG ? f.seg_core : N;
-                const int H = SEG ? f.seg_halo : 0;
-                unroll<N1>([&](auto i) {
-                    constexpr int n1 = decltype(i)::value;
-                    const int e = n2 + N2 * n1;
-                    Lin[n1] = make_float2(0.f, 0.f);
-                    if (geo.valid && e < N && (!SEG || (e >= H && e < H + C)))
-                        Lin[n1] = f.L[geo.base + (int64_t)e * geo.estride];
-                });
+                GMEM const float2* Lp = f.L + first;
+                unroll<N1>([&](auto i) { Lin[decltype(i)::value] = make_float2(0.f, 0.f); });
+                if constexpr (!SEG) {
+                    if (geo.valid) unroll<N1>([&](auto i) { Lin[decltype(i)::value] = *at_step(Lp, decltype(i)::value, step); });
+                } else {
+                    const int C = f.seg_core, H = f.seg_halo;
+                    unroll<N1>([&](auto i) {
+                        constexpr int n1 = decltype(i)::value;
+                        const int e = n2 + N2 * n1;
+                        if (geo.valid && e >= H && e < H + C) Lin[n1] = *at_step(Lp, n1, step);
+                    });
+                }
             }
         };
         if constexpr (SEG) load_L();
@@ -541,57 +564,49 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
         GMEM float2* __restrict__ Lbuf = f.L;
         if (geo.valid) {
             if constexpr (AXIS == 0 && POTX) {
-                // the potential term 2 dtau V / E0 psi^n of the row's cells when V's
-                // box covers few rows: rows off the box store the kinetic term alone,
-                // the others read psi^n again (the tile was just read, so this hits
-                // the cache) rather than hold it in registers through the transforms
-                const int64_t row = ((int64_t)tile * P + pA) / (SEG ? f.nseg : 1);
+                // the potential term 2 dtau (V / E0 + sum_a w_a) psi^n of the row's
+                // cells: rows off V's box store the kinetic term alone (unless the
+                // absorber has a real part), the others read psi^n again (the tile
+                // was just read, so this hits the cache) rather than hold it in
+                // registers through the transforms
+                const int64_t row = (int64_t)tile * P + pA;
                 const int z = (int)((unsigned)row / (unsigned)f.ny), y = (int)row - z * f.ny;
                 const bool brow = (unsigned)(y - f.vlo1) < (unsigned)f.vn1 && (unsigned)(z - f.vlo2) < (unsigned)f.vn2;
-                if (!brow) {
-                    unroll<N1>([&](auto i) {
-                        constexpr int n1 = decltype(i)::value;
-                        const int e = n2 + N2 * n1;
-                        if (e < N && (!SEG || (e >= H && e < H + C))) Lbuf[geo.base + e] = v[n1];
-                    });
+                GMEM const float* __restrict__ wr0 = f.wr0;
+                if (!brow && !wr0) {
+                    unroll<N1>([&](auto i) { *at_step(Lbuf + first, decltype(i)::value, step) = v[decltype(i)::value]; });
                 } else {
                     // every load first (the box value through a clamped index), then
                     // the products and stores, so the loads overlap
                     const int64_t vrow = ((int64_t)(z - f.vlo2) * f.vn1 + (y - f.vlo1)) * f.vn0 - f.vlo0;
+                    const float wyz = wr0 ? f.wr1[y] + f.wr2[z] : 0.f;
                     float2 pv[N1];
                     float vv[N1];
                     unroll<N1>([&](auto i) {
                         constexpr int n1 = decltype(i)::value;
-                        const int e = n2 + N2 * n1;
-                        const int x = geo.g0 + e;
-                        const bool own = e < N && (!SEG || (e >= H && e < H + C));
-                        const bool inb = own && (unsigned)(x - f.vlo0) < (unsigned)f.vn0;
-                        pv[n1] = make_float2(0.f, 0.f);
-                        if (own) pv[n1] = psi[geo.base + e];
+                        const int x = n2 + N2 * n1;
+                        const bool inb = brow && (unsigned)(x - f.vlo0) < (unsigned)f.vn0;
+                        pv[n1] = *at_step(psi + first, n1, step);
                         const float b = f.vbox[inb ? vrow + x : 0];
-                        vv[n1] = inb ? b : 0.f;
+                        vv[n1] = (inb ? b : 0.f) + (wr0 ? wyz + wr0[x] : 0.f);
                     });
                     unroll<N1>([&](auto i) {
                         constexpr int n1 = decltype(i)::value;
-                        const int e = n2 + N2 * n1;
-                        if (e < N && (!SEG || (e >= H && e < H + C)))
-                            Lbuf[geo.base + e] = cadd(v[n1], cscale(pv[n1], vv[n1]));
+                        *at_step(Lbuf + first, n1, step) =
+                            make_float2(fmaf(pv[n1].x, vv[n1], v[n1].x), fmaf(pv[n1].y, vv[n1], v[n1].y));
                     });
                 }
             } else if constexpr (AXIS == 0) {
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    if (e < N && (!SEG || (e >= H && e < H + C))) Lbuf[geo.base + e] = v[n1];
+                    if (!SEG || (e >= H && e < H + C)) *at_step(Lbuf + first, n1, step) = v[n1];
                 });
             } else if constexpr (AXIS == 1) {
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    if (e < N && (!SEG || (e >= H && e < H + C))) {
-                        const int64_t ad = geo.base + (int64_t)e * geo.estride;
-                        Lbuf[ad] = cadd(Lin[n1], v[n1]);
-                    }
+                    if (!SEG || (e >= H && e < H + C)) *at_step(Lbuf + first, n1, step) = cadd(Lin[n1], v[n1]);
                 });
             } else {
                 GMEM const float* __restrict__ t_gam = f.gam;
@@ -602,8 +617,13 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
                 const float2 SA = cadd(cmul(Dx, Zy), cmul(Zx, Dy));  // source terms of axes x, y
                 const float2 SB = cmul(Zx, Zy);                      // multiplies the z-axis term
                 const float gxy = f.gam_x[px] * f.gam_y[py];
-                float2 sigma = make_float2(0.f, 0.f);
-                if constexpr (!ADJ) sigma = f.sigma_tab[nstep];
+                // sigma_n times them: four FMAs per component and cell add the source
+                float2 SAs = SA, SBs = SB;
+                if constexpr (!ADJ) {
+                    const float2 sigma = f.sigma_tab[nstep];
+                    SAs = cmul(sigma, SA);
+                    SBs = cmul(sigma, SB);
+                }
                 GMEM const float2* __restrict__ fwd = nullptr;
                 GMEM float2* __restrict__ stash = nullptr;
                 if constexpr (ADJ) fwd = gmem(f.fwd_tab[nstep]);
@@ -631,27 +651,27 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    if (e < N && (!SEG || (e >= H && e < H + C))) {
+                    if (!SEG || (e >= H && e < H + C)) {
                         const int z = geo.g0 + e;
-                        const int64_t ad = geo.base + (int64_t)e * geo.estride;
-                        const float2 Lt = cadd(load_last<NTL>(Lbuf + ad), v[n1]);
-                        const float2 po = load_last<NTL>(psi_old + ad);
-                        float2 q = Lt;
-                        if constexpr (!POTX) q = cadd(q, cscale(raw[n1], vv[n1]));
+                        float2 q = cadd(load_last<NTL>(at_step(Lbuf + first, n1, step)), v[n1]);
+                        GMEM float2* pold = at_step(psi_old + first, n1, step);
+                        const float2 po = load_last<NTL>((GMEM const float2*)pold);
+                        if constexpr (!POTX) q = make_float2(fmaf(raw[n1].x, vv[n1], q.x), fmaf(raw[n1].y, vv[n1], q.y));
                         if constexpr (!ADJ) {
                             const float4 zd = t_zd[z];
-                            const float2 s = cadd(cmul(SA, make_float2(zd.x, zd.y)), cmul(SB, make_float2(zd.z, zd.w)));
-                            q = cadd(q, cmul(sigma, s));
+                            q = cmadd(SAs, make_float2(zd.x, zd.y), q);
+                            q = cmadd(SBs, make_float2(zd.z, zd.w), q);
                         }
                         const float g = gxy * t_gam[z];
                         // psi^{n+1} = Gamma (psi^{n-1} - i q)
                         const float2 nv = make_float2(g * (po.x + q.y), g * (po.y - q.x));
-                        psi_old[ad] = nv;
-                        if (stash) stash[ad] = nv;
+                        *pold = nv;
                         if constexpr (ADJ) {
                             // Im(chi^m psi^{m-1})
-                            const float2 fv = fwd[ad];
-                            f.grad[ad] += nv.x * fv.y + nv.y * fv.x;
+                            const float2 fv = *at_step(fwd + first, n1, step);
+                            *at_step(f.grad + first, n1, step / 2) += nv.x * fv.y + nv.y * fv.x;
+                        } else if (stash) {
+                            *at_step(stash + first, n1, step) = nv;
                         }
                     }
                 });
@@ -739,7 +759,7 @@ template <int N, int N1, int N2, int M1, int P, bool SEG>
 static hipError_t launch_shape(int axis, const PassArgs& single, const PassArgs* descs, const int* off, int ninst,
                                int tiles, int koff, hipStream_t stream) {
     if (ninst == 0) {
-        // unsegmented axes may take the potential in the x pass
+        // whole pencils along x and z take the potential in the x pass
         if (!SEG && single.potx) {
             if (axis == 0) return launch_kernel<N, N1, N2, M1, P, 0, false, false, false, true>(single, descs, off, 0, tiles, koff, stream);
             if (axis == 2) return launch_z<N, N1, N2, M1, P, false, false, true>(single, descs, off, 0, tiles, koff, stream);
