@@ -165,7 +165,8 @@ pstd_status pstd_run(pstd_solver* s, int64_t n_steps);
 /* Like pstd_run (without the graph), and also times every pass kernel with
  * a pair of HIP events around its launch on the solver's stream; the steps
  * are queued back to back and the events read at the end.  pass_ms_host[3]
- * receives the summed milliseconds of the x, y and z passes.  Synchronises. */
+ * receives the summed milliseconds of the x, y and z passes (where the x and
+ * y passes run in one launch its time is in the x slot).  Synchronises. */
 pstd_status pstd_run_timed(pstd_solver* s, int64_t n_steps, double* pass_ms_host);
 
 /* Pick, for each axis pass, the fastest compiled tile shape (FFT factor
@@ -174,7 +175,8 @@ pstd_status pstd_run_timed(pstd_solver* s, int64_t n_steps, double* pass_ms_host
  * candidate keeps the faster of its two timings); the solver's state is
  * not touched.  Candidates are compared in compiled order and a later one
  * replaces the current choice only when it is at least 3 % faster, so timing
- * noise does not flip the choice between runs.  Also captures the step graph
+ * noise does not flip the choice between runs.  Solvers whose x and y passes
+ * run in one launch take one shape for both.  Also captures the step graph
  * of the chosen shapes, so that the next pstd_run does not.  Synchronises.
  * ENOMEM if the scratch cannot be allocated. */
 pstd_status pstd_autotune(pstd_solver* s, int32_t reps);

@@ -160,26 +160,44 @@ void adjoint_args(const pstd_solver* s, const AdjointState* a, int axis, pstd::P
 }
 
 pstd_status launch_rec(pstd_solver* s, AdjointState* a, hipStream_t st, int count) {
-    for (int k = 0; k < count; ++k)
-        for (int axis = 0; axis < 3; ++axis) {
+    const bool xy = pstd::solver_xy(s);
+    for (int k = 0; k < count; ++k) {
+        if (xy) {
+            pstd::PassArgs px, py;
+            recompute_args(s, a, 0, px);
+            recompute_args(s, a, 1, py);
+            hipError_t e = pstd::launch_variant_xy(s->variant[0], px, py, false, k, st);
+            if (e) return hfail(s, e, "recompute pass");
+        }
+        for (int axis = xy ? 2 : 0; axis < 3; ++axis) {
             pstd::PassArgs pa;
             recompute_args(s, a, axis, pa);
             hipError_t e = pstd::launch_variant_single(s->variant[axis], false, axis, pa, k, st);
             if (e) return hfail(s, e, "recompute pass");
         }
+    }
     hipError_t e = pstd::launch_advance(s->ctr, 1, count, st);
     if (e) return hfail(s, e, "advance");
     return PSTD_OK;
 }
 
 pstd_status launch_adj(pstd_solver* s, AdjointState* a, hipStream_t st, int count) {
-    for (int k = 0; k < count; ++k)
-        for (int axis = 0; axis < 3; ++axis) {
+    const bool xy = pstd::solver_xy(s);
+    for (int k = 0; k < count; ++k) {
+        if (xy) {
+            pstd::PassArgs px, py;
+            adjoint_args(s, a, 0, px);
+            adjoint_args(s, a, 1, py);
+            hipError_t e = pstd::launch_variant_xy(s->variant[0], px, py, true, k, st);
+            if (e) return hfail(s, e, "adjoint pass");
+        }
+        for (int axis = xy ? 2 : 0; axis < 3; ++axis) {
             pstd::PassArgs pa;
             adjoint_args(s, a, axis, pa);
             hipError_t e = pstd::launch_variant_adjoint(s->variant[axis], axis, pa, k, st);
             if (e) return hfail(s, e, "adjoint pass");
         }
+    }
     hipError_t e = pstd::launch_advance(a->ctr_adj, 1, count, st);
     if (e) return hfail(s, e, "advance");
     return PSTD_OK;

@@ -431,7 +431,19 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
             for (int i = 1; i < 6; ++i) HIP_TRY(s, hipEventRecord(ev[i], stream));
         return PSTD_OK;
     }
-    for (int axis = 0; axis < 3; ++axis) {
+    const bool xy = pstd::solver_xy(s);
+    if (xy) {
+        // the x and y passes in one launch; its time goes to the x slot of the timers
+        pstd::PassArgs a, b;
+        pstd::solver_args(s, 0, a);
+        pstd::solver_args(s, 1, b);
+        if (ev) HIP_TRY(s, hipEventRecord(ev[0], stream));
+        hipError_t e = pstd::launch_variant_xy(s->variant[0], a, b, false, koff, stream);
+        if (e != hipSuccess) return hip_fail(s, e, "pass launch");
+        if (ev)
+            for (int i = 1; i < 4; ++i) HIP_TRY(s, hipEventRecord(ev[i], stream));
+    }
+    for (int axis = xy ? 2 : 0; axis < 3; ++axis) {
         pstd::PassArgs a;
         pstd::solver_args(s, axis, a);
         const bool seg = s->prob.sub_core[axis] > 0;
@@ -516,6 +528,7 @@ void solver_args(const pstd_solver* s, int axis, PassArgs& a) {
     a.buf[0] = s->buf[0];
     a.buf[1] = s->buf[1];
     a.L = s->L;
+    a.L2 = solver_xy(s) ? s->L2 : nullptr;
     a.pot = s->pot;
     a.potx = s->potx;
     a.nt = s->nt;
@@ -692,6 +705,14 @@ pstd_status solver_create(const pstd_problem* p, hipStream_t stream, int64_t* ex
     // Segmented x or z pencils take the z pass (segments of 48 + 2 8 points re-read
     // a third more than they update: 72.3 against 69.9 Gcell/s)
     s->potx = p->sub_core[0] == 0 && p->sub_core[2] == 0 ? 1 : 0;
+    // the x and y passes in one launch: axes of one length, whole pencils, one
+    // solver, and fields that stay in the cache with the array more (separate
+    // launches where that array cannot be had)
+    if (!ext_ctr && p->scheme == 0 && p->n[0] == p->n[1] && !p->sub_core[0] && !p->sub_core[1] && !p->sub_core[2] &&
+        32.0 * (double)s->cells <= kXyLaunchBytes && hipMalloc(&s->L2, s->cells * sizeof(float2)) != hipSuccess) {
+        s->L2 = nullptr;
+        (void)hipGetLastError();
+    }
     // fields (psi pair and L, 24 B per cell) beyond the Infinity Cache: the z
     // pass's last-use loads bypass it, which leaves it to the lines the next
     // pass reads (measured: 256^3 +6 %, 288^3 +1 %; within the cache the
@@ -722,16 +743,22 @@ pstd_status solver_create(const pstd_problem* p, hipStream_t stream, int64_t* ex
 // Time `reps` back-to-back launches of each given tile shape of one axis on
 // scratch state of the solver's size (the solver's own state is untouched);
 // ms_out[k] receives the average milliseconds per launch of shape ids[k].
+// axis kAxisXY: the x and y passes in one launch.
+constexpr int kAxisXY = -1;
 pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t reps, float* ms_out) {
-    float2 *tb0 = nullptr, *tb1 = nullptr, *tL = nullptr;
-    double2* tacc = nullptr;
+    float2 *tb0 = nullptr, *tb1 = nullptr, *tL = nullptr, *tL2 = nullptr;
+    double2 *tacc = nullptr, *tacc_y = nullptr;
+    const int ax0 = axis == kAxisXY ? 0 : axis;
+    const bool own = axis == kAxisXY || (axis == 2 && solver_xy(s));
     int64_t* tctr = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     auto release = [&]() {
         (void)hipFree(tb0);
         (void)hipFree(tb1);
         (void)hipFree(tL);
+        (void)hipFree(tL2);
         (void)hipFree(tacc);
+        (void)hipFree(tacc_y);
         (void)hipFree(tctr);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
@@ -739,10 +766,13 @@ pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t
     hipError_t e;
     if ((e = hipMalloc(&tb0, s->cells * sizeof(float2))) || (e = hipMalloc(&tb1, s->cells * sizeof(float2))) ||
         (e = hipMalloc(&tL, s->cells * sizeof(float2))) || (e = hipMalloc(&tctr, 2 * sizeof(int64_t))) ||
-        (e = hipMalloc(&tacc, 8 * s->points[axis] * sizeof(double2))) || (e = hipEventCreate(&e0)) ||
+        (own && (e = hipMalloc(&tL2, s->cells * sizeof(float2)))) ||
+        (axis == kAxisXY && (e = hipMalloc(&tacc_y, 8 * s->points[1] * sizeof(double2)))) ||
+        (axis == kAxisXY && (e = hipMemset(tacc_y, 0, 8 * s->points[1] * sizeof(double2)))) ||
+        (e = hipMalloc(&tacc, 8 * s->points[ax0] * sizeof(double2))) || (e = hipEventCreate(&e0)) ||
         (e = hipEventCreate(&e1)) || (e = hipMemset(tb0, 0, s->cells * sizeof(float2))) ||
         (e = hipMemset(tb1, 0, s->cells * sizeof(float2))) ||
-        (e = hipMemset(tacc, 0, 8 * s->points[axis] * sizeof(double2)))) {
+        (e = hipMemset(tacc, 0, 8 * s->points[ax0] * sizeof(double2)))) {
         release();
         return hip_fail(s, e, "timing scratch");
     }
@@ -772,27 +802,37 @@ pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t
         if (e) return hip_fail(s, e, "FDTD timing");
         return PSTD_OK;
     }
-    const bool seg = s->prob.sub_core[axis] > 0;
+    const bool seg = s->prob.sub_core[ax0] > 0;
     // two rounds over the candidates, the faster of each candidate's two
     // timings: the first candidates of a round may run before the clocks have
     // settled
     for (int k = 0; k < n; ++k) ms_out[k] = std::numeric_limits<float>::max();
     for (int round = 0; round < 2; ++round)
     for (int k = 0; k < n && !e; ++k) {
-        PassArgs a;
-        const int keep = s->variant[axis];
-        s->variant[axis] = ids[k];
-        solver_args(s, axis, a);
-        s->variant[axis] = keep;
-        a.buf[0] = tb0;
-        a.buf[1] = tb1;
-        a.L = tL;
-        a.acc = tacc;
-        a.ctr = tctr;
+        auto args_of = [&](int ax, double2* acc) {
+            PassArgs a;
+            const int keep = s->variant[ax];
+            s->variant[ax] = ids[k];
+            solver_args(s, ax, a);
+            s->variant[ax] = keep;
+            a.buf[0] = tb0;
+            a.buf[1] = tb1;
+            a.L = tL;
+            a.L2 = tL2;
+            a.acc = acc;
+            a.ctr = tctr;
+            return a;
+        };
+        const PassArgs a = args_of(ax0, tacc);
+        const PassArgs ay = axis == kAxisXY ? args_of(1, tacc_y) : PassArgs{};
+        auto launch = [&]() {
+            return axis == kAxisXY ? launch_variant_xy(ids[k], a, ay, false, 0, s->stream)
+                                   : launch_variant_single(ids[k], seg, axis, a, 0, s->stream);
+        };
         float ms = 0;
-        e = launch_variant_single(ids[k], seg, axis, a, 0, s->stream);
+        e = launch();
         if (!e) e = hipEventRecord(e0, s->stream);
-        for (int r = 0; r < reps && !e; ++r) e = launch_variant_single(ids[k], seg, axis, a, 0, s->stream);
+        for (int r = 0; r < reps && !e; ++r) e = launch();
         if (!e) e = hipEventRecord(e1, s->stream);
         if (!e) e = hipEventSynchronize(e1);
         if (!e) e = hipEventElapsedTime(&ms, e0, e1);
@@ -807,18 +847,22 @@ pstd_status solver_autotune(pstd_solver* s, int32_t reps) {
     // time every compiled tile shape of each axis and keep the fastest (the
     // FDTD step has one shape)
     if (s->prob.scheme == 1) return PSTD_OK;
-    for (int axis = 0; axis < 3; ++axis) {
+    // (solvers with L2 take one shape for x and y, timed in their one launch)
+    for (int axis = s->L2 ? 1 : 0; axis < 3; ++axis) {
+        const bool xy = s->L2 && axis == 1;
         const bool seg = s->prob.sub_core[axis] > 0;
         int ids[16];
         float ms[16];
         const int nv = std::min(16, pass_variants(local_len(s->prob, axis), seg, ids, 16));
+        if (xy) s->variant[0] = s->variant[1];
         if (nv <= 1) continue;
-        pstd_status st = time_shapes(s, axis, ids, nv, reps, ms);
+        pstd_status st = time_shapes(s, xy ? kAxisXY : axis, ids, nv, reps, ms);
         if (st) return st;
         int best = 0;
         for (int k = 1; k < nv; ++k)
             if (ms[k] < 0.97f * ms[best]) best = k;  // a later shape must win clearly: stable choices
         s->variant[axis] = ids[best];
+        if (xy) s->variant[0] = ids[best];
     }
     solver_drop_graph(s);
     return PSTD_OK;
@@ -1362,6 +1406,7 @@ pstd_status pstd_destroy(pstd_solver* s) {
     (void)hipFree(s->buf[0]);
     (void)hipFree(s->buf[1]);
     (void)hipFree(s->L);
+    (void)hipFree(s->L2);
     (void)hipFree(s->vbox);
     (void)hipFree(s->v2full);
     (void)hipFree(s->wr);

@@ -39,6 +39,8 @@ struct PotentialArgs {
 struct PassArgs {
     float2* buf[2];            // psi ping-pong
     float2* L;                 // kinetic accumulator (scaled by 2 eta dtau)
+    float2* L2;                // null, or the y term's own array (x and y passes in one launch, and
+                               // their z pass)
     PotentialArgs pot;
     int potx;                  // 1: the x pass takes the potential term (x and z unsegmented), else
                                // the z pass
@@ -120,6 +122,16 @@ hipError_t launch_variant(int v, bool segmented, int axis, const PassArgs* descs
 constexpr double kInfinityCacheBytes = 256.0 * 1024 * 1024;
 // Launch variant v for one instance described by `args` (passed by value)
 hipError_t launch_variant_single(int v, bool segmented, int axis, const PassArgs& args, int koff, hipStream_t stream);
+// The x and y passes of variant v (nx = ny = its length, no segments) in one
+// launch, the y term in ay.L2; the z pass of the same step takes L2 too
+hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff,
+                             hipStream_t stream);
+// The largest fields (psi pair, L and L2, 32 B per cell) whose x and y passes
+// run in one launch: the array more has to stay in the Infinity Cache.
+// Measured, separate passes against one launch: 160 x 160 x 192 (157 MB) 69.0 and
+// 61.5 us per step, 180^3 (187 MB) 81.5 and 75.8, 192^3 (226 MB) 90.6 and
+// 102.1, 256^3 (537 MB) 224 and 229.
+constexpr double kXyLaunchBytes = 200e6;
 // Adjoint step pass (plain pencils, one instance)
 hipError_t launch_variant_adjoint(int v, int axis, const PassArgs& args, int koff, hipStream_t stream);
 // acc64[i] += acc32[i]; acc32[i] = 0

@@ -15,12 +15,13 @@ struct VariantEntry {
     LaunchFn plain;
     LaunchFn seg;  // null when the shape has no segmented instance
     AdjFn adj;
+    XyFn xy;
 };
 
 const VariantEntry kVariants[] = {
 #define PSTD_ENTRY(N_, A_, B_, M_, P_, S_, PART_)                                                              \
     {PassShape{N_, A_, B_, P_, P_ * (A_ > B_ ? A_ : B_), M_}, &PSTD_FN(plain, N_, A_, B_, M_, P_),                  \
-     (S_) ? &PSTD_FN(seg, N_, A_, B_, M_, P_) : nullptr, &PSTD_FN(adj, N_, A_, B_, M_, P_)},
+     (S_) ? &PSTD_FN(seg, N_, A_, B_, M_, P_) : nullptr, &PSTD_FN(adj, N_, A_, B_, M_, P_), &PSTD_FN(xy, N_, A_, B_, M_, P_)},
     PSTD_VARIANTS(PSTD_ENTRY)
 #undef PSTD_ENTRY
 };
@@ -70,6 +71,13 @@ hipError_t launch_variant_single(int v, bool segmented, int axis, const PassArgs
     LaunchFn f = segmented ? kVariants[v].seg : kVariants[v].plain;
     if (!f) return hipErrorInvalidValue;
     return f(axis, args, nullptr, nullptr, 0, args.tiles, koff, stream);
+}
+
+hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff,
+                             hipStream_t stream) {
+    const int N = v < 0 || v >= kNumVariants ? 0 : kVariants[v].shape.N;
+    if (ax.nx != N || ax.ny != N || !ax.L2 || !ay.L2) return hipErrorInvalidValue;
+    return kVariants[v].xy(ax, ay, adjoint, koff, stream);
 }
 
 hipError_t launch_variant_adjoint(int v, int axis, const PassArgs& args, int koff, hipStream_t stream) {

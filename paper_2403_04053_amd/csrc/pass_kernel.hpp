@@ -31,6 +31,13 @@
 // Where x and z are whole pencils (PassArgs::potx) the x pass takes the
 // potential term instead, on the rows that cross the box, and the z pass
 // holds no copy of psi^n through its transforms.
+//
+// x and y in one launch (pass_xy_kernel; both axes of one length and shape):
+// the two terms do not depend on each other, so the y tiles write theirs to
+// an array of their own (PassArgs::L2), x and y tiles of the same planes run
+// side by side (psi^n is fetched from beyond the L2 once for both), and the
+// z pass adds the two, in the order of the separate passes, so the results
+// are the same to the bit.
 // Inside the DFT window each pass also accumulates, in FP64 with Neumaier
 // compensation, the DFT of psi and of its spectral normal derivative on the
 // two planes normal to its axis (Eqs. psiphasor, dpsiphasor).
@@ -102,6 +109,7 @@ struct Fields {
     GMEM float2* buf0;
     GMEM float2* buf1;
     GMEM float2* L;
+    GMEM float2* L2;
     GMEM const float* vbox;
     int vlo0, vlo1, vlo2, vn0, vn1, vn2;
     GMEM const float *wr0, *wr1, *wr2;
@@ -134,6 +142,7 @@ __device__ __forceinline__ Fields fields(const PassArgs& a) {
     f.buf0 = gmem(a.buf[0]);
     f.buf1 = gmem(a.buf[1]);
     f.L = gmem(a.L);
+    f.L2 = gmem(a.L2);
     f.vbox = gmem(a.pot.box);
     f.vlo0 = a.pot.lo[0];
     f.vlo1 = a.pot.lo[1];
@@ -272,56 +281,53 @@ __device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ p, int
     }
 }
 
-// One workgroup per tile of P pencils; MULTI launches find their instance
-// from the prefix table of tiles.
-template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool MULTI, bool ADJ, bool POTX = false,
-          bool NTL = false>
-__global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs single,
-                                                                       const PassArgs* __restrict__ descs,
-                                                                       const int* __restrict__ off, int ninst,
-                                                                       int koff) {
-    constexpr int NT = P * (N1 > N2 ? N1 : N2);
-    constexpr int ROW = N2 + 1;                 // padded exchange row
+// LDS layout of one tile of P pencils
+template <int N, int N1, int N2>
+struct TileLds {
+    static constexpr int ROW = N2 + 1;          // padded exchange row
     // odd pencil stride (float2); also holds the four DFT partials per thread
-    constexpr int STRIDE = (N1 * ROW > 4 * N2 ? N1 * ROW : 4 * N2) | 1;
-    __shared__ float2 ex[P * STRIDE];
-    __shared__ float2 s_tw[N];
-    __shared__ float s_kk[N];
+    static constexpr int STRIDE = (N1 * ROW > 4 * N2 ? N1 * ROW : 4 * N2) | 1;
     // derivative rows of the surface planes: staged in LDS where that costs
     // no occupancy (N <= 200), read from global memory otherwise
-    constexpr bool kRowsInLds = N <= 200;
-    __shared__ float2 s_dl[kRowsInLds ? N : 1], s_dh[kRowsInLds ? N : 1];
+    static constexpr bool kRows = N <= 200;
+    static constexpr int ROWS = kRows ? N : 1;
+};
+// the arrays of a kernel, each its own object so that the compiler knows
+// that they do not overlap (as members of one struct the twiddle reads waited
+// for the exchange writes: 2-4 % of a pass)
+#define PSTD_TILE_LDS(N, N1, N2, P)                    \
+    __shared__ float2 ex[P * TileLds<N, N1, N2>::STRIDE]; \
+    __shared__ float2 s_tw[N];                         \
+    __shared__ float s_kk[N];                          \
+    __shared__ float2 s_dl[TileLds<N, N1, N2>::ROWS], s_dh[TileLds<N, N1, N2>::ROWS];
+
+// Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8); give each
+// XCD a contiguous run of [0, G) instead, so that neighbouring tiles, which
+// share cache lines, meet in the same L2.  A bijection of [0, G); back: the
+// run walked backwards.
+__device__ __forceinline__ int xcd_tile(bool back) {
+    const int G = (int)gridDim.x, gb = (int)blockIdx.x, xcd = gb & 7;
+    const int run0 = xcd * (G >> 3) + min(xcd, G & 7), runlen = (G >> 3) + (xcd < (G & 7) ? 1 : 0);
+    return run0 + (back ? runlen - 1 - (gb >> 3) : (gb >> 3));
+}
+
+// The work of one workgroup on one tile of P pencils along AXIS.  OWN: the y
+// pass writes its term to an array of its own (f.L2) instead of adding to L,
+// so that it does not depend on the x pass; the z pass adds both.
+template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool ADJ, bool POTX, bool NTL, bool OWN>
+__device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, float2* __restrict__ ex,
+                                          float2* __restrict__ s_tw, float* __restrict__ s_kk,
+                                          float2* __restrict__ s_dl, float2* __restrict__ s_dh) {
+    constexpr int NT = P * (N1 > N2 ? N1 : N2);
+    constexpr int ROW = TileLds<N, N1, N2>::ROW;
+    constexpr int STRIDE = TileLds<N, N1, N2>::STRIDE;
+    constexpr bool kRowsInLds = TileLds<N, N1, N2>::kRows;
 
     const int t = threadIdx.x;
     const bool activeA = t < P * N2;
     const int pA = AXIS == 0 ? t / N2 : t % P;
     const int n2 = AXIS == 0 ? t % N2 : t / P;
 
-    // Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8); give
-    // each XCD a contiguous run of tiles instead, so that neighbouring tiles,
-    // which share cache lines (the 4-byte potential of a 16-pencil tile is
-    // half a 128-byte line), meet in the same L2.  A bijection of [0, G).
-    // The y pass walks each XCD's run backwards: the x pass gave that XCD the
-    // same planes and ended on the lines it wrote last, which are still in
-    // its L2 and in the Infinity Cache.
-    const int G = (int)gridDim.x, gb = (int)blockIdx.x, xcd = gb & 7;
-    const int run0 = xcd * (G >> 3) + min(xcd, G & 7), runlen = (G >> 3) + (xcd < (G & 7) ? 1 : 0);
-    const int gt = run0 + (AXIS == 1 && !MULTI ? runlen - 1 - (gb >> 3) : (gb >> 3));
-
-    // instance of this workgroup (uniform), its tile, its step: the base
-    // counter plus this launch's offset in its group of steps
-    Fields f;
-    int tile;
-    if constexpr (!MULTI) {
-        f = fields<AXIS>(single);
-        tile = gt;
-    } else {
-        int inst = 0;
-        for (int i = 1; i < ninst; ++i)
-            if (gt >= off[i]) inst = i;
-        f = fields<AXIS>(descs[inst]);
-        tile = gt - off[inst];
-    }
     const int64_t nstep = f.ctr[0] + koff;
     if (nstep >= f.ctr[1]) return;  // whole workgroup, before any barrier
     const bool surf = f.dft_tab[nstep] != 0;
@@ -362,7 +368,7 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
         // (the other way round there cost 2-3 %)
         float2 Lin[N1];
         auto load_L = [&]() {
-            if constexpr (AXIS == 1) {
+            if constexpr (AXIS == 1 && !OWN) {
                 GMEM const float2* Lp = f.L + first;
                 unroll<N1>([&](auto i) { Lin[decltype(i)::value] = make_float2(0.f, 0.f); });
                 if constexpr (!SEG) {
@@ -606,7 +612,11 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    if (!SEG || (e >= H && e < H + C)) *at_step(Lbuf + first, n1, step) = cadd(Lin[n1], v[n1]);
+                    if constexpr (OWN) {
+                        *at_step(f.L2 + first, n1, step) = v[n1];
+                    } else {
+                        if (!SEG || (e >= H && e < H + C)) *at_step(Lbuf + first, n1, step) = cadd(Lin[n1], v[n1]);
+                    }
                 });
             } else {
                 GMEM const float* __restrict__ t_gam = f.gam;
@@ -653,7 +663,9 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
                     const int e = n2 + N2 * n1;
                     if (!SEG || (e >= H && e < H + C)) {
                         const int z = geo.g0 + e;
-                        float2 q = cadd(load_last<NTL>(at_step(Lbuf + first, n1, step)), v[n1]);
+                        float2 q = load_last<NTL>((GMEM const float2*)at_step(Lbuf + first, n1, step));
+                        if constexpr (OWN) q = cadd(q, load_last<NTL>((GMEM const float2*)at_step(f.L2 + first, n1, step)));
+                        q = cadd(q, v[n1]);
                         GMEM float2* pold = at_step(psi_old + first, n1, step);
                         const float2 po = load_last<NTL>((GMEM const float2*)pold);
                         if constexpr (!POTX) q = make_float2(fmaf(raw[n1].x, vv[n1], q.x), fmaf(raw[n1].y, vv[n1], q.y));
@@ -730,16 +742,64 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
     }
 }
 
+// One workgroup per tile of P pencils; MULTI launches find their instance
+// from the prefix table of tiles (each instance's step: the base counter plus
+// this launch's offset in its group of steps).  The y pass walks each XCD's
+// run backwards: the x pass gave that XCD the same planes and ended on the
+// lines it wrote last, which are still in the Infinity Cache.
+template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool MULTI, bool ADJ, bool POTX = false,
+          bool NTL = false, bool OWN = false>
+__global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs single,
+                                                                       const PassArgs* __restrict__ descs,
+                                                                       const int* __restrict__ off, int ninst,
+                                                                       int koff) {
+    PSTD_TILE_LDS(N, N1, N2, P)
+    const int gt = xcd_tile(AXIS == 1 && !MULTI);
+    if constexpr (!MULTI) {
+        const Fields f = fields<AXIS>(single);
+        pass_tile<N, N1, N2, M1, P, AXIS, SEG, ADJ, POTX, NTL, OWN>(f, gt, koff, ex, s_tw, s_kk, s_dl, s_dh);
+    } else {
+        int inst = 0;
+        for (int i = 1; i < ninst; ++i)
+            if (gt >= off[i]) inst = i;
+        const Fields f = fields<AXIS>(descs[inst]);
+        pass_tile<N, N1, N2, M1, P, AXIS, SEG, ADJ, POTX, NTL, OWN>(f, gt - off[inst], koff, ex, s_tw, s_kk, s_dl, s_dh);
+    }
+}
+
+// The x and y passes of one solver in one launch (axes of one length, whole
+// pencils): x tiles and y tiles of the same planes by turns, so that loads,
+// transforms and stores of tiles at different stages overlap and psi^n is
+// read beyond the L2 once (24 instead of 40 B per cell of the two passes, 8 B
+// more in the z pass).  160^3: 23.2 us against 14.0 + 16.8 us and a launch
+// between them, z pass 22.8 -> 28.0 us, step 59.3 -> 52.7 us; 48^3: 16.1 ->
+// 12.4 us.
+template <int N, int N1, int N2, int M1, int P, bool ADJ>
+__global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_xy_kernel(PassArgs ax, PassArgs ay, int koff) {
+    PSTD_TILE_LDS(N, N1, N2, P)
+    const int gt = xcd_tile(false);
+    const int both = 2 * min(ax.tiles, ay.tiles);
+    const bool isy = gt < both ? (gt & 1) : ay.tiles > ax.tiles;
+    const int tile = gt < both ? gt >> 1 : gt - (both >> 1);
+    if (!isy) {
+        const Fields f = fields<0>(ax);
+        pass_tile<N, N1, N2, M1, P, 0, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dl, s_dh);
+    } else {
+        const Fields f = fields<1>(ay);
+        pass_tile<N, N1, N2, M1, P, 1, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dl, s_dh);
+    }
+}
+
 using LaunchFn = hipError_t (*)(int axis, const PassArgs& single, const PassArgs* descs, const int* off, int ninst,
                                 int tiles, int koff, hipStream_t stream);
 
 template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool MULTI, bool ADJ, bool POTX = false,
-          bool NTL = false>
+          bool NTL = false, bool OWN = false>
 hipError_t launch_kernel(const PassArgs& single, const PassArgs* descs, const int* off, int ninst, int tiles,
                          int koff, hipStream_t stream) {
     constexpr int threads = P * (N1 > N2 ? N1 : N2);
     if (tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL((pass_kernel<N, N1, N2, M1, P, AXIS, SEG, MULTI, ADJ, POTX, NTL>), dim3(tiles), dim3(threads), 0,
+    hipLaunchKernelGGL((pass_kernel<N, N1, N2, M1, P, AXIS, SEG, MULTI, ADJ, POTX, NTL, OWN>), dim3(tiles), dim3(threads), 0,
                        stream, single, descs, off, ninst, koff);
     return hipGetLastError();
 }
@@ -748,6 +808,12 @@ hipError_t launch_kernel(const PassArgs& single, const PassArgs* descs, const in
 template <int N, int N1, int N2, int M1, int P, bool SEG, bool MULTI, bool POTX>
 hipError_t launch_z(const PassArgs& single, const PassArgs* descs, const int* off, int ninst, int tiles, int koff,
                     hipStream_t stream) {
+    // L2 is set within the Infinity Cache only, where nt is not
+    if constexpr (!SEG && !MULTI && POTX) {
+        if (single.L2)
+            return launch_kernel<N, N1, N2, M1, P, 2, false, false, false, true, false, true>(single, descs, off, ninst,
+                                                                                               tiles, koff, stream);
+    }
     if (single.nt)
         return launch_kernel<N, N1, N2, M1, P, 2, SEG, MULTI, false, POTX, true>(single, descs, off, ninst, tiles, koff,
                                                                                   stream);
@@ -777,13 +843,29 @@ static hipError_t launch_shape(int axis, const PassArgs& single, const PassArgs*
     return launch_z<N, N1, N2, M1, P, SEG, true, false>(single, descs, off, ninst, tiles, koff, stream);
 }
 
+// adjoint steps: whole pencils on every axis, so the x pass takes the potential
 template <int N, int N1, int N2, int M1, int P>
 static hipError_t launch_adjoint_shape(int axis, const PassArgs& a, int koff, hipStream_t stream) {
-    if (axis == 0) return launch_kernel<N, N1, N2, M1, P, 0, false, false, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
-    if (axis == 1) return launch_kernel<N, N1, N2, M1, P, 1, false, false, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
-    return launch_kernel<N, N1, N2, M1, P, 2, false, false, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
+    if (axis == 0) return launch_kernel<N, N1, N2, M1, P, 0, false, false, true, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
+    if (axis == 1) return launch_kernel<N, N1, N2, M1, P, 1, false, false, true, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
+    if (a.L2) return launch_kernel<N, N1, N2, M1, P, 2, false, false, true, true, false, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
+    return launch_kernel<N, N1, N2, M1, P, 2, false, false, true, true>(a, nullptr, nullptr, 0, a.tiles, koff, stream);
 }
 
+// the x and y passes in one launch, of forward or adjoint steps
+template <int N, int N1, int N2, int M1, int P>
+static hipError_t launch_xy_shape(const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff, hipStream_t stream) {
+    constexpr int threads = P * (N1 > N2 ? N1 : N2);
+    if (adjoint)
+        hipLaunchKernelGGL((pass_xy_kernel<N, N1, N2, M1, P, true>), dim3(ax.tiles + ay.tiles), dim3(threads), 0, stream,
+                           ax, ay, koff);
+    else
+        hipLaunchKernelGGL((pass_xy_kernel<N, N1, N2, M1, P, false>), dim3(ax.tiles + ay.tiles), dim3(threads), 0, stream,
+                           ax, ay, koff);
+    return hipGetLastError();
+}
+
+using XyFn = hipError_t (*)(const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff, hipStream_t stream);
 using AdjFn = hipError_t (*)(int axis, const PassArgs& a, int koff, hipStream_t stream);
 
 template <int S, int N, int N1, int N2, int M1, int P>
@@ -800,7 +882,8 @@ hipError_t launch_segmented_shape(int axis, const PassArgs& single, const PassAr
                                                  hipStream_t);                                                   \
     hipError_t PSTD_FN(seg, N_, A_, B_, M_, P_)(int, const PassArgs&, const PassArgs*, const int*, int, int, int,   \
                                                hipStream_t);                                                     \
-    hipError_t PSTD_FN(adj, N_, A_, B_, M_, P_)(int, const PassArgs&, int, hipStream_t);
+    hipError_t PSTD_FN(adj, N_, A_, B_, M_, P_)(int, const PassArgs&, int, hipStream_t);                               \
+    hipError_t PSTD_FN(xy, N_, A_, B_, M_, P_)(const PassArgs&, const PassArgs&, bool, int, hipStream_t);
 #define PSTD_DEFINE_SHAPE(N_, A_, B_, M_, P_, S_)                                                                   \
     hipError_t PSTD_FN(plain, N_, A_, B_, M_, P_)(int axis, const PassArgs& single, const PassArgs* descs,            \
                                                  const int* off, int ninst, int tiles, int koff, hipStream_t stream) { \
@@ -812,6 +895,10 @@ hipError_t launch_segmented_shape(int axis, const PassArgs& single, const PassAr
     }                                                                                                              \
     hipError_t PSTD_FN(adj, N_, A_, B_, M_, P_)(int axis, const PassArgs& args, int koff, hipStream_t stream) {       \
         return launch_adjoint_shape<N_, A_, B_, M_, P_>(axis, args, koff, stream);                                    \
+    }                                                                                                              \
+    hipError_t PSTD_FN(xy, N_, A_, B_, M_, P_)(const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff,        \
+                                              hipStream_t stream) {                                                \
+        return launch_xy_shape<N_, A_, B_, M_, P_>(ax, ay, adjoint, koff, stream);                                    \
     }
 
 }  // namespace pstd

@@ -31,6 +31,7 @@ struct pstd_solver {
     int64_t win_steps = 0; // window steps run so far
     float2* buf[2] = {nullptr, nullptr};
     float2* L = nullptr;
+    float2* L2 = nullptr;  // the y term of solvers whose x and y passes run in one launch, else null
     float* vbox = nullptr;       // 2 dtau V / E0 on the taper's core
     float* wr = nullptr;         // complex absorber: 2 dtau w_a per axis (null without it)
     pstd::PotentialArgs pot{};
@@ -77,6 +78,8 @@ void solver_args(const pstd_solver* s, int axis, PassArgs& a);
 void solver_account_steps(pstd_solver* s, int64_t from, int64_t to);
 pstd_status solver_autotune(pstd_solver* s, int32_t reps);
 void solver_drop_graph(pstd_solver* s);
+// the x and y passes run in one launch (solver_args then sets PassArgs::L2)
+inline bool solver_xy(const pstd_solver* s) { return s->L2 && s->variant[0] == s->variant[1]; }
 // the misfit forward run no longer matches the solver state
 void adjoint_invalidate(pstd_solver* s);
 void adjoint_free(pstd_solver* s);

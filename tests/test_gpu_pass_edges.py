@@ -1,5 +1,6 @@
-"""GPU tests of the pass launches that depend on the grid's shape: the place of
-the potential term with segments along some axes."""
+"""GPU tests of the pass launches that depend on the grid's shape: the x and y
+passes in one launch against the separate ones (a batch instance always takes
+those), and the place of the potential term with segments along some axes."""
 import numpy as np
 import pytest
 
@@ -15,6 +16,27 @@ def P():
     assert torch.cuda.is_available()
     import paper_2403_04053_amd as mod
     return mod
+
+
+@pytest.mark.parametrize("n", [(24, 24, 20), (20, 20, 24), (40, 40, 32), (100, 100, 24), (150, 150, 20), (162, 162, 24)])
+@pytest.mark.parametrize("real", [0.0, -0.5])
+def test_xy_launch_equals_separate_passes(P, n, real):
+    """Lengths that leave part of a tile of x rows or y columns empty, small
+    tiles and large; the sums are the same operations in the same order, so
+    psi and the phasors are equal to the bit."""
+    prob, V = synth.tiny(n=n, P=3, transition=2, v0=0.5, radius_cells=3, steps=5, dft=(1, 4), theta=0.7, phi=0.3)
+    prob = prob.replace(ramp_periods=0.1, abc_UR=real)
+    a, b = synth.random_state(n, 1), synth.random_state(n, 2)
+    one = P.Solver(prob)
+    many = P.Batch([prob])
+    inst = many.instance(0)
+    for s in (one, inst):
+        s.set_potential(V)
+        s.set_state(a, b, 1)
+    one.run(5)
+    many.run(5)
+    assert torch.equal(one.psi(), inst.psi()) and torch.equal(one.psi(1), inst.psi(1))
+    assert torch.equal(one.phasors(), inst.phasors())
 
 
 @pytest.mark.parametrize("core", [(0, 16, 16), (16, 0, 16), (16, 16, 0), (0, 0, 16), (16, 0, 0)])
