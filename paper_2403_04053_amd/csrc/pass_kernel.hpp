@@ -262,20 +262,23 @@ __device__ __forceinline__ GMEM const T* at_step(GMEM const T* p, int n1, int64_
     return (GMEM const T*)((GMEM const char*)p + (int64_t)n1 * step);
 }
 
-// raw pencil values of one tile (zero outside the grid and for idle lanes);
-// p: the thread's element 0.  Whole-axis pencils lie inside the grid as a
-// whole, so one branch covers a thread's loads.
+// raw pencil values of one tile; p: the thread's element 0.  A segment's
+// values are zero outside the grid.  Whole-axis pencils lie inside the grid
+// as a whole: threads without one (the last tile's, or idle in stage A) read
+// the pencil of the grid's first cell, whose values they
+// carry through the transforms and never store, so that no branch parts a
+// wave's loads from what was issued before them.
 template <int N, int N1, int N2, bool SEG, bool NTL = false>
 __device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ p, int64_t step, const TileGeo& g, int n2,
                                           float2 (&x)[N1]) {
     static_assert(N == N1 * N2, "pencil factors");
-    unroll<N1>([&](auto i) { x[decltype(i)::value] = make_float2(0.f, 0.f); });
     if constexpr (!SEG) {
-        if (g.valid) unroll<N1>([&](auto i) { x[decltype(i)::value] = load_last<NTL>(at_step(p, decltype(i)::value, step)); });
+        unroll<N1>([&](auto i) { x[decltype(i)::value] = load_last<NTL>(at_step(p, decltype(i)::value, step)); });
     } else {
         unroll<N1>([&](auto i) {
             constexpr int n1 = decltype(i)::value;
             const int e = g.g0 + n2 + N2 * n1;
+            x[n1] = make_float2(0.f, 0.f);
             if (g.valid && e >= 0 && e < g.Ng) x[n1] = load_last<NTL>(at_step(p, n1, step));
         });
     }
@@ -330,19 +333,39 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
 
     const int64_t nstep = f.ctr[0] + koff;
     if (nstep >= f.ctr[1]) return;  // whole workgroup, before any barrier
-    const bool surf = f.dft_tab[nstep] != 0;
     GMEM const float2* __restrict__ psi = (nstep & 1) ? f.buf1 : f.buf0;
     GMEM float2* __restrict__ psi_old = (nstep & 1) ? f.buf0 : f.buf1;
 
-    // tables to LDS (issued before the field loads)
-    for (int i = t; i < N; i += NT) {
-        s_tw[i] = f.tw[i];
-        s_kk[i] = f.kk[i];
-        if (kRowsInLds && surf) {
+    // Start of a tile: tables into registers, then the field loads, then the
+    // tables into LDS, so that one memory latency covers both (waiting for the
+    // tables first cost a latency per workgroup, on launches whose workgroups
+    // all start together the whole of it).  Indexes past the end repeat the
+    // last entry: the loads and LDS writes need no branch.
+    constexpr int TR = (N + NT - 1) / NT;  // table entries per thread
+    float2 r_tw[TR];
+    float r_kk[TR];
+    unroll<TR>([&](auto i) {
+        const int j = min(t + decltype(i)::value * NT, N - 1);
+        r_tw[decltype(i)::value] = f.tw[j];
+        r_kk[decltype(i)::value] = f.kk[j];
+    });
+    const TileGeo geo = tile_geo<N, P, AXIS, SEG>(f, tile, pA, activeA);
+    // this thread's element 0 (a whole pencil's first one for threads without a pencil)
+    const int64_t first = SEG || geo.valid ? geo.base + (int64_t)n2 * geo.estride : 0;
+    const int64_t step = (int64_t)(N2 * sizeof(float2)) * geo.estride;  // bytes between its elements
+    float2 raw[N1];
+    load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi + first, step, geo, n2, raw);
+    unroll<TR>([&](auto i) {
+        const int j = min(t + decltype(i)::value * NT, N - 1);
+        s_tw[j] = r_tw[decltype(i)::value];
+        s_kk[j] = r_kk[decltype(i)::value];
+    });
+    const bool surf = f.dft_tab[nstep] != 0;
+    if (kRowsInLds && surf)
+        for (int i = t; i < N; i += NT) {
             s_dl[i] = f.dlo[i];
             s_dh[i] = f.dhi[i];
         }
-    }
     // entry e of the low (hi = false) or high plane's derivative row
     auto drow = [&](bool hi, int e) -> float2 {
         if constexpr (kRowsInLds) {
@@ -354,11 +377,6 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
     };
 
     {
-        const TileGeo geo = tile_geo<N, P, AXIS, SEG>(f, tile, pA, activeA);
-        const int64_t first = geo.base + (int64_t)n2 * geo.estride;        // this thread's element 0
-        const int64_t step = (int64_t)(N2 * sizeof(float2)) * geo.estride;  // bytes between its elements
-        float2 raw[N1];
-        load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi + first, step, geo, n2, raw);
         // the y pass's epilogue operand (L from the x pass), the same elements
         // the epilogue writes, read by the thread that writes them.  Issued
         // once stage A is done, the field loads have the memory system to
@@ -369,6 +387,8 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
         float2 Lin[N1];
         auto load_L = [&]() {
             if constexpr (AXIS == 1 && !OWN) {
+                // (the branch on geo.valid keeps these loads here: without it the
+                // compiler issues them with the field loads, 103 instead of 85 VGPRs)
                 GMEM const float2* Lp = f.L + first;
                 unroll<N1>([&](auto i) { Lin[decltype(i)::value] = make_float2(0.f, 0.f); });
                 if constexpr (!SEG) {
