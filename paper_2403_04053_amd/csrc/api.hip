@@ -18,6 +18,11 @@ namespace {
 
 constexpr double kPi = 3.141592653589793238462643383279502884;
 constexpr int kGraphSteps = 16;  // steps per replayed graph
+// Box surface: launch groups of at least this many steps stage their plane
+// values (8 B written per value and step, then one flush) instead of a
+// compensated FP64 sum read and written per value and step (64 B, at the end
+// of every workgroup's life); shorter groups would pay the flush's launch.
+constexpr int kStageMin = 4;
 
 thread_local std::string g_create_error;
 
@@ -262,11 +267,11 @@ void taper(const pstd_problem& p, int a, double dxb, int i, double* z, double* z
 
 pstd_status build_tables(pstd_solver* s) {
     const pstd_problem& p = s->prob;
-    // per axis: kk[Nl] f, wloc[Nl] f, tw[Nl] f2, dlo[Nl] f2, dhi[Nl] f2 (local length Nl),
+    // per axis: kk[Nl] f, wloc[Nl] f, tw[Nl] f2, dr[Nl] f2 (local length Nl),
     //           gam[N] f, zt[N] f2, dz[N] f2, zd[N] f4 (global length N)
     size_t bytes = 0;
     for (int a = 0; a < 3; ++a)
-        bytes += (size_t)local_len(p, a) * (2 * sizeof(float) + 3 * sizeof(float2)) +
+        bytes += (size_t)local_len(p, a) * (2 * sizeof(float) + 2 * sizeof(float2)) +
                  (size_t)p.n[a] * (sizeof(float) + 2 * sizeof(float2) + sizeof(float4)) + 16 * 9;
     HIP_TRY(s, hipMalloc(&s->tables, bytes));
     char* cur = (char*)s->tables;
@@ -275,7 +280,8 @@ pstd_status build_tables(pstd_solver* s) {
         const int Nl = local_len(p, a);
         const double dxb = s->dxb[a];
         std::vector<float> kk(Nl), wl(Nl, 1.0f), gam(N);
-        std::vector<float2> tw(Nl), zt(N), dz(N), dlo(Nl), dhi(Nl);
+        std::vector<float2> tw(Nl), zt(N), dz(N), dr(Nl);
+        float ny[2];
         for (int m = 0; m < Nl; ++m) {
             const double k = kbar_of(m, Nl, dxb);
             kk[m] = (float)(2.0 * s->eta * s->dtau * k * k / Nl);
@@ -324,22 +330,18 @@ pstd_status build_tables(pstd_solver* s) {
                 dz[i] = make_float2((float)(f * (cr * er - ci * ei)), (float)(f * (cr * ei + ci * er)));
             }
         }
-        // spectral-derivative rows: d(e) = (1/Nl) sum_m i kbar_m exp(2 pi i m (i0 - e)/Nl)
+        // spectral-derivative rows: d(e) = (1/Nl) sum_m i kbar_m exp(2 pi i m (i0 - e)/Nl).  Indexes
+        // m and Nl - m pair to a real sum; the Nyquist index alone gives i kbar (-1)^(i0 - e) / Nl
         for (int side = 0; side < 2; ++side) {
             int seg, i0;
             plane_local(p, a, side, &seg, &i0);
-            std::vector<float2>& row = side == 0 ? dlo : dhi;
             for (int e = 0; e < Nl; ++e) {
-                double re = 0, im = 0;
-                for (int m = 0; m < Nl; ++m) {
-                    const double k = kbar_of(m, Nl, dxb);
-                    const double ang = 2 * kPi * (double)(((int64_t)m * (i0 - e)) % Nl) / Nl;
-                    // i k e^{i ang}
-                    re += -k * std::sin(ang);
-                    im += k * std::cos(ang);
-                }
-                row[e] = make_float2((float)(re / Nl), (float)(im / Nl));
+                double re = 0;
+                for (int m = 1; m < Nl / 2; ++m)
+                    re -= kbar_of(m, Nl, dxb) * std::sin(2 * kPi * (double)(((int64_t)m * (i0 - e)) % Nl) / Nl);
+                (side == 0 ? dr[e].x : dr[e].y) = (float)(2 * re / Nl);
             }
+            ny[side] = (float)(kbar_of(Nl / 2, Nl, dxb) / Nl) * (i0 & 1 ? -1.f : 1.f);
         }
         auto place = [&](auto& vec) {
             using T = typename std::decay_t<decltype(vec)>::value_type;
@@ -356,14 +358,13 @@ pstd_status build_tables(pstd_solver* s) {
         std::vector<float4> zd(N);
         for (int i = 0; i < N; ++i) zd[i] = make_float4(zt[i].x, zt[i].y, dz[i].x, dz[i].y);
         float4* d_zd = place(zd);
-        float2* d_dlo = place(dlo);
-        float2* d_dhi = place(dhi);
+        float2* d_dr = place(dr);
         pstd_status st;
         if ((st = upload(s, d_kk, kk)) || (st = upload(s, d_wl, wl)) || (st = upload(s, d_gam, gam)) ||
             (st = upload(s, d_tw, tw)) || (st = upload(s, d_zt, zt)) || (st = upload(s, d_dz, dz)) ||
-            (st = upload(s, d_zd, zd)) || (st = upload(s, d_dlo, dlo)) || (st = upload(s, d_dhi, dhi)))
+            (st = upload(s, d_zd, zd)) || (st = upload(s, d_dr, dr)))
             return st;
-        s->ax[a] = pstd::AxisTables{d_kk, d_tw, d_gam, d_zt, d_dz, d_zd, d_dlo, d_dhi};
+        s->ax[a] = pstd::AxisTables{d_kk, d_tw, d_gam, d_zt, d_dz, d_zd, d_dr, ny[0], ny[1]};
         s->wloc[a] = d_wl;
     }
     return PSTD_OK;
@@ -432,11 +433,18 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
         return PSTD_OK;
     }
     const bool xy = pstd::solver_xy(s);
+    // box surface: groups of a few steps stage their plane values and add them
+    // to the sums once, at the group's end (pulsed runs always: solver_args)
+    const bool stage = !s->pulse && s->bring[0] && count >= kStageMin;
+    auto args_of = [&](int axis, pstd::PassArgs& a) {
+        pstd::solver_args(s, axis, a);
+        if (stage) a.bstage = s->bring[axis];
+    };
     if (xy) {
         // the x and y passes in one launch; its time goes to the x slot of the timers
         pstd::PassArgs a, b;
-        pstd::solver_args(s, 0, a);
-        pstd::solver_args(s, 1, b);
+        args_of(0, a);
+        args_of(1, b);
         if (ev) HIP_TRY(s, hipEventRecord(ev[0], stream));
         hipError_t e = pstd::launch_variant_xy(s->variant[0], a, b, false, koff, stream);
         if (e != hipSuccess) return hip_fail(s, e, "pass launch");
@@ -445,16 +453,16 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
     }
     for (int axis = xy ? 2 : 0; axis < 3; ++axis) {
         pstd::PassArgs a;
-        pstd::solver_args(s, axis, a);
+        args_of(axis, a);
         const bool seg = s->prob.sub_core[axis] > 0;
         if (ev) HIP_TRY(s, hipEventRecord(ev[2 * axis], stream));
         hipError_t e = pstd::launch_variant_single(s->variant[axis], seg, axis, a, koff, stream);
         if (e != hipSuccess) return hip_fail(s, e, "pass launch");
         if (ev) HIP_TRY(s, hipEventRecord(ev[2 * axis + 1], stream));
     }
-    if (s->pulse && koff == count - 1) {
-        // a pulsed run on the box: the group's staged plane values into the sums
-        hipError_t e = pstd::pulse_launch_box_flush(s, count, stream);
+    if ((s->pulse || stage) && koff == count - 1) {
+        // the group's staged plane values into the sums
+        hipError_t e = pstd::box_launch_flush(s, count, stream);
         if (e != hipSuccess) return hip_fail(s, e, "plane flush launch");
     }
     if (pstd::sphere_staged(s) && koff == count - 1) {
@@ -463,6 +471,26 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
         if (e != hipSuccess) return hip_fail(s, e, "shell flush launch");
     }
     return PSTD_OK;
+}
+
+// The ring of staged plane values, had on the first run that can use it;
+// without memory for it the passes add each step to the sums themselves
+void ensure_box_ring(pstd_solver* s) {
+    if (s->bring[0] || s->no_ring || s->pulse || s->in_batch || s->prob.surface_kind != 0 || s->prob.scheme != 0 ||
+        s->prob.dft_end <= s->prob.dft_begin)
+        return;
+    size_t total = 0, off[3];
+    for (int a = 0; a < 3; ++a) {
+        off[a] = total;
+        total += (size_t)pstd::kStageSteps * 4 * s->points[a];
+    }
+    float2* ring = nullptr;
+    if (hipMalloc(&ring, total * sizeof(float2)) != hipSuccess) {
+        (void)hipGetLastError();
+        s->no_ring = true;
+        return;
+    }
+    for (int a = 0; a < 3; ++a) s->bring[a] = ring + off[a];
 }
 
 // `count` consecutive steps, then one counter advance
@@ -478,6 +506,7 @@ pstd_status launch_steps(pstd_solver* s, hipStream_t stream, int count, hipEvent
 
 pstd_status build_graph(pstd_solver* s) {
     if (s->graph) return PSTD_OK;
+    ensure_box_ring(s);
     if (!s->cap_stream) HIP_TRY(s, hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking));
     HIP_TRY(s, hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
     pstd_status st = launch_steps(s, s->cap_stream, kGraphSteps, nullptr);
@@ -992,6 +1021,7 @@ pstd_status pstd_run(pstd_solver* s, int64_t n_steps) {
     pstd_status st = solver_ensure_tables(s, s->step + n_steps);
     if (st) return st;
     int64_t left = n_steps;
+    if (left >= kStageMin) ensure_box_ring(s);
     if (left >= kGraphSteps) {
         if ((st = build_graph(s))) return st;
         for (; left >= kGraphSteps; left -= kGraphSteps) HIP_TRY(s, hipGraphLaunch(s->graph, s->stream));
@@ -1407,6 +1437,7 @@ pstd_status pstd_destroy(pstd_solver* s) {
     (void)hipFree(s->buf[1]);
     (void)hipFree(s->L);
     (void)hipFree(s->L2);
+    (void)hipFree(s->bring[0]);
     (void)hipFree(s->vbox);
     (void)hipFree(s->v2full);
     (void)hipFree(s->wr);

@@ -179,4 +179,16 @@ __device__ __forceinline__ void dft(float2 (&v)[R]) {
     }
 }
 
+// Surface DFT in FP64: one step's term w psi, and Neumaier's compensated sum.
+// The term is written in FMAs so that every kernel that adds it rounds alike.
+__device__ __forceinline__ double2 dft_term(double2 w, double re, double im) {
+    return make_double2(fma(w.x, re, -(w.y * im)), fma(w.x, im, w.y * re));
+}
+__device__ __forceinline__ void neumaier(double& s, double& c, double x) {
+    const double t = s + x;
+    if (fabs(s) >= fabs(x)) c += (s - t) + x;
+    else c += (x - t) + s;
+    s = t;
+}
+
 }  // namespace pstd

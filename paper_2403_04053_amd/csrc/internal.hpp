@@ -16,8 +16,8 @@ struct AxisTables {
     const float2* zt;    // zeta(i) exp(i khat_a x_a(i))
     const float2* dz;    // (zeta''(i) + 2 i khat_a zeta'(i)) exp(i khat_a x_a(i))
     const float4* zd;    // zt and dz of index i side by side: one 16-byte load per cell
-    const float2* dlo;   // spectral-derivative row for the low plane
-    const float2* dhi;   // spectral-derivative row for the high plane
+    const float2* dr;    // spectral-derivative rows of the (low, high) plane, real parts
+    float ny_lo, ny_hi;  // their Nyquist parts: row entry e has the imaginary part ny (-1)^e
 };
 
 // The potential term's factor 2 dtau (V / E0 + sum_a w_a) of Eq. PSTDupdating.
@@ -54,8 +54,8 @@ struct PassArgs {
     const int* dft_tab;        // per step: 1 inside the surface-DFT window
     int plane_lo, plane_hi;    // plane indices along this pass's axis (local in segmented mode)
     double2* acc;              // [2 sides][4: sum psi, comp psi, sum dpsi, comp dpsi][points]
-    float2* bstage;            // null, or (pulsed runs) [group step][2 sides][psi, dpsi][points]: the
-                               // plane values are staged there instead of added to acc
+    float2* bstage;            // null, or [group step][2 sides][psi, dpsi][points]: the plane values of
+                               // the step are staged there instead of added to acc
     int64_t points;            // points of one plane of this axis
     // overlapping-subdomain mode along this pass's axis (Section 2.6)
     int seg_core, seg_halo, nseg;

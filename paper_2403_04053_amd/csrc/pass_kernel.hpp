@@ -68,13 +68,6 @@
 
 namespace pstd {
 
-__device__ __forceinline__ void neumaier(double& s, double& c, double x) {
-    const double t = s + x;
-    if (fabs(s) >= fabs(x)) c += (s - t) + x;
-    else c += (x - t) + s;
-    s = t;
-}
-
 // Pointers into device global memory.  The descriptor may come from the
 // kernel arguments or from a table in memory; qualifying every pointer keeps
 // the loads and stores global (not flat) either way.
@@ -115,7 +108,8 @@ struct Fields {
     GMEM const float *wr0, *wr1, *wr2;
     int nx, ny, nz;
     GMEM const float *kk, *gam;
-    GMEM const float2 *tw, *zt, *dz, *dlo, *dhi;
+    GMEM const float2 *tw, *zt, *dz, *dr;
+    float ny_lo, ny_hi;
     GMEM const float4* zd;
     GMEM const float2 *zt_x, *dz_x, *zt_y, *dz_y;
     GMEM const float *gam_x, *gam_y;
@@ -162,8 +156,9 @@ __device__ __forceinline__ Fields fields(const PassArgs& a) {
     f.zt = gmem(a.ax[AXIS].zt);
     f.dz = gmem(a.ax[AXIS].dz);
     f.zd = gmem(a.ax[AXIS].zd);
-    f.dlo = gmem(a.ax[AXIS].dlo);
-    f.dhi = gmem(a.ax[AXIS].dhi);
+    f.dr = gmem(a.ax[AXIS].dr);
+    f.ny_lo = a.ax[AXIS].ny_lo;
+    f.ny_hi = a.ax[AXIS].ny_hi;
     f.zt_x = gmem(a.ax[0].zt);
     f.dz_x = gmem(a.ax[0].dz);
     f.zt_y = gmem(a.ax[1].zt);
@@ -302,7 +297,7 @@ struct TileLds {
     __shared__ float2 ex[P * TileLds<N, N1, N2>::STRIDE]; \
     __shared__ float2 s_tw[N];                         \
     __shared__ float s_kk[N];                          \
-    __shared__ float2 s_dl[TileLds<N, N1, N2>::ROWS], s_dh[TileLds<N, N1, N2>::ROWS];
+    __shared__ float2 s_dr[TileLds<N, N1, N2>::ROWS];
 
 // Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8); give each
 // XCD a contiguous run of [0, G) instead, so that neighbouring tiles, which
@@ -320,7 +315,7 @@ __device__ __forceinline__ int xcd_tile(bool back) {
 template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool ADJ, bool POTX, bool NTL, bool OWN>
 __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, float2* __restrict__ ex,
                                           float2* __restrict__ s_tw, float* __restrict__ s_kk,
-                                          float2* __restrict__ s_dl, float2* __restrict__ s_dh) {
+                                          float2* __restrict__ s_dr) {
     constexpr int NT = P * (N1 > N2 ? N1 : N2);
     constexpr int ROW = TileLds<N, N1, N2>::ROW;
     constexpr int STRIDE = TileLds<N, N1, N2>::STRIDE;
@@ -362,19 +357,22 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
     });
     const bool surf = f.dft_tab[nstep] != 0;
     if (kRowsInLds && surf)
-        for (int i = t; i < N; i += NT) {
-            s_dl[i] = f.dlo[i];
-            s_dh[i] = f.dhi[i];
-        }
-    // entry e of the low (hi = false) or high plane's derivative row
-    auto drow = [&](bool hi, int e) -> float2 {
+        for (int i = t; i < N; i += NT) s_dr[i] = f.dr[i];
+    // entry e of the low and the high plane's derivative row, without its
+    // Nyquist part: the rows are real but for that, i ny (-1)^e, which needs one
+    // alternating sum for both planes (4 FMAs and 2 adds per element; 16
+    // operations and twice the LDS reads as complex rows)
+    auto drow = [&](int e) -> float2 {
         if constexpr (kRowsInLds) {
-            return hi ? s_dh[e] : s_dl[e];
+            return s_dr[e];
         } else {
-            const float2 r = hi ? f.dhi[e] : f.dlo[e];
+            const float2 r = f.dr[e];
             return r;
         }
     };
+    // (-1)^e of element n1 is alt(n1) times the thread's sign
+    const float alt0 = (n2 & 1) ? -1.f : 1.f;
+    constexpr auto alt = [](int n1) { return (N2 & 1) && (n1 & 1) ? -1.f : 1.f; };
 
     {
         // the y pass's epilogue operand (L from the x pass), the same elements
@@ -426,14 +424,18 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
         // spectral normal derivative on the two planes: partial dot products
         float2 dlo = make_float2(0.f, 0.f), dhi = dlo;
         if (!ADJ && surf) {
+            float2 ny = make_float2(0.f, 0.f);  // sum of (-1)^e v_e
             unroll<N1>([&](auto i) {
                 constexpr int n1 = decltype(i)::value;
-                const int e = n2 + N2 * n1;
-                if (e < N) {
-                    dlo = cadd(dlo, cmul(drow(false, e), v[n1]));
-                    dhi = cadd(dhi, cmul(drow(true, e), v[n1]));
-                }
+                const float2 r = drow(n2 + N2 * n1);
+                dlo = make_float2(fmaf(r.x, v[n1].x, dlo.x), fmaf(r.x, v[n1].y, dlo.y));
+                dhi = make_float2(fmaf(r.y, v[n1].x, dhi.x), fmaf(r.y, v[n1].y, dhi.y));
+                if constexpr (alt(n1) > 0) ny = cadd(ny, v[n1]);
+                else ny = csub(ny, v[n1]);
             });
+            const float cl = f.ny_lo * alt0, ch = f.ny_hi * alt0;
+            dlo = make_float2(fmaf(-cl, ny.y, dlo.x), fmaf(cl, ny.x, dlo.y));
+            dhi = make_float2(fmaf(-ch, ny.y, dhi.x), fmaf(ch, ny.x, dhi.y));
         }
 
         // ---- forward: stage A (N1-point DFTs), twiddle, exchange ----
@@ -571,15 +573,19 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                     hph = cmul(cinj, f.inj_hi_p[pt]);
                     hdh = cmul(cinj, f.inj_hi_d[pt]);
                 }
+                // the rows' Nyquist part, i (ny_lo hdl + ny_hi hdh) (-1)^e
+                const float2 hn = make_float2(-alt0 * (f.ny_lo * hdl.y + f.ny_hi * hdh.y),
+                                              alt0 * (f.ny_lo * hdl.x + f.ny_hi * hdh.x));
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    if (e < N) {
-                        float2 x = cadd(cmul(drow(false, e), hdl), cmul(drow(true, e), hdh));
-                        if (e == plane_lo) x = cadd(x, hpl);
-                        if (e == plane_hi) x = cadd(x, hph);
-                        v[n1] = cadd(v[n1], x);
-                    }
+                    const float2 r = drow(e);
+                    float2 x = make_float2(fmaf(r.x, hdl.x, r.y * hdh.x), fmaf(r.x, hdl.y, r.y * hdh.y));
+                    if constexpr (alt(n1) > 0) x = cadd(x, hn);
+                    else x = csub(x, hn);
+                    if (e == plane_lo) x = cadd(x, hpl);
+                    if (e == plane_hi) x = cadd(x, hph);
+                    v[n1] = cadd(v[n1], x);
                 });
             }
         }
@@ -736,7 +742,7 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                     if (x < f.nx && geo.tq % nseg == segp) spt = x + (int64_t)f.nx * (geo.tq / nseg);
                 }
                 if (spt >= 0 && f.bstage) {
-                    // pulsed runs: stage the plane value of this step of the group
+                    // stage the plane value of this step of the group
                     float2 s = make_float2(0.f, 0.f);
                     for (int m = 0; m < N2; ++m) s = cadd(s, ex[p * STRIDE + m * 4 + q]);
                     f.bstage[((int64_t)(koff * 2 + side) * 2 + (q >> 1)) * f.points + spt] = s;
@@ -745,15 +751,14 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                     for (int m = 0; m < N2; ++m) s = cadd(s, ex[p * STRIDE + m * 4 + q]);
                     const double re = (double)s.x, im = (double)s.y;
                     const double2 w = f.w_tab[nstep];
-                    const double zr = w.x * re - w.y * im;
-                    const double zi = w.x * im + w.y * re;
+                    const double2 z = dft_term(w, re, im);
                     const int field = (q >> 1) * 2;
                     const int64_t points = f.points;
                     GMEM double2* __restrict__ S = f.acc + (int64_t)(side * 4 + field) * points + spt;
                     GMEM double2* __restrict__ Cc = f.acc + (int64_t)(side * 4 + field + 1) * points + spt;
                     double2 sv = *S, cv = *Cc;
-                    neumaier(sv.x, cv.x, zr);
-                    neumaier(sv.y, cv.y, zi);
+                    neumaier(sv.x, cv.x, z.x);
+                    neumaier(sv.y, cv.y, z.y);
                     *S = sv;
                     *Cc = cv;
                 }
@@ -777,13 +782,13 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
     const int gt = xcd_tile(AXIS == 1 && !MULTI);
     if constexpr (!MULTI) {
         const Fields f = fields<AXIS>(single);
-        pass_tile<N, N1, N2, M1, P, AXIS, SEG, ADJ, POTX, NTL, OWN>(f, gt, koff, ex, s_tw, s_kk, s_dl, s_dh);
+        pass_tile<N, N1, N2, M1, P, AXIS, SEG, ADJ, POTX, NTL, OWN>(f, gt, koff, ex, s_tw, s_kk, s_dr);
     } else {
         int inst = 0;
         for (int i = 1; i < ninst; ++i)
             if (gt >= off[i]) inst = i;
         const Fields f = fields<AXIS>(descs[inst]);
-        pass_tile<N, N1, N2, M1, P, AXIS, SEG, ADJ, POTX, NTL, OWN>(f, gt - off[inst], koff, ex, s_tw, s_kk, s_dl, s_dh);
+        pass_tile<N, N1, N2, M1, P, AXIS, SEG, ADJ, POTX, NTL, OWN>(f, gt - off[inst], koff, ex, s_tw, s_kk, s_dr);
     }
 }
 
@@ -803,10 +808,10 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_xy_kernel(PassAr
     const int tile = gt < both ? gt >> 1 : gt - (both >> 1);
     if (!isy) {
         const Fields f = fields<0>(ax);
-        pass_tile<N, N1, N2, M1, P, 0, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dl, s_dh);
+        pass_tile<N, N1, N2, M1, P, 0, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dr);
     } else {
         const Fields f = fields<1>(ay);
-        pass_tile<N, N1, N2, M1, P, 1, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dl, s_dh);
+        pass_tile<N, N1, N2, M1, P, 1, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dr);
     }
 }
 

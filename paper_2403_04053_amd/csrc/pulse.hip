@@ -28,6 +28,7 @@
 #include <string>
 #include <vector>
 
+#include "dft.hpp"
 #include "solver.hpp"
 
 namespace pstd {
@@ -66,13 +67,6 @@ constexpr int kLag = 8;
 constexpr int kModeChunk = 256;
 
 // compensated (Neumaier) summation step
-__device__ __forceinline__ void neumaier(double& s, double& c, double x) {
-    const double t = s + x;
-    if (fabs(s) >= fabs(x)) c += (s - t) + x;
-    else c += (x - t) + s;
-    s = t;
-}
-
 // in-place radix-2 DFT, forward (e^{-i 2 pi l j / N}), N a power of two
 void fft_pow2(std::vector<std::complex<double>>& a) {
     const size_t n = a.size();
@@ -238,12 +232,17 @@ struct BoxFlush {
 };
 
 // one thread per (wavenumber, side, field, plane point): the group's staged
-// values are loaded before the step counter is read, then added in step
-// order to the compensated sums
+// values are added in step order to the compensated sums.  Bound by HBM and
+// the cache (192 B per value and wavenumber for 16 steps).  A group without a
+// window step reads nothing.
 __global__ __launch_bounds__(256) void box_flush_kernel(const int64_t* __restrict__ ctr, int count,
                                                         const int* __restrict__ dft_tab,
                                                         const double2* __restrict__ w_tab, int64_t wstride, int nk,
                                                         BoxFlush bf) {
+    const int64_t first = ctr[0], end = ctr[1];
+    bool any = false;
+    for (int k = 0; k < count; ++k) any |= first + k < end && dft_tab[first + k] != 0;
+    if (!any) return;
     int b = (int)blockIdx.x, a = 0;
     while (a < 2 && b >= bf.blocks[a]) b -= bf.blocks[a++];
     const int64_t points = bf.points[a];
@@ -260,21 +259,16 @@ __global__ __launch_bounds__(256) void box_flush_kernel(const int64_t* __restric
     double2* S = bf.acc[a] + ((int64_t)f * 8 + (sf >> 1) * 4 + (sf & 1) * 2) * points + pt;
     double2* Cc = S + points;
     double2 s = *S, c = *Cc;
-    const int64_t first = ctr[0], end = ctr[1];
-    bool any = false;
 #pragma unroll
     for (int k = 0; k < kStageSteps; ++k) {
         const int64_t m = first + k;
         if (k >= count || m >= end || !dft_tab[m]) continue;
-        any = true;
-        const double2 w = w_tab[f * wstride + m];
-        neumaier(s.x, c.x, w.x * v[k].x - w.y * v[k].y);
-        neumaier(s.y, c.y, w.x * v[k].y + w.y * v[k].x);
+        const double2 z = dft_term(w_tab[f * wstride + m], v[k].x, v[k].y);
+        neumaier(s.x, c.x, z.x);
+        neumaier(s.y, c.y, z.y);
     }
-    if (any) {
-        *S = s;
-        *Cc = c;
-    }
+    *S = s;
+    *Cc = c;
 }
 
 }  // namespace
@@ -575,16 +569,16 @@ hipError_t pulse_load(pstd_solver* s, const char* src, int64_t from) {
 
 float2* pulse_box_stage(const pstd_solver* s, int axis) { return s->pulse ? s->pulse->bstage[axis] : nullptr; }
 
-hipError_t pulse_launch_box_flush(const pstd_solver* s, int count, hipStream_t stream) {
+hipError_t box_launch_flush(const pstd_solver* s, int count, hipStream_t stream) {
     const PulseState* ps = s->pulse;
-    if (!ps || !ps->box) return hipSuccess;
+    if (ps ? !ps->box : !s->bring[0]) return hipSuccess;
     if (count < 1 || count > kStageSteps) return hipErrorInvalidValue;
-    const int nk = (int)ps->kbar.size();
+    const int nk = ps ? (int)ps->kbar.size() : 1;
     BoxFlush bf{};
     int blocks = 0;
     for (int a = 0; a < 3; ++a) {
-        bf.stage[a] = ps->bstage[a];
-        bf.acc[a] = ps->bacc[a];
+        bf.stage[a] = ps ? ps->bstage[a] : s->bring[a];
+        bf.acc[a] = ps ? ps->bacc[a] : s->acc[a];
         bf.points[a] = s->points[a];
         bf.blocks[a] = (int)((nk * 4 * s->points[a] + 255) / 256);
         blocks += bf.blocks[a];

@@ -42,6 +42,8 @@ struct pstd_solver {
     pstd::AxisTables ax[3]{};
     const float* wloc[3] = {nullptr, nullptr, nullptr};
     double2* acc[3] = {nullptr, nullptr, nullptr};
+    float2* bring[3] = {nullptr, nullptr, nullptr};  // box surface: staged plane values of a launch group (one allocation)
+    bool no_ring = false;         // no memory for it
     int64_t points[3] = {0, 0, 0};
     int variant[3] = {0, 0, 0};   // tile shape of each axis pass
     // per-step tables, steps [0, tab_cap)
@@ -153,10 +155,12 @@ hipError_t pulse_load(pstd_solver* s, const char* src, int64_t from);
 // the output of wavenumber ik
 pstd_status pulse_output(pstd_solver* s, int ik, SphereOut* o);
 // box surface: the staging ring of the pass along `axis` (null unless a
-// pulsed run integrates over the box), the group flush, and the inputs of the
-// box projection for wavenumber ik (rescaled: units of that wavenumber)
+// pulsed run integrates over the box), the flush of a launch group's staged
+// values (the pulse's, or the solver's own ring into its sums), and the
+// inputs of the box projection for wavenumber ik (rescaled: units of that
+// wavenumber)
 float2* pulse_box_stage(const pstd_solver* s, int axis);
-hipError_t pulse_launch_box_flush(const pstd_solver* s, int count, hipStream_t stream);
+hipError_t box_launch_flush(const pstd_solver* s, int count, hipStream_t stream);
 struct BoxOut {
     pstd_problem prob;
     double dxb[3];
