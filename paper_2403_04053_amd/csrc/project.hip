@@ -1,28 +1,36 @@
 // Near-to-distant-field projection over the virtual box (Section 3.2).
 //
-// All sums are FP64.  The phasors of each face plane are first brought to
-// their 2D spectrum (the coefficients of the trigonometric interpolant of
-// Eq. AnBottomPsi).  Then:
+// All sums are FP64.  Both outputs are linear in the phasors of each face
+// plane, through the trigonometric interpolant of Eq. AnBottomPsi; its DFT is
+// folded into the tables below, so no plane is transformed on a call.
 //
 //  * far field: the cell formula of Eqs. bottomPsi_lm ... leftrightPsi_ln in
 //    the limit of Eq. FDTDfarfieldapprox.  For a direction r_hat every cell
 //    term factors into an in-plane b-part and c-part, so a face contributes
-//    g_c(r_hat)^T [F_dpsi + i r_hat_a F_psi] g_b(r_hat): one complex GEMM
-//    [directions x Nb] x [Nb x 2Nc] per face and a fused row-wise dot;
+//    h_c(r_c)^T [P_dpsi + i r_a P_psi] h_b(r_b).  Each factor is an entire
+//    function of its component of exponential type X, the box's reduced half
+//    width, so its Chebyshev series on [-1, 1] ends, to rounding, a little
+//    past X: a face is a K x K matrix of coefficients (two small GEMMs per
+//    plane and call) and a direction costs sum_jk C_jk T_j(r_c) T_k(r_b), real
+//    times complex, on the FP64 matrix cores;
 //  * Fresnel points: each sinc of the cell formula is expanded to 8th order
 //    in its shift alpha = k d R_hat / 2, so the spectral double sum of a cell
 //    becomes sum_pq alpha_b^p alpha_c^q Q_pq(cell); the Q tables are two
-//    batched GEMMs per face and field, and the per-point work is a Horner
-//    evaluation per cell with the exact distance R and exp(ikR)/R.
+//    batched GEMMs per face and field.  The 36 terms of total degree 9 to 16
+//    are economised onto the 45 of degree 8 and less, and the per-point work
+//    is a Horner evaluation per cell with the exact distance R and
+//    exp(ikR)/R.
 //
 // Reduced units throughout (k = 1); the far-field amplitude is divided by k0
 // at the end to return physical length units.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <vector>
 
+#include "fp64_math.hpp"
 #include "project.hpp"
 
 namespace pstd {
@@ -32,6 +40,11 @@ namespace {
 constexpr double kPi = 3.141592653589793238462643383279502884;
 constexpr int kOrder = 8;            // sinc expansion order
 constexpr int kTerms = kOrder + 1;
+constexpr int kPairs = kTerms * kTerms;               // (p, q), p, q <= 8
+constexpr int kLow = kTerms * (kTerms + 1) / 2;       // those with p + q <= 8
+constexpr int kHigh = kPairs - kLow;
+// row p of the low terms starts here: (p, 0), (p, 1), ... (p, 8 - p)
+__host__ __device__ constexpr int low_row(int p) { return p * kTerms - p * (p - 1) / 2; }
 
 __host__ __device__ inline int face_axis_b(int a) { return a == 0 ? 1 : 0; }
 __host__ __device__ inline int face_axis_c(int a) { return a == 2 ? 1 : 2; }
@@ -43,102 +56,141 @@ __device__ __forceinline__ double2 zadd(double2 a, double2 b) { return make_doub
 __device__ __forceinline__ double dsinc(double x) { return fabs(x) < 1e-8 ? 1.0 - x * x / 6.0 : sin(x) / x; }
 
 // ---------------------------------------------------------------------------
-// phasor finalisation
+// phasor finalisation: the six faces in one launch
 // ---------------------------------------------------------------------------
 
-__global__ void finalize_kernel(const double2* __restrict__ acc, int side, int64_t points, double2 sv, double2 sd,
-                                double2* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+struct FinalizeArgs {
+    const double2* acc[3];
+    int64_t points[3];
+    int blocks[3];  // of one face
+};
+
+__global__ void finalize_kernel(FinalizeArgs f, double2 sv, double2 sd, double2* __restrict__ out) {
+    int b = (int)blockIdx.x, a = 0;
+    while (a < 2 && b >= 2 * f.blocks[a]) {
+        b -= 2 * f.blocks[a];
+        out += 4 * f.points[a];
+        ++a;
+    }
+    const int side = b >= f.blocks[a];
+    const int64_t points = f.points[a];
+    const int64_t i = (int64_t)(b - side * f.blocks[a]) * blockDim.x + threadIdx.x;
     if (i >= points) return;
-    const double2* base = acc + (int64_t)side * 4 * points;
+    out += 2 * side * points;
+    const double2* base = f.acc[a] + (int64_t)side * 4 * points;
     const double2 s0 = base[i], c0 = base[points + i], s1 = base[2 * points + i], c1 = base[3 * points + i];
     const double ar = s0.x + c0.x, ai = s0.y + c0.y, br = s1.x + c1.x, bi = s1.y + c1.y;
     out[i] = make_double2(ar * sv.x - ai * sv.y, ar * sv.y + ai * sv.x);
     out[points + i] = make_double2(br * sd.x - bi * sd.y, br * sd.y + bi * sd.x);
 }
 
-// ---------------------------------------------------------------------------
-// naive separable 2D DFT of a [Nc][Nb] plane (FP64, forward)
-// ---------------------------------------------------------------------------
-
-__global__ void dft_rows_kernel(const double2* __restrict__ x, double2* __restrict__ y, int Nb, int Nc,
-                                const double2* __restrict__ twb) {
+// W[m][i] = exp(-2 pi i m i / N), the plane DFT as a matrix
+__global__ void dft_matrix_kernel(int N, double2* __restrict__ W) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)Nb * Nc) return;
-    const int bp = (int)(id % Nb), c = (int)(id / Nb);
-    double2 s = make_double2(0, 0);
-    for (int b = 0; b < Nb; ++b) s = zadd(s, zmul(x[(int64_t)c * Nb + b], twb[(int)(((int64_t)b * bp) % Nb)]));
-    y[id] = s;
-}
-
-__global__ void dft_cols_kernel(const double2* __restrict__ y, double2* __restrict__ z, int Nb, int Nc,
-                                const double2* __restrict__ twc) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)Nb * Nc) return;
-    const int bp = (int)(id % Nb), cp = (int)(id / Nb);
-    double2 s = make_double2(0, 0);
-    for (int c = 0; c < Nc; ++c) s = zadd(s, zmul(y[(int64_t)c * Nb + bp], twc[(int)(((int64_t)c * cp) % Nc)]));
-    z[id] = s;
+    if (id >= (int64_t)N * N) return;
+    const int64_t j = ((id / N) * (id % N)) % N;
+    double sn, cs;
+    sincospi(2.0 * (double)j / N, &sn, &cs);
+    W[id] = make_double2(cs, -sn);
 }
 
 // ---------------------------------------------------------------------------
 // batched complex GEMM on the FP64 matrix cores, row-major:
-// C[i][j] = sum_k A[i][k] B[k][j]
+// C[i][j] = sum_k A[i][k] B[k][j]; TA: A is given as [k][i], TB: B as [j][k];
+// CA, CB: the conjugate of A, B
 //
 // v_mfma_f64_16x16x4f64 takes, per lane l, A[i][k] with i = l % 16, k = l / 16
 // and B[k][j] with j = l % 16, k = l / 16, and leaves D[i][j] in register r
 // of lane l for i = 4 r + l / 16, j = l % 16.  A complex product is four real
 // ones: re += Ar Br - Ai Bi, im += Ar Bi + Ai Br.  A workgroup (4 waves)
-// computes a 64 x 64 tile, each wave 32 x 32 (2 x 2 MFMA tiles), from
-// 16-deep slices of A and B staged in LDS.
+// computes a T x T tile, each wave a quarter of it (U x U MFMA tiles), from
+// 16-deep slices of A and B staged in LDS, the next slice's loads in flight
+// during the products.  The matrices here are a few tiles each, so the batch
+// (two levels of strides) is what fills the chip: one launch takes every
+// (field, p, q) of a face, and where that gives 64 x 64 tiles to fewer than
+// half of the CUs, tiles of 32 x 32 (a quarter of the work per slice) shorten
+// the chain of slices: 160 x 92 x 160, batch 4: 41 us with 64 (before the loads ran ahead), 11 us with 32.
 // ---------------------------------------------------------------------------
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int ZT = 64;   // output tile edge
 constexpr int ZK = 16;   // K slice
 
-__global__ __launch_bounds__(256) void zgemm_kernel(int M, int N, int K, const double2* __restrict__ A, int64_t lda,
-                                                    int64_t sA, const double2* __restrict__ B, int64_t ldb, int64_t sB,
-                                                    double2* __restrict__ C, int64_t ldc, int64_t sC) {
-    __shared__ double2 As[ZT][ZK + 1];
-    __shared__ double2 Bs[ZK][ZT + 1];
-    const int bz = blockIdx.z;
-    A += bz * sA;
-    B += bz * sB;
-    C += bz * sC;
-    const int i0 = blockIdx.y * ZT, j0 = blockIdx.x * ZT;
+// one operand of a batched product: leading dimension and the strides of the
+// inner and outer batch index
+struct ZOp {
+    const double2* p;
+    int64_t ld, s0 = 0, s1 = 0;
+};
+
+template <int T, bool TA, bool CA, bool TB, bool CB>
+__global__ __launch_bounds__(256) void zgemm_kernel(int M, int N, int K, ZOp a_, ZOp b_, ZOp c_, int n0) {
+    constexpr int U = T / 32;            // MFMA tiles per wave and axis
+    constexpr int LD = T * ZK / 256;     // elements per thread, slice and operand
+    __shared__ double2 As[T][ZK + 1];
+    __shared__ double2 Bs[ZK][T + 1];
+    const int z0 = (int)blockIdx.z % n0, z1 = (int)blockIdx.z / n0;
+    const double2* __restrict__ A = a_.p + z0 * a_.s0 + z1 * a_.s1;
+    const double2* __restrict__ B = b_.p + z0 * b_.s0 + z1 * b_.s1;
+    double2* __restrict__ C = const_cast<double2*>(c_.p) + z0 * c_.s0 + z1 * c_.s1;
+    const int64_t lda = a_.ld, ldb = b_.ld, ldc = c_.ld;
+    const int i0 = blockIdx.y * T, j0 = blockIdx.x * T;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
-    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
+    const int wi = (wave >> 1) * (T / 2), wj = (wave & 1) * (T / 2);
     const int li = lane & 15, lk = lane >> 4;
-    v4d re[2][2], im[2][2];
-    for (int u = 0; u < 2; ++u)
-        for (int v = 0; v < 2; ++v) {
+    v4d re[U][U], im[U][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int v = 0; v < U; ++v) {
             re[u][v] = v4d{0, 0, 0, 0};
             im[u][v] = v4d{0, 0, 0, 0};
         }
-    for (int k0 = 0; k0 < K; k0 += ZK) {
-        for (int e = t; e < ZT * ZK; e += 256) {
-            const int r = e / ZK, c = e % ZK;
-            const int gi = i0 + r, gk = k0 + c;
-            As[r][c] = (gi < M && gk < K) ? A[(int64_t)gi * lda + gk] : make_double2(0, 0);
+    double2 ra[LD], rb[LD];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int n = 0; n < LD; ++n) {
+            const int e = t + n * 256;
+            {
+                const int r = TA ? e % T : e / ZK, c = TA ? e / T : e % ZK;
+                const int gi = i0 + r, gk = k0 + c;
+                double2 x = make_double2(0, 0);
+                if (gi < M && gk < K) x = A[TA ? (int64_t)gk * lda + gi : (int64_t)gi * lda + gk];
+                if (CA) x.y = -x.y;
+                ra[n] = x;
+            }
+            {
+                const int r = TB ? e % ZK : e / T, c = TB ? e / ZK : e % T;
+                const int gk = k0 + r, gj = j0 + c;
+                double2 x = make_double2(0, 0);
+                if (gk < K && gj < N) x = B[TB ? (int64_t)gj * ldb + gk : (int64_t)gk * ldb + gj];
+                if (CB) x.y = -x.y;
+                rb[n] = x;
+            }
         }
-        for (int e = t; e < ZK * ZT; e += 256) {
-            const int r = e / ZT, c = e % ZT;
-            const int gk = k0 + r, gj = j0 + c;
-            Bs[r][c] = (gk < K && gj < N) ? B[(int64_t)gk * ldb + gj] : make_double2(0, 0);
+    };
+    load(0);
+    for (int k0 = 0; k0 < K; k0 += ZK) {
+#pragma unroll
+        for (int n = 0; n < LD; ++n) {
+            const int e = t + n * 256;
+            As[TA ? e % T : e / ZK][TA ? e / T : e % ZK] = ra[n];
+            Bs[TB ? e % ZK : e / T][TB ? e / ZK : e % T] = rb[n];
         }
         __syncthreads();
+        if (k0 + ZK < K) load(k0 + ZK);
 #pragma unroll
         for (int ks = 0; ks < ZK; ks += 4) {
-            double2 a[2], b[2];
-            for (int u = 0; u < 2; ++u) a[u] = As[wi + u * 16 + li][ks + lk];
-            for (int v = 0; v < 2; ++v) b[v] = Bs[ks + lk][wj + v * 16 + li];
+            double2 a[U], b[U];
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int u = 0; u < U; ++u) a[u] = As[wi + u * 16 + li][ks + lk];
 #pragma unroll
-                for (int v = 0; v < 2; ++v) {
+            for (int v = 0; v < U; ++v) b[v] = Bs[ks + lk][wj + v * 16 + li];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int v = 0; v < U; ++v) {
                     re[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[v].x, re[u][v], 0, 0, 0);
                     re[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].y, b[v].y, re[u][v], 0, 0, 0);
                     im[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[v].y, im[u][v], 0, 0, 0);
@@ -148,9 +200,9 @@ __global__ __launch_bounds__(256) void zgemm_kernel(int M, int N, int K, const d
         __syncthreads();
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int v = 0; v < 2; ++v)
+        for (int v = 0; v < U; ++v)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int gi = i0 + wi + u * 16 + 4 * r + lk, gj = j0 + wj + v * 16 + li;
@@ -158,85 +210,296 @@ __global__ __launch_bounds__(256) void zgemm_kernel(int M, int N, int K, const d
             }
 }
 
-hipError_t zgemm(int M, int N, int K, const double2* A, int64_t lda, int64_t sA, const double2* B, int64_t ldb,
-                 int64_t sB, double2* C, int64_t ldc, int64_t sC, int batch, hipStream_t stream) {
-    if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
-    dim3 grid((N + ZT - 1) / ZT, (M + ZT - 1) / ZT, batch);
-    hipLaunchKernelGGL(zgemm_kernel, grid, dim3(256), 0, stream, M, N, K, A, lda, sA, B, ldb, sB, C, ldc, sC);
+struct ZOpts {
+    bool ta = false, ca = false, tb = false, cb = false;
+};
+
+template <int T>
+hipError_t zgemm_tile(int M, int N, int K, ZOp A, ZOp B, ZOp C, int n0, int n1, ZOpts o, hipStream_t stream) {
+    const dim3 grid((N + T - 1) / T, (M + T - 1) / T, n0 * n1);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, M, N, K, A, B, C, n0); };
+    // the forms in use
+    if (o.ta && o.ca && !o.tb && !o.cb) go(zgemm_kernel<T, true, true, false, false>);
+    else if (!o.ta && !o.ca && o.tb && !o.cb) go(zgemm_kernel<T, false, false, true, false>);
+    else if (!o.ta && !o.ca && !o.tb && o.cb) go(zgemm_kernel<T, false, false, false, true>);
+    else if (!o.ta && !o.ca && !o.tb && !o.cb) go(zgemm_kernel<T, false, false, false, false>);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+hipError_t zgemm(int M, int N, int K, ZOp A, ZOp B, double2* Cp, int64_t ldc, int64_t sc0, int64_t sc1, int n0, int n1,
+                 ZOpts o, hipStream_t stream) {
+    if (M <= 0 || N <= 0 || n0 <= 0 || n1 <= 0) return hipSuccess;
+    const ZOp C{Cp, ldc, sc0, sc1};
+    const int64_t groups = (int64_t)((N + 63) / 64) * ((M + 63) / 64) * n0 * n1;
+    return groups < 128 ? zgemm_tile<32>(M, N, K, A, B, C, n0, n1, o, stream)
+                        : zgemm_tile<64>(M, N, K, A, B, C, n0, n1, o, stream);
 }
 
 // ---------------------------------------------------------------------------
 // far field
 // ---------------------------------------------------------------------------
 
-// g(b') = (-1)^b' sinc(pi b'/N - d r/2) sum_{l=lo}^{hi-1} exp(i (2 pi b'/(N d) - r) x_l),
-// x_l = (l - N/2 + 1/2) d: the closed form of the geometric sum is used.
-__global__ void farfield_factor_kernel(const double3* __restrict__ dirs, int64_t nd, int comp, int N, double d,
-                                       int lo, int hi, double2* __restrict__ G) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= nd * N) return;
-    const int m = (int)(id % N);
-    const int64_t di = id / N;
-    const double3 rh = dirs[di];
-    const double r = comp == 0 ? rh.x : comp == 1 ? rh.y : rh.z;
-    const int bp = m < N / 2 ? m : m - N;
-    const double beta = 2.0 * kPi * bp / (N * d) - r;
-    const int M = hi - lo;
-    const double theta = beta * d / 2.0;
-    const double mag = (double)M * dsinc(M * theta) / dsinc(theta) * dsinc(kPi * bp / N - d * r / 2.0) *
+// One axis of the box as the far field sees it: N points of spacing d, the
+// face's cells between grid indices lo and hi
+struct FarAxis {
+    int N, lo, hi;
+    double d;
+    double mid, half;  // centre and half width of the cells
+};
+
+// g(m) = (-1)^b' sinc(pi b'/N - d r/2) sum_{l=lo}^{hi-1} exp(i (2 pi b'/(N d) - r) x_l),
+// b' the signed index of m, x_l = (l - N/2 + 1/2) d: the closed form of the
+// geometric sum is used.  centred: without the factor exp(-i r mid).
+__device__ __forceinline__ double2 far_factor(const FarAxis& ax, double r, int m, bool centred) {
+    const int bp = m < ax.N / 2 ? m : m - ax.N;
+    const double beta = 2.0 * kPi * bp / (ax.N * ax.d) - r;
+    const int M = ax.hi - ax.lo;
+    const double theta = beta * ax.d / 2.0;
+    const double mag = (double)M * dsinc(M * theta) / dsinc(theta) * dsinc(kPi * bp / ax.N - ax.d * r / 2.0) *
                        ((bp & 1) ? -1.0 : 1.0);
-    const double ph = beta * d * (lo - N / 2 + 0.5 * M);
+    const double ph = beta * ax.mid + (centred ? r * ax.mid : 0.0);
     double sn, cs;
     sincos(ph, &sn, &cs);
-    G[id] = make_double2(mag * cs, mag * sn);
+    return make_double2(mag * cs, mag * sn);
 }
 
-// Mt[b'][j] = F_dpsi[j][b'] (j < Nc), F_psi[j - Nc][b'] (j >= Nc)
-__global__ void stack_transpose_kernel(const double2* __restrict__ Fp, const double2* __restrict__ Fd, int Nb, int Nc,
-                                       double2* __restrict__ Mt) {
+// G[j][m]: the centred factor at the Chebyshev nodes r_j = cos(pi (j + 1/2) / K)
+__global__ void far_nodes_kernel(FarAxis ax, int K, double2* __restrict__ G) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)Nb * 2 * Nc) return;
-    const int j = (int)(id % (2 * Nc));
-    const int bp = (int)(id / (2 * Nc));
-    Mt[id] = j < Nc ? Fd[(int64_t)j * Nb + bp] : Fp[(int64_t)(j - Nc) * Nb + bp];
+    if (id >= (int64_t)K * ax.N) return;
+    const int m = (int)(id % ax.N), j = (int)(id / ax.N);
+    G[id] = far_factor(ax, cospi((j + 0.5) / K), m, true);
 }
 
-// f[d] += pref exp(-i r_a x_a) sum_c' Gc[d][c'] (T[d][c'] + i r_a T[d][Nc + c'])
-// One wave per direction: the lanes read consecutive c' (coalesced rows of T
-// and Gc) and the partial sums are reduced across the wave.
-constexpr int kDotWaves = 4;
+// D[k][j]: values at the K nodes to Chebyshev coefficients
+__global__ void far_dct_kernel(int K, double2* __restrict__ D) {
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= (int64_t)K * K) return;
+    const int64_t k = id / K, j = id % K;
+    // cos(k pi (j + 1/2) / K), the angle reduced in integers
+    const int64_t q = (k * (2 * j + 1)) % (4 * K);
+    D[id] = make_double2((k ? 2.0 : 1.0) / K * cospi((double)q / (2 * K)), 0.0);
+}
 
-__global__ __launch_bounds__(64 * kDotWaves) void farfield_dot_kernel(const double3* __restrict__ dirs, int64_t nd,
-                                                                      int comp_a, double xa, double pref,
-                                                                      const double2* __restrict__ Gc,
-                                                                      const double2* __restrict__ T, int Nc,
-                                                                      double2* __restrict__ f) {
-    const int lane = threadIdx.x & 63;
-    const int64_t d = (int64_t)blockIdx.x * kDotWaves + (threadIdx.x >> 6);
-    if (d >= nd) return;  // whole wave
-    const double3 rh = dirs[d];
-    const double ra = comp_a == 0 ? rh.x : comp_a == 1 ? rh.y : rh.z;
-    double sx = 0, sy = 0;
-    const double2* t = T + d * 2 * Nc;
-    const double2* g = Gc + d * Nc;
-    for (int c = lane; c < Nc; c += 64) {
-        const double2 a = t[c], b = t[Nc + c];
-        // a + i ra b
-        const double2 m = make_double2(a.x - ra * b.y, a.y + ra * b.x);
-        const double2 p = zmul(g[c], m);
-        sx += p.x;
-        sy += p.y;
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        sx += __shfl_down(sx, o, 64);
-        sy += __shfl_down(sy, o, 64);
-    }
-    if (lane == 0) {
+// coefficients of one axis's two faces in the order the direction kernel
+// reads: [k (Kb, padded to 4)][j (Kc, padded to 16)][side][psi, dpsi][re, im],
+// zero in the padding; C: [side][psi, dpsi][Kc][Kb]
+__global__ void far_pack_kernel(int Kb, int Kc, int Kbp, int Kcp, const double2* __restrict__ C,
+                                double2* __restrict__ out) {
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= (int64_t)Kbp * Kcp * 4) return;
+    const int sf = (int)(id & 3);
+    const int j = (int)((id >> 2) % Kcp), k = (int)((id >> 2) / Kcp);
+    out[id] = j < Kc && k < Kb ? C[((int64_t)sf * Kc + j) * Kb + k] : make_double2(0, 0);
+}
+
+struct FarEval {
+    const double* coef;  // far_pack_kernel's output of this axis
+    int Kbp, Kcp;
+    double half;         // of the normal axis: the faces lie at mid -+ half
+    double pref;
+};
+struct FarArgs {
+    FarEval ax[3];
+    int jsplit;
+};
+
+// sum_jk C_jk T_j(r_c) T_k(r_b) of one axis's two faces for 16 directions per
+// wave: the sum over k is a product of [16 directions x Kb] by [Kb x 16 j] for
+// each of the eight numbers (side, field, re/im) on the FP64 matrix cores,
+// T_k(cos t) = cos(k t) advancing by four k per step as a rotation in the
+// lane that feeds it; the sum over j is taken from the accumulators with the
+// faces' phases.  grid.y = axis * jsplit + part: few directions split the j
+// tiles; row y of part receives the sums.  Bound by the matrix cores (three
+// axes of about 92 x 96 coefficients: 65160 directions in 560 us, 0.35 ms of it
+// at their full rate; 3 waves per SIMD although 22 registers spill, 790 us at 2).
+// The former path, a complex product per 8192 directions and face with the
+// factors themselves, took 7.3 ms in all.
+constexpr int kFarWaves = 4;
+
+__global__ __launch_bounds__(64 * kFarWaves, 3) void far_eval_kernel(const double3* __restrict__ dirs, int64_t nd,
+                                                                  FarArgs f, double2* __restrict__ part) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const int64_t d0 = ((int64_t)blockIdx.x * kFarWaves + (threadIdx.x >> 6)) * 16;
+    if (d0 >= nd) return;  // whole wave
+    const int a = (int)blockIdx.y / f.jsplit, js = (int)blockIdx.y % f.jsplit;
+    const int b = face_axis_b(a), c = face_axis_c(a);
+    const FarEval ev = f.ax[a];
+    auto comp = [](double3 v, int i) { return i == 0 ? v.x : i == 1 ? v.y : v.z; };
+    // directions beyond the interval are replaced afterwards
+    auto angle = [](double r) { return acos(fmin(1.0, fmax(-1.0, r))); };
+    // feeder: direction li, k = lk + 4 step
+    const double tb = angle(comp(dirs[min(d0 + li, nd - 1)], b));
+    double c0, s0, c4, s4;
+    sincos(lk * tb, &s0, &c0);
+    sincos(4.0 * tb, &s4, &c4);
+    // receiver: directions 4 r + lk, column j = 16 tile + li
+    const int tiles = ev.Kcp / 16, per = (tiles + f.jsplit - 1) / f.jsplit;
+    const int t0 = js * per, t1 = min(tiles, t0 + per);
+    double tc[4], ts[4], c16[4], s16[4], ra[4], orr[4], oi[4];
+    double2 wlo[4], whi[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double3 v = dirs[min(d0 + 4 * r + lk, nd - 1)];
+        const double t = angle(comp(v, c));
+        sincos((16 * t0 + li) * t, &ts[r], &tc[r]);
+        sincos(16.0 * t, &s16[r], &c16[r]);
+        ra[r] = comp(v, a);
         double sn, cs;
-        sincos(-ra * xa, &sn, &cs);
-        const double2 r = zmul(make_double2(sx, sy), make_double2(pref * cs, pref * sn));
-        f[d] = zadd(f[d], r);
+        sincos(ra[r] * ev.half, &sn, &cs);
+        wlo[r] = make_double2(ev.pref * cs, ev.pref * sn);    // exp(+i ra half), low face
+        whi[r] = make_double2(-ev.pref * cs, ev.pref * sn);   // -exp(-i ra half)
+        orr[r] = 0;
+        oi[r] = 0;
+    }
+    for (int tile = t0; tile < t1; ++tile) {
+        v4d acc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = v4d{0, 0, 0, 0};
+        const double2* __restrict__ cf = reinterpret_cast<const double2*>(ev.coef) + ((int64_t)lk * ev.Kcp + tile * 16 + li) * 4;
+        double cc = c0, ss = s0;
+        // the coefficients of a step are loaded one step ahead (the last step
+        // loads its own again)
+        double2 n0 = cf[0], n1 = cf[1], n2 = cf[2], n3 = cf[3];
+        for (int k = 0; k < ev.Kbp; k += 4) {
+            const double2 x0 = n0, x1 = n1, x2 = n2, x3 = n3;
+            if (k + 4 < ev.Kbp) cf += (int64_t)16 * ev.Kcp;
+            n0 = cf[0];
+            n1 = cf[1];
+            n2 = cf[2];
+            n3 = cf[3];
+            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x0.x, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x0.y, acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x1.x, acc[2], 0, 0, 0);
+            acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x1.y, acc[3], 0, 0, 0);
+            acc[4] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x2.x, acc[4], 0, 0, 0);
+            acc[5] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x2.y, acc[5], 0, 0, 0);
+            acc[6] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x3.x, acc[6], 0, 0, 0);
+            acc[7] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x3.y, acc[7], 0, 0, 0);
+            const double cn = cc * c4 - ss * s4;
+            ss = cc * s4 + ss * c4;
+            cc = cn;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            // dpsi + i r_a psi of the low and the high face
+            const double lr = acc[2][r] - ra[r] * acc[1][r], lm = acc[3][r] + ra[r] * acc[0][r];
+            const double hr = acc[6][r] - ra[r] * acc[5][r], hm = acc[7][r] + ra[r] * acc[4][r];
+            orr[r] += tc[r] * (wlo[r].x * lr - wlo[r].y * lm + whi[r].x * hr - whi[r].y * hm);
+            oi[r] += tc[r] * (wlo[r].x * lm + wlo[r].y * lr + whi[r].x * hm + whi[r].y * hr);
+            const double cn = tc[r] * c16[r] - ts[r] * s16[r];
+            ts[r] = tc[r] * s16[r] + ts[r] * c16[r];
+            tc[r] = cn;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        for (int o = 8; o > 0; o >>= 1) {
+            orr[r] += __shfl_xor(orr[r], o, 64);
+            oi[r] += __shfl_xor(oi[r], o, 64);
+        }
+        const int64_t d = d0 + 4 * r + lk;
+        if (li == 0 && d < nd) part[(int64_t)blockIdx.y * nd + d] = make_double2(orr[r], oi[r]);
+    }
+}
+
+// out[d] = exp(-i r_hat . mid) times the rows of part, in order
+__global__ void far_sum_kernel(const double3* __restrict__ dirs, int64_t nd, double3 mid,
+                               const double2* __restrict__ part, int rows, double2* __restrict__ out) {
+    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= nd) return;
+    double2 s = part[d];
+    for (int k = 1; k < rows; ++k) s = zadd(s, part[(int64_t)k * nd + d]);
+    const double3 r = dirs[d];
+    double sn, cs;
+    sincos(-(r.x * mid.x + r.y * mid.y + r.z * mid.z), &sn, &cs);
+    out[d] = zmul(s, make_double2(cs, sn));
+}
+
+// Directions with a component beyond 1 (no unit vector, but the formula holds
+// for any): each by a workgroup from the factors themselves.  A workgroup
+// looks over 256 directions; scratch: 2 (Nx + Ny + Nz) values per workgroup.
+constexpr double kFarLimit = 1.0 + 4.0e-16;
+constexpr int kWideGroups = 64;
+
+struct FarWide {
+    FarAxis ax[3];
+    double pref[3];
+    const double2* planes;  // phasors, [face][psi, dpsi][plane]
+};
+
+__global__ __launch_bounds__(256) void far_wide_kernel(const double3* __restrict__ dirs, int64_t nd, FarWide f,
+                                                       double2* __restrict__ scratch, double2* __restrict__ out) {
+    __shared__ int todo[256];
+    __shared__ int count;
+    __shared__ double red[2][256];
+    const int t = threadIdx.x;
+    const int Ns = f.ax[0].N + f.ax[1].N + f.ax[2].N;
+    double2* g = scratch + (int64_t)blockIdx.x * 2 * Ns;
+    double2* h = g + Ns;
+    const int off[3] = {0, f.ax[0].N, f.ax[0].N + f.ax[1].N};
+    for (int64_t base = (int64_t)blockIdx.x * 256; base < nd; base += (int64_t)gridDim.x * 256) {
+        __syncthreads();
+        if (t == 0) count = 0;
+        __syncthreads();
+        if (base + t < nd) {
+            const double3 r = dirs[base + t];
+            if (fabs(r.x) > kFarLimit || fabs(r.y) > kFarLimit || fabs(r.z) > kFarLimit) todo[atomicAdd(&count, 1)] = t;
+        }
+        __syncthreads();
+        const int n = count;
+        for (int q = 0; q < n; ++q) {
+            const int64_t d = base + todo[q];
+            const double3 rh = dirs[d];
+            const double rr[3] = {rh.x, rh.y, rh.z};
+            __syncthreads();
+            for (int a = 0; a < 3; ++a)
+                for (int m = t; m < f.ax[a].N; m += 256) g[off[a] + m] = far_factor(f.ax[a], rr[a], m, false);
+            __syncthreads();
+            for (int a = 0; a < 3; ++a) {
+                const int N = f.ax[a].N;
+                for (int i = t; i < N; i += 256) {
+                    double2 s = make_double2(0, 0);
+                    for (int m = 0; m < N; ++m) {
+                        double sn, cs;
+                        sincospi(-2.0 * (double)(((int64_t)m * i) % N) / N, &sn, &cs);
+                        s = zadd(s, zmul(g[off[a] + m], make_double2(cs, sn)));
+                    }
+                    h[off[a] + i] = s;
+                }
+            }
+            __syncthreads();
+            double2 acc = make_double2(0, 0);
+            const double2* pl = f.planes;
+            for (int face = 0; face < 6; ++face) {
+                const int a = face / 2, side = face % 2, b = face_axis_b(a), c = face_axis_c(a);
+                const int Nb = f.ax[b].N, Nc = f.ax[c].N;
+                const int64_t np = (int64_t)Nb * Nc;
+                double2 s = make_double2(0, 0);
+                for (int64_t i = t; i < np; i += 256) {
+                    const double2 v = pl[i], dv = pl[np + i];
+                    const double2 x = make_double2(dv.x - rr[a] * v.y, dv.y + rr[a] * v.x);
+                    s = zadd(s, zmul(zmul(h[off[b] + i % Nb], h[off[c] + i / Nb]), x));
+                }
+                double sn, cs;
+                sincos(-rr[a] * (f.ax[a].mid + (side ? f.ax[a].half : -f.ax[a].half)), &sn, &cs);
+                const double w = side ? -f.pref[a] : f.pref[a];
+                acc = zadd(acc, zmul(s, make_double2(w * cs, w * sn)));
+                pl += 2 * np;
+            }
+            red[0][t] = acc.x;
+            red[1][t] = acc.y;
+            __syncthreads();
+            for (int w = 128; w > 0; w >>= 1) {
+                if (t < w) {
+                    red[0][t] += red[0][t + w];
+                    red[1][t] += red[1][t + w];
+                }
+                __syncthreads();
+            }
+            if (t == 0) out[d] = make_double2(red[0][0], red[1][0]);
+        }
     }
 }
 
@@ -244,9 +507,9 @@ __global__ __launch_bounds__(64 * kDotWaves) void farfield_dot_kernel(const doub
 // Fresnel points
 // ---------------------------------------------------------------------------
 
-constexpr int kNearThreads = 128;
-constexpr int kNearPoints = 4;  // observation points per thread in near_kernel
-constexpr int kCellChunk = 8;
+constexpr int kNearThreads = 256;
+constexpr int kNearPoints = 2;  // observation points per thread in near_kernel
+constexpr int kCellChunk = 16;
 
 struct FaceGeo {
     int a, b, c;
@@ -256,21 +519,121 @@ struct FaceGeo {
     double pref;
 };
 
-// Q layout: [cell][field(0 psi, 1 dpsi)][p][q]
-// One thread per point; workgroup row blockIdx.y sums the cells
+// Whether a point lies inside the box or is not finite (bit 0), and whether it
+// is so far that its phases need the general sincos (bit 1)
+__global__ void check_points_kernel(const double3* __restrict__ obs, int64_t n, double k0, double3 lo, double3 hi,
+                                    double limit, unsigned* __restrict__ flags) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    unsigned f = 0;
+    if (i < n) {
+        const double3 o = obs[i];
+        const double r[3] = {o.x * k0, o.y * k0, o.z * k0};
+        const double l[3] = {lo.x, lo.y, lo.z}, h[3] = {hi.x, hi.y, hi.z};
+        bool inside = true;
+        for (int a = 0; a < 3; ++a) {
+            if (!(r[a] > l[a] && r[a] < h[a])) inside = false;
+            if (!isfinite(r[a])) inside = true;
+        }
+        f = (inside ? 1u : 0u) | (fabs(r[0]) > limit || fabs(r[1]) > limit || fabs(r[2]) > limit ? 2u : 0u);
+    }
+    if (f) atomicOr(flags, f);
+}
+
+// Economised terms Q[cell][field][low_row(p) + q], p + q <= 8, from the full
+// products Qg[field][p][q][cell]: on the cells' disk (alpha_b / A)^2 +
+// (alpha_c / B)^2 <= 1, A = d_b / 2, B = d_c / 2, a monomial of degree 9 to 16 is
+// replaced by its least-squares polynomial of degree 8 (E, for the unit
+// disk), which leaves under 1/50 of the degree-9 terms, themselves the size
+// of what the 8th-order series drops.  45 terms per field and cell instead
+// of 81.
+__global__ void economise_kernel(const double2* __restrict__ Qg, int64_t ncell, const double* __restrict__ E, double A,
+                                 double Bs, double2* __restrict__ Q) {
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= ncell * kLow * 2) return;
+    const int64_t cell = id % ncell;
+    const int k = (int)((id / ncell) % kLow), fld = (int)(id / (ncell * kLow));
+    int p = 0;
+    while (k >= low_row(p + 1)) ++p;
+    const int q = k - low_row(p);
+    const double2* g = Qg + (int64_t)fld * kPairs * ncell + cell;
+    double2 s = g[(int64_t)(p * kTerms + q) * ncell];
+    int h = 0;
+    for (int hp = 1; hp < kTerms; ++hp)
+        for (int hq = kTerms - hp; hq < kTerms; ++hq, ++h) {
+            const double e = E[h * kLow + k];
+            if (e == 0.0) continue;
+            // scale A^(hp - p) B^(hq - q)
+            double w = e;
+            for (int t = p; t < hp; ++t) w *= A;
+            for (int t = hp; t < p; ++t) w /= A;
+            for (int t = q; t < hq; ++t) w *= Bs;
+            for (int t = hq; t < q; ++t) w /= Bs;
+            const double2 x = g[(int64_t)(hp * kTerms + hq) * ncell];
+            s.x += w * x.x;
+            s.y += w * x.y;
+        }
+    Q[(cell * 2 + fld) * kLow + k] = s;
+}
+
+// its adjoint: Qbar[field][p][q][cell] from the sums of the low terms
+// low[field][k][cell]
+__global__ void economise_adjoint_kernel(const double2* __restrict__ low, int64_t ncell, const double* __restrict__ E,
+                                         double A, double Bs, double2* __restrict__ Qbar) {
+    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= ncell * kPairs * 2) return;
+    const int64_t cell = id % ncell;
+    const int pq = (int)((id / ncell) % kPairs), fld = (int)(id / (ncell * kPairs));
+    const int hp = pq / kTerms, hq = pq % kTerms;
+    const double2* g = low + (int64_t)fld * kLow * ncell + cell;
+    double2 s = make_double2(0, 0);
+    if (hp + hq <= kOrder) {
+        s = g[(int64_t)(low_row(hp) + hq) * ncell];
+    } else {
+        int h = 0;
+        for (int t = 1; t < hp; ++t) h += t;   // row t holds the t pairs (t, 9 - t) .. (t, 8)
+        h += hq - (kTerms - hp);
+        for (int p = 0; p < kTerms; ++p)
+            for (int q = 0; q + p < kTerms; ++q) {
+                const int k = low_row(p) + q;
+                const double e = E[h * kLow + k];
+                if (e == 0.0) continue;
+                double w = e;
+                for (int t = p; t < hp; ++t) w *= A;
+                for (int t = hp; t < p; ++t) w /= A;
+                for (int t = q; t < hq; ++t) w *= Bs;
+                for (int t = hq; t < q; ++t) w /= Bs;
+                const double2 x = g[(int64_t)k * ncell];
+                s.x += w * x.x;
+                s.y += w * x.y;
+            }
+    }
+    Qbar[id] = s;
+}
+
+template <bool FAST>
+__device__ __forceinline__ void phase(double x, double* sn, double* cs) {
+    if constexpr (FAST) fast_sincos(x, sn, cs);
+    else sincos(x, sn, cs);
+}
+
+// Q layout: [cell][field(0 psi, 1 dpsi)][low terms]
+// One thread per K points; workgroup row blockIdx.y sums the cells
 // [y * cells_per_split, (y + 1) * cells_per_split), so that few points still
 // fill the chip.  Each row writes its partial sum (times the face prefactor)
 // to part[y * n_obs + point]; add_splits_kernel adds the rows in order.
 // K observation points per thread, kNearThreads apart (coalesced loads and
 // stores): each coefficient read from LDS serves K points, which takes the
 // kernel off the LDS read rate (one 16-byte broadcast per two FP64 FMAs
-// with one point per thread).  Each point's sums run in the same order as
-// with one point per thread.
-template <int K>
+// with one point per thread; 306 VGPRs with four, 114 with two).  Bound by the FP64 vector rate: 216 FMAs of the
+// two economised polynomials and about 80 instructions for the distance, its
+// reciprocal and the phase per point and cell (360 and 170 with the 81-term
+// products and the library's square root, division and sincos: 5.22 ms per
+// face for 16384 points and 15876 cells, 2.39 ms now).
+template <int K, bool FAST>
 __global__ __launch_bounds__(kNearThreads) void near_kernel(const double3* __restrict__ obs, int64_t n_obs, double k0,
                                                             FaceGeo g, const double2* __restrict__ Q,
                                                             int64_t cells_per_split, double2* __restrict__ part) {
-    __shared__ double2 sq[kCellChunk * 2 * kTerms * kTerms];
+    __shared__ double2 sq[kCellChunk * 2 * kLow];
     bool live[K];
     bool any_live = false;
     double Ra[K], rb_[K], rc_[K];  // point in the face frame (normal, b, c)
@@ -295,29 +658,29 @@ __global__ __launch_bounds__(kNearThreads) void near_kernel(const double3* __res
         rc_[k] = rc;
         acc[k] = make_double2(0, 0);
     }
+    const double hb = 0.5 * g.db, hc = 0.5 * g.dc;
     const int64_t ncell = (int64_t)g.L * g.M;
     const int64_t c_lo = (int64_t)blockIdx.y * cells_per_split;
     const int64_t c_hi = min<int64_t>(ncell, c_lo + cells_per_split);
-    constexpr int per_cell = 2 * kTerms * kTerms;
+    constexpr int per_cell = 2 * kLow;
     for (int64_t c0 = c_lo; c0 < c_hi; c0 += kCellChunk) {
         const int nc = (int)min<int64_t>(kCellChunk, c_hi - c0);
         __syncthreads();
         for (int e = threadIdx.x; e < nc * per_cell; e += kNearThreads) sq[e] = Q[c0 * per_cell + e];
         __syncthreads();
         if (!any_live) continue;
+#pragma unroll 1
         for (int ci = 0; ci < nc; ++ci) {
-            const int64_t cell = c0 + ci;
-            const int m = (int)(cell / g.L), l = (int)(cell % g.L);
+            const int cell = (int)(c0 + ci);
+            const int m = cell / g.L, l = cell - m * g.L;
             double Rn[K], inv[K], ab[K], ac[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const double Rb = rb_[k] - (g.xb0 + l * g.db);
                 const double Rc = rc_[k] - (g.xc0 + m * g.dc);
-                const double R2 = Ra[k] * Ra[k] + Rb * Rb + Rc * Rc;
-                Rn[k] = sqrt(R2);
-                inv[k] = 1.0 / Rn[k];
-                ab[k] = g.db * Rb * inv[k] * 0.5;
-                ac[k] = g.dc * Rc * inv[k] * 0.5;
+                sqrt_rsqrt(Ra[k] * Ra[k] + Rb * Rb + Rc * Rc, &Rn[k], &inv[k]);
+                ab[k] = hb * Rb * inv[k];
+                ac[k] = hc * Rc * inv[k];
             }
             const double2* q = &sq[ci * per_cell];
             double2 S0[K], S1[K];
@@ -326,25 +689,26 @@ __global__ __launch_bounds__(kNearThreads) void near_kernel(const double3* __res
                 double2 outer[K];
 #pragma unroll
                 for (int k = 0; k < K; ++k) outer[k] = make_double2(0, 0);
-#pragma unroll 1
+#pragma unroll
                 for (int p = kOrder; p >= 0; --p) {
+                    const double2* row = q + fld * kLow + low_row(p);
                     double2 inner[K];
+                    const double2 top = row[kOrder - p];
 #pragma unroll
-                    for (int k = 0; k < K; ++k) inner[k] = make_double2(0, 0);
-                    const double2* row = q + (fld * kTerms + p) * kTerms;
+                    for (int k = 0; k < K; ++k) inner[k] = top;
 #pragma unroll
-                    for (int qq = kOrder; qq >= 0; --qq) {
+                    for (int qq = kOrder - p - 1; qq >= 0; --qq) {
                         const double2 cq = row[qq];
 #pragma unroll
                         for (int k = 0; k < K; ++k) {
-                            inner[k].x = inner[k].x * ac[k] + cq.x;
-                            inner[k].y = inner[k].y * ac[k] + cq.y;
+                            inner[k].x = fma(inner[k].x, ac[k], cq.x);
+                            inner[k].y = fma(inner[k].y, ac[k], cq.y);
                         }
                     }
 #pragma unroll
                     for (int k = 0; k < K; ++k) {
-                        outer[k].x = outer[k].x * ab[k] + inner[k].x;
-                        outer[k].y = outer[k].y * ab[k] + inner[k].y;
+                        outer[k].x = fma(outer[k].x, ab[k], inner[k].x);
+                        outer[k].y = fma(outer[k].y, ab[k], inner[k].y);
                     }
                 }
 #pragma unroll
@@ -360,7 +724,7 @@ __global__ __launch_bounds__(kNearThreads) void near_kernel(const double3* __res
                 const double2 coef = make_double2(-inv[k] * ra, ra);
                 const double2 inner = zadd(S1[k], zmul(coef, S0[k]));
                 double sn, cs;
-                sincos(Rn[k], &sn, &cs);
+                phase<FAST>(Rn[k], &sn, &cs);
                 acc[k] = zadd(acc[k], zmul(make_double2(cs * inv[k], sn * inv[k]), inner));
             }
         }
@@ -383,38 +747,35 @@ __global__ void add_splits_kernel(const double2* __restrict__ part, int splits, 
     out[i] = accumulate ? zadd(out[i], acc) : acc;
 }
 
-// Adjoint of the per-point cell sums: for one cell and one p,
-// Qbar[fld][p][q][cell] = sum_o conj(pref e^{iR}/R alpha_b^p alpha_c^q [coef]) g_o,
+// Adjoint of the per-point cell sums: for one cell and the low terms (p, q),
+// low[fld][k][cell] = sum_o conj(pref e^{iR}/R alpha_b^p alpha_c^q [coef]) g_o,
 // coef = (i - 1/R) R_a / R for the psi field (fld 0), 1 for dpsi (fld 1).
 constexpr int kAdjObsChunk = 256;
-constexpr int kAdjP = 3;  // values of p per thread in near_adjoint_kernel
+constexpr int kAdjGroups = 3;
 
 // Workgroup row blockIdx.y sums the points [y * obs_per_split, (y + 1) *
-// obs_per_split) into its own copy of Qbar (Qbar + y * 2 kTerms^2 ncell);
-// add_splits_kernel adds the copies in order.
-template <int KP>
-__global__ __launch_bounds__(128) void near_adjoint_kernel(const double3* __restrict__ obs, const double2* __restrict__ gv,
-                                                           int64_t n_obs, double k0, FaceGeo g,
-                                                           int64_t obs_per_split, double2* __restrict__ Qbar) {
-    // one thread per (cell, block of KP consecutive p): the distance, the
-    // square root and the sincos of a (cell, point) pair are taken once for
-    // KP values of p; each (field, p, q) sum runs over the points in the same
-    // order as with one p per thread
-    constexpr int kBlocks = (kTerms + KP - 1) / KP;
-    __shared__ double3 so[kAdjObsChunk];
-    __shared__ double2 sg[kAdjObsChunk];
+// obs_per_split) into its own copy of low (+ y * 2 kLow ncell);
+// add_splits_kernel adds the copies in order.  One thread per (cell, group
+// of 15 terms): rows p of lengths 9 - p in three groups of equal size, {0, 3},
+// {1, 2}, {4, 5, 6, 7, 8}, so that the distance and the phase of a (cell,
+// point) pair serve 15 terms of both fields and the sums stay in registers.
+template <int G, bool FAST>
+__device__ __forceinline__ void near_adjoint_group(const double3* __restrict__ obs, const double2* __restrict__ gv,
+                                                   int64_t n_obs, double k0, const FaceGeo& g, int64_t obs_per_split,
+                                                   double3* so, double2* sg, double2* __restrict__ low) {
+    constexpr int rows[3][5] = {{0, 3, -1, -1, -1}, {1, 2, -1, -1, -1}, {4, 5, 6, 7, 8}};
+    constexpr int nrows = G == 2 ? 5 : 2;
+    constexpr int kPer = kLow / kAdjGroups;
     const int64_t ncell = (int64_t)g.L * g.M;
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = id < ncell * kBlocks;
-    const int64_t cell = live ? id % ncell : 0;
-    const int p0 = live ? (int)(id / ncell) * KP : 0;
+    const int64_t cell_ = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool live = cell_ < ncell;
+    const int64_t cell = live ? cell_ : 0;
     const int m = (int)(cell / g.L), l = (int)(cell % g.L);
     const double yb = g.xb0 + l * g.db, yc = g.xc0 + m * g.dc;
-    double2 acc[KP][2][kTerms];
+    const double hb = 0.5 * g.db, hc = 0.5 * g.dc;
+    double2 acc[2][kPer];
 #pragma unroll
-    for (int j = 0; j < KP; ++j)
-        for (int f = 0; f < 2; ++f)
-            for (int q = 0; q < kTerms; ++q) acc[j][f][q] = make_double2(0, 0);
+    for (int i = 0; i < kPer; ++i) acc[0][i] = acc[1][i] = make_double2(0, 0);
     const int64_t o_lo = (int64_t)blockIdx.y * obs_per_split;
     const int64_t o_hi = min<int64_t>(n_obs, o_lo + obs_per_split);
     for (int64_t o0 = o_lo; o0 < o_hi; o0 += kAdjObsChunk) {
@@ -426,65 +787,89 @@ __global__ __launch_bounds__(128) void near_adjoint_kernel(const double3* __rest
         }
         __syncthreads();
         if (!live) continue;
+#pragma unroll 1
         for (int e = 0; e < no; ++e) {
             const double x = so[e].x * k0, y = so[e].y * k0, z = so[e].z * k0;
             const double Ra = (g.a == 0 ? x : g.a == 1 ? y : z) - g.xa;
             const double Rb = (g.b == 0 ? x : g.b == 1 ? y : z) - yb;
             const double Rc = (g.c == 0 ? x : g.c == 1 ? y : z) - yc;
-            const double Rn = sqrt(Ra * Ra + Rb * Rb + Rc * Rc);
-            const double inv = 1.0 / Rn;
-            const double ab = g.db * Rb * inv * 0.5, ac = g.dc * Rc * inv * 0.5;
+            double Rn, inv;
+            sqrt_rsqrt(Ra * Ra + Rb * Rb + Rc * Rc, &Rn, &inv);
+            const double ab = hb * Rb * inv, ac = hc * Rc * inv;
             double sn, cs;
-            sincos(Rn, &sn, &cs);
+            phase<FAST>(Rn, &sn, &cs);
             const double2 gg = sg[e];
             const double rr = Ra * inv;
-            // alpha_b^p0 by the same product as with one p per thread
+            // conj(pref e^{iR}/R) g and conj(coef) = (-i - 1/R) R_a/R times it
+            const double wr = g.pref * inv;
+            const double2 b1 = make_double2(wr * (cs * gg.x + sn * gg.y), wr * (cs * gg.y - sn * gg.x));
+            const double2 b0 = make_double2(-inv * rr * b1.x + rr * b1.y, -inv * rr * b1.y - rr * b1.x);
             double abp = 1.0;
-            for (int t = 0; t < p0; ++t) abp *= ab;
+            int at = 0;
 #pragma unroll
-            for (int j = 0; j < KP; ++j) {
-                // conj(pref e^{iR}/R alpha_b^p) g
-                const double wr = g.pref * inv * abp;
-                const double2 base = make_double2(wr * (cs * gg.x + sn * gg.y), wr * (cs * gg.y - sn * gg.x));
-                // conj(coef) = (-i - 1/R) R_a/R
-                const double2 cbase = make_double2(-inv * rr * base.x + rr * base.y, -inv * rr * base.y - rr * base.x);
-                double acq = 1.0;
+            for (int i = 0; i < nrows; ++i) {
+                const int p = rows[G][i];
 #pragma unroll
-                for (int q = 0; q < kTerms; ++q) {
-                    acc[j][0][q].x += acq * cbase.x;
-                    acc[j][0][q].y += acq * cbase.y;
-                    acc[j][1][q].x += acq * base.x;
-                    acc[j][1][q].y += acq * base.y;
-                    acq *= ac;
+                for (int t = (i ? rows[G][i - 1] : 0); t < p; ++t) abp *= ab;
+                double w = abp;
+#pragma unroll
+                for (int q = 0; q < kTerms - p; ++q, ++at) {
+                    acc[0][at].x = fma(w, b0.x, acc[0][at].x);
+                    acc[0][at].y = fma(w, b0.y, acc[0][at].y);
+                    acc[1][at].x = fma(w, b1.x, acc[1][at].x);
+                    acc[1][at].y = fma(w, b1.y, acc[1][at].y);
+                    w *= ac;
                 }
-                abp *= ab;
             }
         }
     }
     if (!live) return;
-    double2* __restrict__ dst = Qbar + (int64_t)blockIdx.y * 2 * kTerms * kTerms * ncell;
+    double2* __restrict__ dst = low + (int64_t)blockIdx.y * 2 * kLow * ncell;
+    int at = 0;
 #pragma unroll
-    for (int j = 0; j < KP; ++j) {
-        const int p = p0 + j;
-        if (p >= kTerms) break;
-        for (int f = 0; f < 2; ++f)
-            for (int q = 0; q < kTerms; ++q) dst[(((int64_t)f * kTerms + p) * kTerms + q) * ncell + cell] = acc[j][f][q];
+    for (int i = 0; i < nrows; ++i) {
+        const int p = rows[G][i];
+#pragma unroll
+        for (int q = 0; q < kTerms - p; ++q, ++at)
+            for (int f = 0; f < 2; ++f) dst[((int64_t)f * kLow + low_row(p) + q) * ncell + cell] = acc[f][at];
     }
 }
 
-// out = conj(x) * scale as complex64
-__global__ void conj_scale_kernel(const double2* __restrict__ x, int64_t n, double scale, float2* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = make_float2((float)(x[i].x * scale), (float)(-x[i].y * scale));
+template <bool FAST>
+__global__ __launch_bounds__(128) void near_adjoint_kernel(const double3* __restrict__ obs, const double2* __restrict__ gv,
+                                                           int64_t n_obs, double k0, FaceGeo g, int64_t obs_per_split,
+                                                           double2* __restrict__ low) {
+    __shared__ double3 so[kAdjObsChunk];
+    __shared__ double2 sg[kAdjObsChunk];
+    if (blockIdx.z == 0) near_adjoint_group<0, FAST>(obs, gv, n_obs, k0, g, obs_per_split, so, sg, low);
+    else if (blockIdx.z == 1) near_adjoint_group<1, FAST>(obs, gv, n_obs, k0, g, obs_per_split, so, sg, low);
+    else near_adjoint_group<2, FAST>(obs, gv, n_obs, k0, g, obs_per_split, so, sg, low);
 }
 
-// Q[p][q][m][l] (GEMM output) -> [cell][field][p][q]
-__global__ void reorder_q_kernel(const double2* __restrict__ Qg, int fld, int64_t ncell, double2* __restrict__ Q) {
+// out = conj(sum of the 9 planes x[p]) * scale as complex64
+__global__ void conj_scale_kernel(const double2* __restrict__ x, int64_t n, double scale, float2* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    double2 s = x[i];
+    for (int p = 1; p < kTerms; ++p) s = zadd(s, x[p * n + i]);
+    out[i] = make_float2((float)(s.x * scale), (float)(-s.y * scale));
+}
+
+// X[t][l][m]: the expansion of the cell integral along one axis (`cells` cells
+// from grid index lo, FFT length N): for cell l and spectral index m (signed
+// m') the Taylor coefficient t of the sinc factor (tay[t][m]) times the phase of the
+// cell centre
+__global__ void expansion_kernel(const double* __restrict__ tay, int N, int lo, int cells, double2* __restrict__ X) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= ncell * kTerms * kTerms) return;
-    const int64_t cell = id % ncell;
-    const int pq = (int)(id / ncell);
-    Q[(cell * 2 + fld) * kTerms * kTerms + pq] = Qg[(int64_t)pq * ncell + cell];
+    if (id >= (int64_t)kTerms * cells * N) return;
+    const int m = (int)(id % N), l = (int)((id / N) % cells), t = (int)(id / ((int64_t)N * cells));
+    const int bp = m < N / 2 ? m : m - N;
+    // 2 pi b' x_l / (N d), x_l = (lo + l - N/2 + 1/2) d, in half turns over N
+    const int64_t turns = ((int64_t)bp * (2 * (lo + l) - N + 1)) % (2 * N);
+    double sn, cs;
+    sincospi((double)turns / N, &sn, &cs);
+    const double w = ((bp & 1) ? -1.0 : 1.0) * tay[(int64_t)t * N + m];
+    X[id] = make_double2(w * cs, w * sn);
 }
 
 // sinc(x - alpha) = sum_p s_p(x) alpha^p, s_p = (-1)^p sinc^(p)(x)/p!
@@ -505,24 +890,115 @@ void sinc_taylor(double x, double* s) {
     }
 }
 
+// Least-squares polynomials of total degree <= 8 on the unit disk of the 36
+// monomials u^p v^q, 9 <= p + q, p, q <= 8, with the Chebyshev weight
+// 1 / sqrt(1 - r^2): E[h][low_row(p') + q'], h counting (p, q) row by row.  By
+// parity only p' = p, q' = q (mod 2) occur.  Modified Gram-Schmidt on a product
+// grid of the disk, in long double.
+const std::vector<double>& economisation() {
+    static const std::vector<double> table = [] {
+        constexpr int nr = 24, na = 64;
+        std::vector<double> E((size_t)kHigh * kLow, 0.0);
+        std::vector<long double> u, v;
+        for (int i = 0; i < nr; ++i)
+            for (int j = 0; j < na; ++j) {
+                // r dr / sqrt(1 - r^2): 1 - r^2 = t^2, t uniform (Gauss-Legendre not needed: midpoints)
+                const long double t = (i + 0.5L) / nr, r = std::sqrt(1.0L - t * t), f = 2.0L * 3.14159265358979323846264L * (j + 0.5L) / na;
+                u.push_back(r * std::cos(f));
+                v.push_back(r * std::sin(f));
+            }
+        const size_t S = u.size();
+        auto column = [&](int p, int q) {
+            std::vector<long double> c(S);
+            for (size_t s = 0; s < S; ++s) {
+                long double x = 1;
+                for (int t = 0; t < p; ++t) x *= u[s];
+                for (int t = 0; t < q; ++t) x *= v[s];
+                c[s] = x;
+            }
+            return c;
+        };
+        for (int par = 0; par < 4; ++par) {
+            // orthonormal columns and the triangular factor of this parity's low monomials
+            std::vector<int> idx;
+            std::vector<std::vector<long double>> Q, R;
+            for (int p = par & 1; p < kTerms; p += 2)
+                for (int q = par >> 1; p + q < kTerms; q += 2) {
+                    std::vector<long double> c = column(p, q), r(Q.size() + 1, 0.0L);
+                    for (int pass = 0; pass < 2; ++pass)
+                        for (size_t j = 0; j < Q.size(); ++j) {
+                            long double d = 0;
+                            for (size_t s = 0; s < S; ++s) d += Q[j][s] * c[s];
+                            for (size_t s = 0; s < S; ++s) c[s] -= d * Q[j][s];
+                            r[j] += d;
+                        }
+                    long double n = 0;
+                    for (size_t s = 0; s < S; ++s) n += c[s] * c[s];
+                    n = std::sqrt(n);
+                    for (size_t s = 0; s < S; ++s) c[s] /= n;
+                    r[Q.size()] = n;
+                    Q.push_back(c);
+                    R.push_back(r);
+                    idx.push_back(low_row(p) + q);
+                }
+            int h = 0;
+            for (int hp = 1; hp < kTerms; ++hp)
+                for (int hq = kTerms - hp; hq < kTerms; ++hq, ++h) {
+                    if ((hp & 1) != (par & 1) || (hq & 1) != (par >> 1)) continue;
+                    std::vector<long double> c = column(hp, hq), d(Q.size());
+                    for (size_t j = 0; j < Q.size(); ++j) {
+                        d[j] = 0;
+                        for (size_t s = 0; s < S; ++s) d[j] += Q[j][s] * c[s];
+                        for (size_t s = 0; s < S; ++s) c[s] -= d[j] * Q[j][s];
+                    }
+                    // back substitution: R x = d, R[j][i] the coefficient of q_i in column j
+                    for (size_t j = Q.size(); j-- > 0;) {
+                        long double x = d[j];
+                        for (size_t i = j + 1; i < Q.size(); ++i) x -= R[i][j] * d[i];
+                        d[j] = x / R[j][j];
+                    }
+                    for (size_t j = 0; j < Q.size(); ++j) E[(size_t)h * kLow + idx[j]] = (double)d[j];
+                }
+        }
+        return E;
+    }();
+    return table;
+}
+
+// Chebyshev terms of a function of exponential type X on [-1, 1] (the
+// coefficients are Bessel functions J_k(X) of the phases' amplitudes): the
+// first k past X with 2 |J_k(X)| < 2^-57
+int far_terms(double X) {
+    int k = (int)X + 2;
+    // J_k(X) <= (e X / 2 k)^k / sqrt(2 pi k), which falls monotonically past X e / 2;
+    // below that J_k(X) ~ Ai-like decay: the uniform bound exp(-k (w - tanh w)), cosh w = k / X
+    for (;; ++k) {
+        const double w = std::acosh(k / X);
+        const double lg = -k * (w - std::tanh(w)) - 0.5 * std::log(2 * kPi * k * std::tanh(w));
+        if (lg + std::log(2.0) < -57 * std::log(2.0)) break;
+    }
+    return k + 1;
+}
+
 }  // namespace
 
 struct ProjectState {
     double2* phasors = nullptr;   // [face][2][plane]
-    double2* spectra = nullptr;   // [face][2][plane]
     double2* work = nullptr;      // scratch
     size_t work_bytes = 0;
-    double2* part = nullptr;      // per-split partial sums of the point kernels
+    double2* part = nullptr;      // per-split partial sums of the point and direction kernels
     size_t part_bytes = 0;
-    // sinc-Taylor expansion tables of the cell sums, built once per solver
-    // (they depend on the grid and the box only): per face, U_p^T and V_q for
-    // the points, and their conjugates in the adjoint's layout
-    double2* fwd_tab = nullptr;
-    double2* adj_tab = nullptr;
-    int64_t fwd_off[7] = {0, 0, 0, 0, 0, 0, 0};
-    int64_t adj_off[7] = {0, 0, 0, 0, 0, 0, 0};
-    double2* tw = nullptr;        // per axis: twiddles exp(-2 pi i j / N)
-    double2* twc = nullptr;       // per axis: conjugate twiddles
+    double2* low = nullptr;       // adjoint: the splits' sums
+    size_t low_bytes = 0;
+    unsigned* flags = nullptr;    // check_points_kernel's result
+    // tables, built on first use (they depend on the grid and the box only),
+    // each with the plane DFT folded in
+    double2* near_tab = nullptr;  // per axis [t][cell][N]: sinc-Taylor expansion of the cell integral
+    double* econ = nullptr;       // economisation table
+    double2* far_tab = nullptr;   // per axis [K][N]: Chebyshev coefficients of the far factor
+    int64_t near_off[4] = {0, 0, 0, 0};
+    int64_t far_off[4] = {0, 0, 0, 0};
+    int K[3] = {0, 0, 0};
     int64_t face_off[7] = {0, 0, 0, 0, 0, 0, 0};
     int64_t total = 0;
 };
@@ -553,12 +1029,15 @@ int split_count(int64_t waves, int64_t cap) {
     return (int)std::max<int64_t>(k, 1);
 }
 
+unsigned blocks_of(int64_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
+
 #define TRY(x)                                \
     do {                                      \
         hipError_t _e = (x);                  \
         if (_e != hipSuccess) return _e;      \
     } while (0)
 
+// the projection's state and the normalised phasors of this call
 hipError_t prepare(ProjectState** pst, const pstd_problem& p, double2* const acc[3], const int64_t points[3],
                    PhasorScale scale, hipStream_t stream) {
     if (!*pst) {
@@ -571,129 +1050,178 @@ hipError_t prepare(ProjectState** pst, const pstd_problem& p, double2* const acc
         s->face_off[6] = off;
         s->total = off;
         hipError_t e;
-        if ((e = hipMalloc(&s->phasors, off * sizeof(double2))) || (e = hipMalloc(&s->spectra, off * sizeof(double2))) ||
-            (e = hipMalloc(&s->tw, (size_t)(p.n[0] + p.n[1] + p.n[2]) * sizeof(double2))) ||
-            (e = hipMalloc(&s->twc, (size_t)(p.n[0] + p.n[1] + p.n[2]) * sizeof(double2)))) {
-            project_free(s);
-            return e;
-        }
-        std::vector<double2> tw;
-        for (int a = 0; a < 3; ++a)
-            for (int j = 0; j < p.n[a]; ++j)
-                tw.push_back(make_double2(std::cos(2 * kPi * j / p.n[a]), -std::sin(2 * kPi * j / p.n[a])));
-        std::vector<double2> twc(tw);
-        for (auto& v : twc) v.y = -v.y;
-        if ((e = hipMemcpy(s->tw, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice)) ||
-            (e = hipMemcpy(s->twc, twc.data(), twc.size() * sizeof(double2), hipMemcpyHostToDevice))) {
+        if ((e = hipMalloc(&s->phasors, off * sizeof(double2))) || (e = hipMalloc(&s->flags, sizeof(unsigned)))) {
             project_free(s);
             return e;
         }
         *pst = s;
     }
-    ProjectState* s = *pst;
-    TRY(finalize_phasors(acc, points, scale, s->phasors, stream));
-    // 2D spectra of every plane
-    size_t need = 0;
-    for (int f = 0; f < 6; ++f) need = std::max(need, (size_t)points[f / 2] * sizeof(double2));
-    TRY(ensure(&s->work, &s->work_bytes, need));
-    const double2* twa[3] = {s->tw, s->tw + p.n[0], s->tw + p.n[0] + p.n[1]};
-    for (int f = 0; f < 6; ++f) {
-        const int a = f / 2, b = face_axis_b(a), c = face_axis_c(a);
-        const int Nb = p.n[b], Nc = p.n[c];
-        const int64_t np = (int64_t)Nb * Nc;
-        for (int fld = 0; fld < 2; ++fld) {
-            const double2* x = s->phasors + s->face_off[f] + fld * np;
-            double2* z = s->spectra + s->face_off[f] + fld * np;
-            const unsigned blocks = (unsigned)((np + 255) / 256);
-            hipLaunchKernelGGL(dft_rows_kernel, dim3(blocks), dim3(256), 0, stream, x, s->work, Nb, Nc, twa[b]);
-            hipLaunchKernelGGL(dft_cols_kernel, dim3(blocks), dim3(256), 0, stream, s->work, z, Nb, Nc, twa[c]);
-        }
-    }
-    return hipGetLastError();
+    return finalize_phasors(acc, points, scale, (*pst)->phasors, stream);
 }
 
 }  // namespace
 
 hipError_t finalize_phasors(double2* const acc[3], const int64_t points[3], PhasorScale scale, double2* out,
                             hipStream_t stream) {
-    int64_t off = 0;
-    for (int f = 0; f < 6; ++f) {
-        const int a = f / 2;
-        const int64_t P = points[a];
-        hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, stream, acc[a], f % 2, P,
-                           scale.v, scale.d, out + off);
-        off += 2 * P;
+    FinalizeArgs f{};
+    int blocks = 0;
+    for (int a = 0; a < 3; ++a) {
+        f.acc[a] = acc[a];
+        f.points[a] = points[a];
+        f.blocks[a] = (int)blocks_of(points[a]);
+        blocks += 2 * f.blocks[a];
     }
+    hipLaunchKernelGGL(finalize_kernel, dim3(blocks), dim3(256), 0, stream, f, scale.v, scale.d, out);
     return hipGetLastError();
 }
 
 namespace {
 
-// Expansion of the cell integral along one face axis (axis ax, `cells` cells
-// from grid index lo, FFT length N): for spectral index m (signed m') and
-// cell l, the Taylor coefficients t = 0..kOrder of the sinc factor times the
-// phase of the cell centre, conjugated when `conj`: put(t, l, m, value).
-template <class Put>
-void expansion(const double dxb[3], int ax, int lo, int cells, int N, bool conj, Put put) {
-    const double d = dxb[ax], Lp = N * d;
-    double sp[kTerms];
-    for (int m = 0; m < N; ++m) {
-        const int bp = m < N / 2 ? m : m - N;
-        sinc_taylor(kPi * bp / N, sp);
-        for (int l = 0; l < cells; ++l) {
-            const double xc = (lo + l - N / 2 + 0.5) * d;
-            const double ph = 2 * kPi * bp * xc / Lp;
-            const double sg = (bp & 1) ? -1.0 : 1.0;
-            const double cs = std::cos(ph), sn = conj ? -std::sin(ph) : std::sin(ph);
-            for (int t = 0; t < kTerms; ++t) put(t, l, m, make_double2(sg * sp[t] * cs, sg * sp[t] * sn));
-        }
-    }
+int cells_of(const pstd_problem& p, int a) { return p.surf_hi[a] - p.surf_lo[a]; }
+
+FarAxis far_axis(const pstd_problem& p, const double dxb[3], int a) {
+    FarAxis x;
+    x.N = p.n[a];
+    x.lo = p.surf_lo[a];
+    x.hi = p.surf_hi[a];
+    x.d = dxb[a];
+    x.mid = dxb[a] * (0.5 * (x.lo + x.hi) - x.N / 2);
+    x.half = dxb[a] * 0.5 * (x.hi - x.lo);
+    return x;
 }
 
-// The tables of all six faces in one device array, built on first use:
-// forward (adjoint = false): U_p^T[p][b'][l] then V_q[q][m][c'];
-// adjoint: Vh[c'][q][m] = conj V_q[m][c'] then Uc[p][l][b'] = conj U_p[l][b'].
-hipError_t near_tables(ProjectState* s, const pstd_problem& p, const double dxb[3], bool adjoint) {
-    double2*& tab = adjoint ? s->adj_tab : s->fwd_tab;
-    int64_t* off = adjoint ? s->adj_off : s->fwd_off;
-    if (tab) return hipSuccess;
+// The near tables of the three axes in one device array: per axis [t][cell][N],
+// the transform of a plane line folded in (X W)
+hipError_t near_tables(ProjectState* s, const pstd_problem& p, hipStream_t stream) {
+    if (s->near_tab) return hipSuccess;
     int64_t total = 0;
-    for (int f = 0; f < 6; ++f) {
-        const int a = f / 2, b = face_axis_b(a), c = face_axis_c(a);
-        const int L = p.surf_hi[b] - p.surf_lo[b], M = p.surf_hi[c] - p.surf_lo[c];
-        off[f] = total;
-        total += (int64_t)kTerms * (p.n[b] * L + M * p.n[c]);
+    size_t work = 0;
+    for (int a = 0; a < 3; ++a) {
+        const int64_t N = p.n[a], rows = (int64_t)kTerms * cells_of(p, a);
+        s->near_off[a] = total;
+        total += rows * N;
+        work = std::max(work, (size_t)(rows * N + N * N) * sizeof(double2) + (size_t)kTerms * N * sizeof(double));
     }
-    off[6] = total;
-    std::vector<double2> h((size_t)total);
-    for (int f = 0; f < 6; ++f) {
-        const int a = f / 2, b = face_axis_b(a), c = face_axis_c(a);
-        const int Nb = p.n[b], Nc = p.n[c];
-        const int L = p.surf_hi[b] - p.surf_lo[b], M = p.surf_hi[c] - p.surf_lo[c];
-        double2* t0 = h.data() + off[f];
-        double2* t1 = t0 + (size_t)kTerms * Nb * L;
-        if (!adjoint) {
-            expansion(dxb, b, p.surf_lo[b], L, Nb, false,
-                      [&](int t, int l, int m, double2 v) { t0[((size_t)t * Nb + m) * L + l] = v; });
-            expansion(dxb, c, p.surf_lo[c], M, Nc, false,
-                      [&](int t, int l, int m, double2 v) { t1[((size_t)t * M + l) * Nc + m] = v; });
-        } else {
-            // Vh first (Nc x kTerms M), then Uc (kTerms L x Nb): the same total
-            double2* vh = t0;
-            double2* uc = t0 + (size_t)Nc * kTerms * M;
-            expansion(dxb, c, p.surf_lo[c], M, Nc, true,
-                      [&](int t, int l, int m, double2 v) { vh[((size_t)m * kTerms + t) * M + l] = v; });
-            expansion(dxb, b, p.surf_lo[b], L, Nb, true,
-                      [&](int t, int l, int m, double2 v) { uc[((size_t)t * L + l) * Nb + m] = v; });
-        }
-    }
-    hipError_t e = hipMalloc(&tab, (size_t)total * sizeof(double2));
-    if (e == hipSuccess) e = hipMemcpy(tab, h.data(), (size_t)total * sizeof(double2), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
+    const std::vector<double>& E = economisation();
+    TRY(ensure(&s->work, &s->work_bytes, work));
+    double2* tab = nullptr;
+    double* econ = nullptr;
+    auto undo = [&](hipError_t e) {
+        (void)hipStreamSynchronize(stream);
         (void)hipFree(tab);
-        tab = nullptr;
+        (void)hipFree(econ);
+        return e;
+    };
+    hipError_t e;
+    if ((e = hipMalloc(&tab, (size_t)total * sizeof(double2))) || (e = hipMalloc(&econ, E.size() * sizeof(double))) ||
+        (e = hipMemcpy(econ, E.data(), E.size() * sizeof(double), hipMemcpyHostToDevice)))
+        return undo(e);
+    for (int a = 0; a < 3; ++a) {
+        const int N = p.n[a], cells = cells_of(p, a);
+        const int64_t rows = (int64_t)kTerms * cells;
+        std::vector<double> tay((size_t)kTerms * N);
+        for (int m = 0; m < N; ++m) {
+            double sp[kTerms];
+            sinc_taylor(kPi * (m < N / 2 ? m : m - N) / N, sp);
+            for (int t = 0; t < kTerms; ++t) tay[(size_t)t * N + m] = sp[t];
+        }
+        double2* X = s->work;
+        double2* W = X + rows * N;
+        double* dtay = reinterpret_cast<double*>(W + (int64_t)N * N);
+        // the scratch is the previous axis's until its products are done
+        if ((e = hipStreamSynchronize(stream)) ||
+            (e = hipMemcpy(dtay, tay.data(), tay.size() * sizeof(double), hipMemcpyHostToDevice)))
+            return undo(e);
+        hipLaunchKernelGGL(dft_matrix_kernel, dim3(blocks_of((int64_t)N * N)), dim3(256), 0, stream, N, W);
+        hipLaunchKernelGGL(expansion_kernel, dim3(blocks_of(rows * N)), dim3(256), 0, stream, dtay, N, p.surf_lo[a],
+                           cells, X);
+        if ((e = zgemm((int)rows, N, N, ZOp{X, N}, ZOp{W, N}, tab + s->near_off[a], N, 0, 0, 1, 1, {}, stream)))
+            return undo(e);
     }
-    return e;
+    s->near_tab = tab;
+    s->econ = econ;
+    return hipSuccess;
+}
+
+// The far tables of the three axes: per axis [K][N], the Chebyshev
+// coefficients of the centred factor with the transform folded in (D G W)
+hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3], hipStream_t stream) {
+    if (s->far_tab) return hipSuccess;
+    int64_t total = 0;
+    size_t work = 0;
+    for (int a = 0; a < 3; ++a) {
+        const int64_t N = p.n[a], K = s->K[a] = far_terms(far_axis(p, dxb, a).half);
+        s->far_off[a] = total;
+        total += K * N;
+        work = std::max(work, (size_t)(2 * K * N + K * K + N * N) * sizeof(double2));
+    }
+    TRY(ensure(&s->work, &s->work_bytes, work));
+    double2* tab = nullptr;
+    TRY(hipMalloc(&tab, (size_t)total * sizeof(double2)));
+    hipError_t e = hipSuccess;
+    for (int a = 0; a < 3 && !e; ++a) {
+        const int N = p.n[a], K = s->K[a];
+        double2* G = s->work;
+        double2* DG = G + (int64_t)K * N;
+        double2* D = DG + (int64_t)K * N;
+        double2* W = D + (int64_t)K * K;
+        hipLaunchKernelGGL(far_nodes_kernel, dim3(blocks_of((int64_t)K * N)), dim3(256), 0, stream, far_axis(p, dxb, a),
+                           K, G);
+        hipLaunchKernelGGL(far_dct_kernel, dim3(blocks_of((int64_t)K * K)), dim3(256), 0, stream, K, D);
+        hipLaunchKernelGGL(dft_matrix_kernel, dim3(blocks_of((int64_t)N * N)), dim3(256), 0, stream, N, W);
+        e = zgemm(K, N, K, ZOp{D, K}, ZOp{G, N}, DG, N, 0, 0, 1, 1, {}, stream);
+        if (!e) e = zgemm(K, N, N, ZOp{DG, N}, ZOp{W, N}, tab + s->far_off[a], N, 0, 0, 1, 1, {}, stream);
+    }
+    if (e) {
+        (void)hipStreamSynchronize(stream);
+        (void)hipFree(tab);
+        return e;
+    }
+    s->far_tab = tab;
+    return hipSuccess;
+}
+
+FaceGeo face_geo(const pstd_problem& p, const double dxb[3], int f) {
+    FaceGeo g;
+    const int a = f / 2, side = f % 2, b = face_axis_b(a), c = face_axis_c(a);
+    g.a = a;
+    g.b = b;
+    g.c = c;
+    g.lo_b = p.surf_lo[b];
+    g.lo_c = p.surf_lo[c];
+    g.L = cells_of(p, b);
+    g.M = cells_of(p, c);
+    g.db = dxb[b];
+    g.dc = dxb[c];
+    g.xa = ((side == 0 ? p.surf_lo[a] : p.surf_hi[a]) - p.n[a] / 2) * dxb[a];
+    g.xb0 = (p.surf_lo[b] - p.n[b] / 2 + 0.5) * dxb[b];
+    g.xc0 = (p.surf_lo[c] - p.n[c] / 2 + 0.5) * dxb[c];
+    g.pref = (side == 0 ? 1.0 : -1.0) * dxb[b] * dxb[c] / (4 * kPi * p.n[b] * p.n[c]);
+    return g;
+}
+
+// the largest coordinate of a point whose distances to the box stay within
+// fast_sincos's range
+double fast_limit(const pstd_problem& p, const double dxb[3]) {
+    double box = 0;
+    for (int a = 0; a < 3; ++a) box = std::max(box, dxb[a] * p.n[a]);
+    return kFastSincosLimit / 2 - box;
+}
+
+// flags of the observation points (see check_points_kernel), read back
+hipError_t check_points(ProjectState* s, const pstd_problem& p, const double dxb[3], const double3* obs, int64_t n_obs,
+                        unsigned* flags, hipStream_t stream) {
+    double lo[3], hi[3];
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = (p.surf_lo[a] - p.n[a] / 2) * dxb[a];
+        hi[a] = (p.surf_hi[a] - p.n[a] / 2) * dxb[a];
+    }
+    TRY(hipMemsetAsync(s->flags, 0, sizeof(unsigned), stream));
+    hipLaunchKernelGGL(check_points_kernel, dim3(blocks_of(n_obs)), dim3(256), 0, stream, obs, n_obs, p.k0,
+                       make_double3(lo[0], lo[1], lo[2]), make_double3(hi[0], hi[1], hi[2]), fast_limit(p, dxb), s->flags);
+    TRY(hipGetLastError());
+    TRY(hipMemcpyAsync(flags, s->flags, sizeof(unsigned), hipMemcpyDeviceToHost, stream));
+    return hipStreamSynchronize(stream);
 }
 
 }  // namespace
@@ -703,44 +1231,61 @@ hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb
                      hipStream_t stream, std::string* msg) {
     TRY(prepare(pst, p, acc, points, scale, stream));
     ProjectState* s = *pst;
-    TRY(hipMemsetAsync(out, 0, n_dir * sizeof(double2), stream));
-    const int64_t chunk = 8192;
-    {
-        // the largest scratch any face needs, allocated before the first
-        // launch that uses it
-        size_t need = 0;
-        for (int f = 0; f < 6; ++f) {
-            const int a = f / 2, Nb = p.n[face_axis_b(a)], Nc = p.n[face_axis_c(a)];
-            const size_t nd = (size_t)std::min(chunk, n_dir);
-            need = std::max(need, (nd * Nb + nd * Nc + (size_t)Nb * 2 * Nc + nd * 2 * Nc) * sizeof(double2));
-        }
-        TRY(ensure(&s->work, &s->work_bytes, need));
+    TRY(far_tables(s, p, dxb, stream));
+    // coefficients of every axis's two faces: C = B_c P B_b^T
+    const int64_t Ns = (int64_t)p.n[0] + p.n[1] + p.n[2];
+    int64_t coef_off[4] = {0}, ybytes = 0, cbytes = 0;
+    int Kbp[3], Kcp[3];
+    for (int a = 0; a < 3; ++a) {
+        const int b = face_axis_b(a), c = face_axis_c(a);
+        Kbp[a] = (s->K[b] + 3) / 4 * 4;
+        Kcp[a] = (s->K[c] + 15) / 16 * 16;
+        coef_off[a + 1] = coef_off[a] + (int64_t)Kbp[a] * Kcp[a] * 4;
+        ybytes = std::max(ybytes, (int64_t)4 * p.n[c] * s->K[b]);
+        cbytes = std::max(cbytes, (int64_t)4 * s->K[c] * s->K[b]);
+    }
+    const int64_t chunk = 1 << 20;  // directions of one launch: bounds the rows of part
+    const int64_t wide = (int64_t)kWideGroups * 2 * Ns;
+    TRY(ensure(&s->work, &s->work_bytes, (size_t)(coef_off[3] + ybytes + cbytes + wide) * sizeof(double2)));
+    double2* coef = s->work;
+    double2* Y = coef + coef_off[3];
+    double2* C = Y + ybytes;
+    double2* scratch = C + cbytes;
+    FarArgs args{};
+    FarWide fw{};
+    fw.planes = s->phasors;
+    double mid[3];
+    for (int a = 0; a < 3; ++a) {
+        const int b = face_axis_b(a), c = face_axis_c(a);
+        const int Nb = p.n[b], Nc = p.n[c], Kb = s->K[b], Kc = s->K[c];
+        const int64_t np = (int64_t)Nb * Nc;
+        // the four planes (low psi, low dpsi, high psi, high dpsi) lie side by side
+        TRY(zgemm(Nc, Kb, Nb, ZOp{s->phasors + s->face_off[2 * a], Nb, np}, ZOp{s->far_tab + s->far_off[b], Nb}, Y, Kb,
+                  (int64_t)Nc * Kb, 0, 4, 1, ZOpts{false, false, true, false}, stream));
+        TRY(zgemm(Kc, Kb, Nc, ZOp{s->far_tab + s->far_off[c], Nc}, ZOp{Y, Kb, (int64_t)Nc * Kb}, C, Kb,
+                  (int64_t)Kc * Kb, 0, 4, 1, {}, stream));
+        const int64_t n = (int64_t)Kbp[a] * Kcp[a] * 4;
+        hipLaunchKernelGGL(far_pack_kernel, dim3(blocks_of(n)), dim3(256), 0, stream, Kb, Kc, Kbp[a], Kcp[a], C,
+                           coef + coef_off[a]);
+        fw.ax[a] = far_axis(p, dxb, a);
+        fw.pref[a] = dxb[b] * dxb[c] / (4 * kPi * Nb * Nc) / p.k0;
+        args.ax[a] = FarEval{reinterpret_cast<const double*>(coef + coef_off[a]), Kbp[a], Kcp[a], fw.ax[a].half, fw.pref[a]};
+        mid[a] = fw.ax[a].mid;
     }
     for (int64_t d0 = 0; d0 < n_dir; d0 += chunk) {
         const int64_t nd = std::min(chunk, n_dir - d0);
-        for (int f = 0; f < 6; ++f) {
-            const int a = f / 2, side = f % 2, b = face_axis_b(a), c = face_axis_c(a);
-            const int Nb = p.n[b], Nc = p.n[c];
-            const int idx = side == 0 ? p.surf_lo[a] : p.surf_hi[a];
-            const double xa = (idx - p.n[a] / 2) * dxb[a];
-            const double pref = (side == 0 ? 1.0 : -1.0) * dxb[b] * dxb[c] / (4 * kPi * Nb * Nc) / p.k0;
-            // scratch: Gb [nd][Nb], Gc [nd][Nc], Mt [Nb][2Nc], T [nd][2Nc]
-            double2* Gb = s->work;
-            double2* Gc = Gb + nd * Nb;
-            double2* Mt = Gc + nd * Nc;
-            double2* T = Mt + (int64_t)Nb * 2 * Nc;
-            const double2* Fp = s->spectra + s->face_off[f];
-            const double2* Fd = Fp + (int64_t)Nb * Nc;
-            hipLaunchKernelGGL(farfield_factor_kernel, dim3((unsigned)((nd * Nb + 255) / 256)), dim3(256), 0, stream,
-                               dirs + d0, nd, b, Nb, dxb[b], p.surf_lo[b], p.surf_hi[b], Gb);
-            hipLaunchKernelGGL(farfield_factor_kernel, dim3((unsigned)((nd * Nc + 255) / 256)), dim3(256), 0, stream,
-                               dirs + d0, nd, c, Nc, dxb[c], p.surf_lo[c], p.surf_hi[c], Gc);
-            hipLaunchKernelGGL(stack_transpose_kernel, dim3((unsigned)(((int64_t)Nb * 2 * Nc + 255) / 256)), dim3(256),
-                               0, stream, Fp, Fd, Nb, Nc, Mt);
-            TRY(zgemm((int)nd, 2 * Nc, Nb, Gb, Nb, 0, Mt, 2 * Nc, 0, T, 2 * Nc, 0, 1, stream));
-            hipLaunchKernelGGL(farfield_dot_kernel, dim3((unsigned)((nd + kDotWaves - 1) / kDotWaves)),
-                               dim3(64 * kDotWaves), 0, stream, dirs + d0, nd, a, xa, pref, Gc, T, Nc, out + d0);
-        }
+        // j tiles split until there are two waves per SIMD
+        const int64_t waves = 3 * ((nd + 15) / 16);
+        const int tiles = std::min(std::min(Kcp[0], Kcp[1]), Kcp[2]) / 16;
+        args.jsplit = (int)std::max<int64_t>(1, std::min<int64_t>(tiles, (2048 + waves - 1) / waves));
+        const int rows = 3 * args.jsplit;
+        TRY(ensure(&s->part, &s->part_bytes, (size_t)rows * nd * sizeof(double2)));
+        hipLaunchKernelGGL(far_eval_kernel, dim3(blocks_of(nd, 16 * kFarWaves), rows), dim3(64 * kFarWaves), 0, stream,
+                           dirs + d0, nd, args, s->part);
+        hipLaunchKernelGGL(far_sum_kernel, dim3(blocks_of(nd)), dim3(256), 0, stream, dirs + d0, nd,
+                           make_double3(mid[0], mid[1], mid[2]), s->part, rows, out + d0);
+        hipLaunchKernelGGL(far_wide_kernel, dim3(std::min<unsigned>(kWideGroups, blocks_of(nd))), dim3(256), 0, stream,
+                           dirs + d0, nd, fw, scratch, out + d0);
     }
     return hipGetLastError();
 }
@@ -748,78 +1293,46 @@ hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb
 hipError_t project_points(ProjectState** pst, const pstd_problem& p, const double dxb[3], double2* const acc[3],
                           const int64_t points[3], PhasorScale scale, const double3* obs, int64_t n_obs, double2* out,
                           hipStream_t stream, std::string* msg) {
-    // the cell formula holds outside the box only
-    {
-        std::vector<double3> h(n_obs);
-        TRY(hipMemcpyAsync(h.data(), obs, n_obs * sizeof(double3), hipMemcpyDeviceToHost, stream));
-        TRY(hipStreamSynchronize(stream));
-        for (int64_t i = 0; i < n_obs; ++i) {
-            const double r[3] = {h[i].x * p.k0, h[i].y * p.k0, h[i].z * p.k0};
-            bool inside = true;
-            for (int a = 0; a < 3; ++a) {
-                const double lo = (p.surf_lo[a] - p.n[a] / 2) * dxb[a], hi = (p.surf_hi[a] - p.n[a] / 2) * dxb[a];
-                if (!(r[a] > lo && r[a] < hi)) inside = false;
-                if (!std::isfinite(r[a])) inside = true;
-            }
-            if (inside) {
-                *msg = "observation point inside the box or not finite";
-                return hipErrorInvalidValue;
-            }
-        }
-    }
     TRY(prepare(pst, p, acc, points, scale, stream));
     ProjectState* s = *pst;
-    TRY(near_tables(s, p, dxb, false));
-    TRY(hipMemsetAsync(out, 0, n_obs * sizeof(double2), stream));
+    // the cell formula holds outside the box only
+    unsigned flags = 0;
+    TRY(check_points(s, p, dxb, obs, n_obs, &flags, stream));
+    if (flags & 1) {
+        *msg = "observation point inside the box or not finite";
+        return hipErrorInvalidValue;
+    }
+    TRY(near_tables(s, p, stream));
     for (int f = 0; f < 6; ++f) {
-        const int a = f / 2, side = f % 2, b = face_axis_b(a), c = face_axis_c(a);
-        const int Nb = p.n[b], Nc = p.n[c];
-        const int L = p.surf_hi[b] - p.surf_lo[b], M = p.surf_hi[c] - p.surf_lo[c];
-        const int64_t ncell = (int64_t)L * M;
-        // expansion tables U_p^T[b'][l] (batched over p) and V_q[m][c'] (batched over q)
-        const double2* dUt = s->fwd_tab + s->fwd_off[f];
-        const double2* dV = dUt + (size_t)kTerms * Nb * L;
-        // scratch: W [p][Nc][L], Qg [p][q][M][L], Q [cell][2][p][q]
-        const size_t nW = (size_t)kTerms * Nc * L, nQg = (size_t)kTerms * kTerms * ncell,
-                     nQ = (size_t)2 * kTerms * kTerms * ncell;
+        const FaceGeo g = face_geo(p, dxb, f);
+        const int Nb = p.n[g.b], Nc = p.n[g.c], L = g.L, M = g.M;
+        const int64_t ncell = (int64_t)L * M, np = (int64_t)Nb * Nc;
+        const double2* Tb = s->near_tab + s->near_off[g.b];
+        const double2* Tc = s->near_tab + s->near_off[g.c];
+        // scratch: W [fld][p][Nc][L], Qg [fld][p][q][M][L], Q [cell][2][low terms]
+        const size_t nW = (size_t)2 * kTerms * Nc * L, nQg = (size_t)2 * kPairs * ncell, nQ = (size_t)2 * kLow * ncell;
         TRY(ensure(&s->work, &s->work_bytes, (nW + nQg + nQ) * sizeof(double2)));
         double2* dW = s->work;
         double2* dQg = dW + nW;
         double2* dQ = dQg + nQg;
-        for (int fld = 0; fld < 2; ++fld) {
-            const double2* F = s->spectra + s->face_off[f] + (int64_t)fld * Nb * Nc;
-            // W_p = F [Nc x Nb] * Ut_p [Nb x L]
-            TRY(zgemm(Nc, L, Nb, F, Nb, 0, dUt, L, (int64_t)Nb * L, dW, L, (int64_t)Nc * L, kTerms, stream));
-            // Q_pq = V_q [M x Nc] * W_p [Nc x L]
-            for (int pp = 0; pp < kTerms; ++pp)
-                TRY(zgemm(M, L, Nc, dV, Nc, (int64_t)M * Nc, dW + (size_t)pp * Nc * L, L, 0,
-                          dQg + (size_t)pp * kTerms * ncell, L, ncell, kTerms, stream));
-            const int64_t tot = ncell * kTerms * kTerms;
-            hipLaunchKernelGGL(reorder_q_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, stream, dQg, fld,
-                               ncell, dQ);
-        }
-        FaceGeo g;
-        g.a = a;
-        g.b = b;
-        g.c = c;
-        g.lo_b = p.surf_lo[b];
-        g.lo_c = p.surf_lo[c];
-        g.L = L;
-        g.M = M;
-        g.db = dxb[b];
-        g.dc = dxb[c];
-        g.xa = ((side == 0 ? p.surf_lo[a] : p.surf_hi[a]) - p.n[a] / 2) * dxb[a];
-        g.xb0 = (p.surf_lo[b] - Nb / 2 + 0.5) * dxb[b];
-        g.xc0 = (p.surf_lo[c] - Nc / 2 + 0.5) * dxb[c];
-        g.pref = (side == 0 ? 1.0 : -1.0) * dxb[b] * dxb[c] / (4 * kPi * Nb * Nc);
+        const int64_t sW = (int64_t)Nc * L;
+        // W_p = P [Nc x Nb] * Tb_p^T [Nb x L]
+        TRY(zgemm(Nc, L, Nb, ZOp{s->phasors + s->face_off[f], Nb, 0, np}, ZOp{Tb, Nb, (int64_t)L * Nb, 0}, dW, L, sW,
+                  kTerms * sW, kTerms, 2, ZOpts{false, false, true, false}, stream));
+        // Q_pq = Tc_q [M x Nc] * W_p [Nc x L]
+        TRY(zgemm(M, L, Nc, ZOp{Tc, Nc, (int64_t)M * Nc, 0}, ZOp{dW, L, 0, sW}, dQg, L, ncell, kTerms * ncell, kTerms,
+                  2 * kTerms, {}, stream));
+        hipLaunchKernelGGL(economise_kernel, dim3(blocks_of(ncell * kLow * 2)), dim3(256), 0, stream, dQg, ncell,
+                           s->econ, 0.5 * g.db, 0.5 * g.dc, dQ);
         const int64_t bx = (n_obs + kNearThreads * kNearPoints - 1) / (kNearThreads * kNearPoints);
         const int splits = split_count(bx * (kNearThreads / 64), (ncell + kCellChunk - 1) / kCellChunk);
         const int64_t per = (ncell + splits - 1) / splits;
         TRY(ensure(&s->part, &s->part_bytes, (size_t)splits * n_obs * sizeof(double2)));
-        hipLaunchKernelGGL(near_kernel<kNearPoints>, dim3((unsigned)bx, (unsigned)splits), dim3(kNearThreads), 0, stream,
-                           obs, n_obs, p.k0, g, dQ, per, s->part);
-        hipLaunchKernelGGL(add_splits_kernel, dim3((unsigned)((n_obs + 255) / 256)), dim3(256), 0, stream, s->part, splits,
-                           n_obs, true, out);
+        auto near = (flags & 2) ? near_kernel<kNearPoints, false> : near_kernel<kNearPoints, true>;
+        hipLaunchKernelGGL(near, dim3((unsigned)bx, (unsigned)splits), dim3(kNearThreads), 0, stream, obs, n_obs, p.k0,
+                           g, dQ, per, s->part);
+        hipLaunchKernelGGL(add_splits_kernel, dim3(blocks_of(n_obs)), dim3(256), 0, stream, s->part, splits, n_obs,
+                           f > 0, out);
         // the next face reuses the scratch after these kernels, in stream order
     }
     return hipGetLastError();
@@ -828,67 +1341,52 @@ hipError_t project_points(ProjectState** pst, const pstd_problem& p, const doubl
 hipError_t project_adjoint(ProjectState** pst, const pstd_problem& p, const double dxb[3], double2* const acc[3],
                            const int64_t points[3], double scale, const double3* obs, int64_t n_obs, const double2* g,
                            float2* inj, hipStream_t stream, std::string* msg) {
-    // the state (twiddles, offsets) is shared with the forward projection
+    // the state (tables, offsets) is shared with the forward projection
     TRY(prepare(pst, p, acc, points, real_scale(1.0), stream));
     ProjectState* s = *pst;
-    TRY(near_tables(s, p, dxb, true));
-    const double2* twc[3] = {s->twc, s->twc + p.n[0], s->twc + p.n[0] + p.n[1]};
+    unsigned flags = 0;
+    TRY(check_points(s, p, dxb, obs, n_obs, &flags, stream));
+    TRY(near_tables(s, p, stream));
     for (int f = 0; f < 6; ++f) {
-        const int a = f / 2, side = f % 2, b = face_axis_b(a), c = face_axis_c(a);
-        const int Nb = p.n[b], Nc = p.n[c];
-        const int L = p.surf_hi[b] - p.surf_lo[b], M = p.surf_hi[c] - p.surf_lo[c];
-        const int64_t ncell = (int64_t)L * M, np_ = (int64_t)Nb * Nc;
-        // conjugated expansion tables: Vh[c'][q M + m] = conj V_q[m][c'], Uc[p L + l][b'] = conj U_p[l][b']
-        const double2* dVh = s->adj_tab + s->adj_off[f];
-        const double2* dUc = dVh + (size_t)Nc * kTerms * M;
-        const size_t nQ = (size_t)2 * kTerms * kTerms * ncell, nW = (size_t)Nc * kTerms * L, nF = (size_t)np_;
-        TRY(ensure(&s->work, &s->work_bytes, (nQ + nW + 2 * nF) * sizeof(double2)));
-        double2* dQ = s->work;
+        const FaceGeo geo = face_geo(p, dxb, f);
+        const int Nb = p.n[geo.b], Nc = p.n[geo.c], L = geo.L, M = geo.M;
+        const int64_t ncell = (int64_t)L * M, np = (int64_t)Nb * Nc;
+        const double2* Tb = s->near_tab + s->near_off[geo.b];
+        const double2* Tc = s->near_tab + s->near_off[geo.c];
+        // scratch: low [fld][k][cell], Qbar [fld][p][q][cell], W [fld][Nc][9 L], F [fld][p][plane]
+        const size_t nl = (size_t)2 * kLow * ncell, nQ = (size_t)2 * kPairs * ncell, nW = (size_t)2 * Nc * kTerms * L,
+                     nF = (size_t)2 * kTerms * np;
+        TRY(ensure(&s->work, &s->work_bytes, (nl + nQ + nW + nF) * sizeof(double2)));
+        double2* dl = s->work;
+        double2* dQ = dl + nl;
         double2* dW = dQ + nQ;
         double2* dF = dW + nW;
-        double2* dT = dF + nF;
-        FaceGeo geo;
-        geo.a = a;
-        geo.b = b;
-        geo.c = c;
-        geo.lo_b = p.surf_lo[b];
-        geo.lo_c = p.surf_lo[c];
-        geo.L = L;
-        geo.M = M;
-        geo.db = dxb[b];
-        geo.dc = dxb[c];
-        geo.xa = ((side == 0 ? p.surf_lo[a] : p.surf_hi[a]) - p.n[a] / 2) * dxb[a];
-        geo.xb0 = (p.surf_lo[b] - Nb / 2 + 0.5) * dxb[b];
-        geo.xc0 = (p.surf_lo[c] - Nc / 2 + 0.5) * dxb[c];
-        geo.pref = (side == 0 ? 1.0 : -1.0) * dxb[b] * dxb[c] / (4 * kPi * Nb * Nc);
-        const int64_t nthr = ncell * ((kTerms + kAdjP - 1) / kAdjP);
-        const int64_t bx = (nthr + 127) / 128;
-        const int splits = split_count(bx * 2, std::min<int64_t>((n_obs + kAdjObsChunk - 1) / kAdjObsChunk, 16));
+        const int64_t bx = (ncell + 127) / 128;
+        const int splits = split_count(bx * 2 * kAdjGroups,
+                                       std::min<int64_t>((n_obs + kAdjObsChunk - 1) / kAdjObsChunk, 16));
         const int64_t per = (n_obs + splits - 1) / splits;
-        const int64_t nq = 2 * kTerms * kTerms * ncell;
-        double2* qdst = dQ;
+        double2* ldst = dl;
         if (splits > 1) {
-            TRY(ensure(&s->part, &s->part_bytes, (size_t)splits * nq * sizeof(double2)));
-            qdst = s->part;
+            TRY(ensure(&s->low, &s->low_bytes, (size_t)splits * nl * sizeof(double2)));
+            ldst = s->low;
         }
-        hipLaunchKernelGGL(near_adjoint_kernel<kAdjP>, dim3((unsigned)bx, (unsigned)splits), dim3(128), 0, stream, obs, g,
-                           n_obs, p.k0, geo, per, qdst);
+        auto near = (flags & 2) ? near_adjoint_kernel<false> : near_adjoint_kernel<true>;
+        hipLaunchKernelGGL(near, dim3((unsigned)bx, (unsigned)splits, kAdjGroups), dim3(128), 0, stream, obs, g, n_obs,
+                           p.k0, geo, per, ldst);
         if (splits > 1)
-            hipLaunchKernelGGL(add_splits_kernel, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, stream, s->part,
-                               splits, nq, false, dQ);
-        for (int fld = 0; fld < 2; ++fld) {
-            // Wbar[c'][p L + l] = sum_q Vh_q [Nc x M] Qbar[fld][p][q] [M x L]
-            TRY(zgemm(Nc, L, kTerms * M, dVh, (int64_t)kTerms * M, 0, dQ + (size_t)fld * kTerms * kTerms * ncell, L,
-                      (int64_t)kTerms * ncell, dW, (int64_t)kTerms * L, L, kTerms, stream));
-            // Fbar = Wbar [Nc x 9L] * Uc [9L x Nb]
-            TRY(zgemm(Nc, Nb, kTerms * L, dW, (int64_t)kTerms * L, 0, dUc, Nb, 0, dF, Nb, 0, 1, stream));
-            // plane adjoint of the forward 2D DFT: the unnormalised conjugate DFT
-            const unsigned blocks = (unsigned)((np_ + 255) / 256);
-            hipLaunchKernelGGL(dft_rows_kernel, dim3(blocks), dim3(256), 0, stream, dF, dT, Nb, Nc, twc[b]);
-            hipLaunchKernelGGL(dft_cols_kernel, dim3(blocks), dim3(256), 0, stream, dT, dF, Nb, Nc, twc[c]);
-            hipLaunchKernelGGL(conj_scale_kernel, dim3(blocks), dim3(256), 0, stream, dF, np_, scale,
-                               inj + s->face_off[f] + fld * np_);
-        }
+            hipLaunchKernelGGL(add_splits_kernel, dim3(blocks_of((int64_t)nl)), dim3(256), 0, stream, s->low, splits,
+                               (int64_t)nl, false, dl);
+        hipLaunchKernelGGL(economise_adjoint_kernel, dim3(blocks_of((int64_t)nQ)), dim3(256), 0, stream, dl, ncell,
+                           s->econ, 0.5 * geo.db, 0.5 * geo.dc, dQ);
+        // Wbar[fld][c'][p L + l] = sum_qm conj(Tc[q M + m][c']) Qbar[fld][p][q M + m][l]
+        TRY(zgemm(Nc, L, kTerms * M, ZOp{Tc, Nc}, ZOp{dQ, L, kTerms * ncell, kPairs * ncell}, dW, (int64_t)kTerms * L, L,
+                  (int64_t)Nc * kTerms * L, kTerms, 2, ZOpts{true, true, false, false}, stream));
+        // plane adjoint, one plane per p: Wbar_p [Nc x L] * conj(Tb_p) [L x Nb]
+        TRY(zgemm(Nc, Nb, L, ZOp{dW, (int64_t)kTerms * L, L, (int64_t)Nc * kTerms * L}, ZOp{Tb, Nb, (int64_t)L * Nb, 0},
+                  dF, Nb, np, kTerms * np, kTerms, 2, ZOpts{false, false, false, true}, stream));
+        for (int fld = 0; fld < 2; ++fld)
+            hipLaunchKernelGGL(conj_scale_kernel, dim3(blocks_of(np)), dim3(256), 0, stream, dF + fld * kTerms * np, np,
+                               scale, inj + s->face_off[f] + fld * np);
         // the next face reuses the scratch after these kernels, in stream order
     }
     return hipGetLastError();
@@ -896,14 +1394,8 @@ hipError_t project_adjoint(ProjectState** pst, const pstd_problem& p, const doub
 
 void project_free(ProjectState* s) {
     if (!s) return;
-    (void)hipFree(s->phasors);
-    (void)hipFree(s->spectra);
-    (void)hipFree(s->work);
-    (void)hipFree(s->part);
-    (void)hipFree(s->fwd_tab);
-    (void)hipFree(s->adj_tab);
-    (void)hipFree(s->tw);
-    (void)hipFree(s->twc);
+    void* ptrs[] = {s->phasors, s->work, s->part, s->low, s->flags, s->near_tab, s->econ, s->far_tab};
+    for (void* q : ptrs) (void)hipFree(q);
     delete s;
 }
 

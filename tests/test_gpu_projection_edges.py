@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import synth
+from oracle import ntdf as ontdf
 from oracle import pstd as opstd
 from oracle import sphere as osph
 
@@ -50,3 +51,74 @@ def test_node_phasors_of_a_given_field(P, nodes):
     v, d = (x.cpu().numpy() for x in s.sphere_phasors())
     assert np.abs(v - rv).max() <= 1e-12 * np.abs(rv).max()
     assert np.abs(d - rd).max() <= 1e-12 * np.abs(rd).max()
+
+
+def box_case(P, n, steps=200):
+    prob, V = synth.tiny(n=n, P=3, transition=2, v0=0.5, radius_cells=3, steps=steps, theta=0.4, phi=1.0)
+    prob = prob.replace(ramp_periods=0.5, dft_begin=steps // 2, dft_end=steps)
+    s = P.Solver(prob)
+    s.set_potential(V)
+    s.run(steps)
+    return prob, s, ontdf.Box(prob.n, opstd.dxbar(prob), prob.surf_lo, prob.surf_hi)
+
+
+def directions(count, seed=0):
+    d = np.random.default_rng(seed).normal(size=(count, 3))
+    return d / np.linalg.norm(d, axis=1, keepdims=True)
+
+
+@pytest.mark.parametrize("n", [(24, 20, 32), (40, 24, 20), (64, 48, 24)])
+@pytest.mark.parametrize("count", [1, 15, 17, 64, 65, 300])
+def test_box_far_field_counts(P, n, count):
+    """Direction counts that leave waves and their lanes idle, the poles and
+    the axes among them, on boxes with odd and even numbers of Chebyshev terms.
+    Series cut at 2^-57 and a few hundred FP64 additions: 1e-12 of the largest."""
+    prob, s, box = box_case(P, n)
+    phi, dphi = s.split_phasors(s.phasors().cpu().numpy())
+    d = directions(count)
+    special = np.array([[0, 0, 1.0], [0, 0, -1.0], [1.0, 0, 0], [0, -1.0, 0]])
+    d[:min(4, count)] = special[:count]
+    got = s.far_field(d).cpu().numpy()
+    ref = ontdf.far_field(box, phi, dphi, d) / prob.k0
+    big = ontdf.far_field(box, phi, dphi, directions(20, 1)) / prob.k0
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(big).max()
+
+
+def test_box_far_field_of_vectors_beyond_unit_length(P):
+    """The formula holds for any vector; components beyond 1 lie outside the
+    series' interval and take the direct sums (one among many unit vectors, in
+    a second group of 256)."""
+    prob, s, box = box_case(P, (24, 20, 32))
+    phi, dphi = s.split_phasors(s.phasors().cpu().numpy())
+    d = directions(600)
+    d[3] *= 2.5
+    d[400] = (0.0, 1.5, -0.3)
+    d[599] = (0.2, -0.3, 1.0000001)
+    got = s.far_field(d).cpu().numpy()
+    ref = ontdf.far_field(box, phi, dphi, d) / prob.k0
+    assert np.all(np.abs(got - ref) <= 1e-11 * np.maximum(np.abs(ref), np.abs(ref).max() * 1e-3))
+    assert torch.isnan(torch.view_as_real(s.far_field(np.array([[np.nan, 0.0, 0.0]])))).all()
+
+
+@pytest.mark.parametrize("n", [(24, 20, 32), (40, 24, 20)])
+@pytest.mark.parametrize("count", [1, 255, 257, 513])
+def test_box_points_counts(P, n, count):
+    """Point counts around the workgroup's 2 x 256, close points (the largest
+    cell angles) among them, against the 8th-order series of the oracle; the economised terms differ from it by
+    under 1/50 of the degree-9 terms, a^9 / 10! with a <= pi/8: 1e-11 of the largest."""
+    prob, s, box = box_case(P, n)
+    phi, dphi = s.split_phasors(s.phasors().cpu().numpy())
+    h = prob.h[0]
+    half = [(prob.surf_hi[a] - prob.surf_lo[a]) * h / 2 for a in range(3)]
+    pts = directions(count, 2) * np.random.default_rng(3).uniform(1.8, 6.0, size=(count, 1)) * max(half)
+    if count > 2:
+        pts[0] = (half[0] + 0.05, 0.02, -0.03)
+        pts[1] = (0.1, -(half[1] + 0.3), 0.0)
+    tab = ontdf.TaylorTables(box, phi, dphi)
+    ref = tab.project(pts * prob.k0)
+    got = s.project(pts).cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-11 * np.abs(ref).max()
+    # a point beyond the short sincos's range sends all through the general one
+    far = np.vstack([pts[:3], [[3e9, -1e9, 2e9]]])
+    got = s.project(far).cpu().numpy()
+    assert np.abs(got[:-1] - s.project(pts[:3]).cpu().numpy()).max() <= 1e-13 * np.abs(ref).max()
