@@ -1357,13 +1357,9 @@ pstd_status pstd_project_k(pstd_solver* s, int32_t ik, const double* obs_dev, in
         SphereOut o;
         if (pstd_status st = pulse_output(s, ik, &o)) return st;
         // the Kirchhoff integral holds outside the sphere only
-        std::vector<double> h(3 * n_obs);
-        HIP_TRY(s, hipMemcpyAsync(h.data(), obs_dev, h.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
-        HIP_TRY(s, hipStreamSynchronize(s->stream));
-        for (int64_t o = 0; o < n_obs; ++o) {
-            const double r = std::sqrt(h[3 * o] * h[3 * o] + h[3 * o + 1] * h[3 * o + 1] + h[3 * o + 2] * h[3 * o + 2]);
-            if (!(r > s->prob.sphere_radius)) return fail(s, PSTD_EINVAL, "observation point inside the sphere or not finite");
-        }
+        bool outside = false;
+        HIP_TRY(s, sphere_outside(s, (const double3*)obs_dev, n_obs, &outside, s->stream));
+        if (!outside) return fail(s, PSTD_EINVAL, "observation point inside the sphere or not finite");
         hipError_t e = sphere_project(s, o, (const double3*)obs_dev, n_obs, (double2*)out_dev, s->stream);
         if (e) return hip_fail(s, e, "sphere projection");
         return PSTD_OK;

@@ -112,6 +112,8 @@ struct SphereOut {
 };
 // node phasors (psi, d_n psi; scattered part, normalised)
 hipError_t sphere_phasors(pstd_solver* s, const SphereOut& o, double2* out, hipStream_t stream);
+// whether every point lies outside the sphere (and is finite); synchronises
+hipError_t sphere_outside(pstd_solver* s, const double3* obs, int64_t n_obs, bool* outside, hipStream_t stream);
 hipError_t sphere_project(pstd_solver* s, const SphereOut& o, const double3* obs, int64_t n_obs, double2* out,
                           hipStream_t stream);
 hipError_t sphere_far_field(pstd_solver* s, const SphereOut& o, const double3* dirs, int64_t n_dir, double2* out,

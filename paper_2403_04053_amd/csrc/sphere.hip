@@ -14,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "fp64_math.hpp"
 #include "solver.hpp"
 
 namespace pstd {
@@ -39,6 +40,10 @@ struct SphereState {
                                   // interpolation adds it, the saved state carries it)
     float2* stage = nullptr;      // [kStageSteps][slot]: psi of the steps of a launch group (pulsed runs)
     double2* phasor = nullptr;    // [2][node]: psi, d_n psi
+    double2* pack = nullptr;      // [node][4]: (x, y), (z, 0), w psi, w d_n psi, what the sums read
+    double2* part = nullptr;      // [split][output]: partial sums of the nodes
+    size_t part_bytes = 0;
+    unsigned* flags = nullptr;    // check_outside_kernel's result
 };
 
 namespace {
@@ -194,7 +199,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 __global__ __launch_bounds__(64 * kNodeWaves) void node_kernel(
     int n_nodes, const int* __restrict__ start, const double* __restrict__ lw, const double3* __restrict__ normal,
     const int* __restrict__ slot, int nx, int ny, const double2* __restrict__ sum, const double2* __restrict__ comp,
-    const double2* __restrict__ inc, double2 scale, double2* __restrict__ out) {
+    const double2* __restrict__ inc, double2 scale, const double3* __restrict__ node, const double* __restrict__ weight,
+    double2* __restrict__ out, double2* __restrict__ pack) {
     static_assert(kStencil == 8, "a wave is an 8 x 8 stencil plane");
     const int lane = threadIdx.x & 63;
     const int q = blockIdx.x * kNodeWaves + (threadIdx.x >> 6);
@@ -227,99 +233,166 @@ __global__ __launch_bounds__(64 * kNodeWaves) void node_kernel(
     if (lane == 0) {
         out[q] = make_double2(orr, oi);
         out[n_nodes + q] = make_double2(gr, gi);
+        const double3 x = node[q];
+        const double w = weight[q];
+        double2* p = pack + (int64_t)q * 4;
+        p[0] = make_double2(x.x, x.y);
+        p[1] = make_double2(x.z, 0.0);
+        p[2] = make_double2(w * orr, w * oi);
+        p[3] = make_double2(w * gr, w * gi);
     }
 }
 
+// The node sums.  The sphere's normal is s / R_s, so a node is its position and
+// its two weighted phasors: four 16-byte LDS reads serve K outputs per thread.
+// blockIdx.y takes a range of nodes (part of the sum goes to row y of part), so
+// that few outputs still fill the chip.  Bound by the FP64 vector rate: about
+// 66 (points) and 45 (directions) instructions per output and node, 150 and
+// 110 with the library's square root, division and sincos and one output per
+// thread.  8192 nodes: 65160 directions 2.49 -> 0.89 ms, 65536 points 3.43 -> 1.37,
+// 16384 points 3.25 -> 0.40; 64 outputs, one workgroup's chain before, 2.40 ->
+// 0.07 and 3.15 -> 0.10 ms.
 constexpr int kNodeChunk = 256;
+constexpr int kSumThreads = 256;
 
-// Psi(r) = -(1/4pi) sum_q w_q exp(ikR)/R [dn psi + (-ik + 1/R)(n . (s - r)/R) psi],
-// k the reduced wavenumber of the phasors (1 for the central wave)
-__global__ __launch_bounds__(256) void sphere_points_kernel(int n_nodes, const double3* __restrict__ node,
-                                                            const double3* __restrict__ normal,
-                                                            const double* __restrict__ weight,
-                                                            const double2* __restrict__ ph, const double3* __restrict__ obs,
-                                                            int64_t n_obs, double k0, double kw,
-                                                            double2* __restrict__ out) {
-    __shared__ double3 s_node[kNodeChunk], s_nrm[kNodeChunk];
-    __shared__ double s_w[kNodeChunk];
-    __shared__ double2 s_v[kNodeChunk], s_d[kNodeChunk];
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = o < n_obs;
-    double3 r = make_double3(0, 0, 0);
-    if (live) {
-        const double3 p = obs[o];
-        r = make_double3(p.x * k0, p.y * k0, p.z * k0);
-    }
-    double ar = 0, ai = 0;
-    for (int q0 = 0; q0 < n_nodes; q0 += kNodeChunk) {
-        const int nq = min(kNodeChunk, n_nodes - q0);
-        __syncthreads();
-        for (int e = threadIdx.x; e < nq; e += blockDim.x) {
-            s_node[e] = node[q0 + e];
-            s_nrm[e] = normal[q0 + e];
-            s_w[e] = weight[q0 + e];
-            s_v[e] = ph[q0 + e];
-            s_d[e] = ph[n_nodes + q0 + e];
-        }
-        __syncthreads();
-        if (!live) continue;
-        for (int e = 0; e < nq; ++e) {
-            const double dx = s_node[e].x - r.x, dy = s_node[e].y - r.y, dz = s_node[e].z - r.z;
-            const double R = sqrt(dx * dx + dy * dy + dz * dz);
-            const double inv = 1.0 / R;
-            const double ndr = (s_nrm[e].x * dx + s_nrm[e].y * dy + s_nrm[e].z * dz) * inv;
-            // dn psi + (-ik + 1/R) ndr psi
-            const double2 v = s_v[e], d = s_d[e];
-            const double tr = d.x + ndr * (kw * v.y + inv * v.x);
-            const double ti = d.y + ndr * (-kw * v.x + inv * v.y);
-            double sn, cs;
-            sincos(kw * R, &sn, &cs);
-            const double f = s_w[e] * inv;
-            ar += f * (cs * tr - sn * ti);
-            ai += f * (cs * ti + sn * tr);
-        }
-    }
-    if (live) out[o] = make_double2(-ar / (4 * kPi), -ai / (4 * kPi));
+template <bool FAST>
+__device__ __forceinline__ void node_phase(double x, double* sn, double* cs) {
+    if constexpr (FAST) fast_sincos(x, sn, cs);
+    else sincos(x, sn, cs);
 }
 
-// f(r_hat) = -(1/4pi) sum_q w_q [dn psi + ik (n . r_hat) psi] exp(-ik r_hat . s) / k0
-__global__ __launch_bounds__(256) void sphere_far_kernel(int n_nodes, const double3* __restrict__ node,
-                                                         const double3* __restrict__ normal,
-                                                         const double* __restrict__ weight,
-                                                         const double2* __restrict__ ph, const double3* __restrict__ dirs,
-                                                         int64_t n_dir, double k0, double kw,
-                                                         double2* __restrict__ out) {
-    __shared__ double3 s_node[kNodeChunk], s_nrm[kNodeChunk];
-    __shared__ double s_w[kNodeChunk];
-    __shared__ double2 s_v[kNodeChunk], s_d[kNodeChunk];
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = o < n_dir;
-    double3 rh = make_double3(0, 0, 1);
-    if (live) rh = dirs[o];
-    double ar = 0, ai = 0;
-    for (int q0 = 0; q0 < n_nodes; q0 += kNodeChunk) {
-        const int nq = min(kNodeChunk, n_nodes - q0);
+// FAR: f(r_hat) = -(1/4pi) sum_q w_q [dn psi + ik (n . r_hat) psi] exp(-ik r_hat . s_q) / k0;
+// else Psi(r) = -(1/4pi) sum_q w_q exp(ikR)/R [dn psi + (-ik + 1/R)(n . (s - r)/R) psi],
+// k the reduced wavenumber of the phasors (1 for the central wave); r: the
+// thread's direction or reduced point
+template <bool FAR, bool FAST, int K>
+__device__ __forceinline__ void node_sums(const double2* __restrict__ pack, int q_lo, int q_hi, double inv_rs, double kw,
+                                          const double3 (&r)[K], double2* lds, double2 (&acc)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[k] = make_double2(0, 0);
+    for (int q0 = q_lo; q0 < q_hi; q0 += kNodeChunk) {
+        const int nq = min(kNodeChunk, q_hi - q0);
         __syncthreads();
-        for (int e = threadIdx.x; e < nq; e += blockDim.x) {
-            s_node[e] = node[q0 + e];
-            s_nrm[e] = normal[q0 + e];
-            s_w[e] = weight[q0 + e];
-            s_v[e] = ph[q0 + e];
-            s_d[e] = ph[n_nodes + q0 + e];
-        }
+        for (int e = threadIdx.x; e < nq * 4; e += kSumThreads) lds[e] = pack[(int64_t)q0 * 4 + e];
         __syncthreads();
-        if (!live) continue;
+#pragma unroll 2
         for (int e = 0; e < nq; ++e) {
-            const double nr = s_nrm[e].x * rh.x + s_nrm[e].y * rh.y + s_nrm[e].z * rh.z;
-            const double2 v = s_v[e], d = s_d[e];
-            const double tr = d.x - kw * nr * v.y, ti = d.y + kw * nr * v.x;  // dn psi + ik nr psi
-            double sn, cs;
-            sincos(-kw * (rh.x * s_node[e].x + rh.y * s_node[e].y + rh.z * s_node[e].z), &sn, &cs);
-            ar += s_w[e] * (cs * tr - sn * ti);
-            ai += s_w[e] * (cs * ti + sn * tr);
+            const double2 sxy = lds[4 * e], sz = lds[4 * e + 1], v = lds[4 * e + 2], d = lds[4 * e + 3];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                double sn, cs;
+                if constexpr (FAR) {
+                    const double p = kw * fma(r[k].x, sxy.x, fma(r[k].y, sxy.y, r[k].z * sz.x));
+                    const double nr = p * inv_rs;   // k n . r_hat
+                    const double tr = fma(-nr, v.y, d.x), ti = fma(nr, v.x, d.y);
+                    node_phase<FAST>(p, &sn, &cs);
+                    // exp(-ip) (tr + i ti)
+                    acc[k].x = fma(cs, tr, fma(sn, ti, acc[k].x));
+                    acc[k].y = fma(cs, ti, fma(-sn, tr, acc[k].y));
+                } else {
+                    const double dx = sxy.x - r[k].x, dy = sxy.y - r[k].y, dz = sz.x - r[k].z;
+                    double R, inv;
+                    sqrt_rsqrt(fma(dx, dx, fma(dy, dy, dz * dz)), &R, &inv);
+                    const double ndr = fma(sxy.x, dx, fma(sxy.y, dy, sz.x * dz)) * (inv_rs * inv);
+                    const double tr = fma(ndr, fma(kw, v.y, inv * v.x), d.x);
+                    const double ti = fma(ndr, fma(-kw, v.x, inv * v.y), d.y);
+                    node_phase<FAST>(kw * R, &sn, &cs);
+                    acc[k].x = fma(inv, fma(cs, tr, -(sn * ti)), acc[k].x);
+                    acc[k].y = fma(inv, fma(cs, ti, sn * tr), acc[k].y);
+                }
+            }
         }
     }
-    if (live) out[o] = make_double2(-ar / (4 * kPi * k0), -ai / (4 * kPi * k0));
+}
+
+template <bool FAR, int K>
+__global__ __launch_bounds__(kSumThreads) void sphere_sum_kernel(const double2* __restrict__ pack, int n_nodes,
+                                                                 int per_split, double rs, double kw,
+                                                                 const double3* __restrict__ where, int64_t n, double k0,
+                                                                 double2* __restrict__ part) {
+    __shared__ double2 lds[kNodeChunk * 4];
+    double3 r[K];
+    bool far_off = false;  // a phase beyond fast_sincos's range is possible
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t o = ((int64_t)blockIdx.x * K + k) * kSumThreads + threadIdx.x;
+        // an idle slot takes a place off the sphere (its sums are dropped)
+        r[k] = FAR ? make_double3(0, 0, 1) : make_double3(0, 0, 2 * rs);
+        if (o < n) {
+            const double3 p = where[o];
+            r[k] = FAR ? p : make_double3(p.x * k0, p.y * k0, p.z * k0);
+        }
+        const double big = fabs(r[k].x) + fabs(r[k].y) + fabs(r[k].z);
+        far_off |= !(kw * (FAR ? big * rs : big + 2 * rs) <= kFastSincosLimit);
+    }
+    const int q_lo = (int)blockIdx.y * per_split, q_hi = min(n_nodes, q_lo + per_split);
+    double2 acc[K];
+    // one choice per workgroup: the sums' barriers are inside
+    if (__syncthreads_or(far_off)) node_sums<FAR, false, K>(pack, q_lo, q_hi, 1.0 / rs, kw, r, lds, acc);
+    else node_sums<FAR, true, K>(pack, q_lo, q_hi, 1.0 / rs, kw, r, lds, acc);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t o = ((int64_t)blockIdx.x * K + k) * kSumThreads + threadIdx.x;
+        if (o < n) part[(int64_t)blockIdx.y * n + o] = acc[k];
+    }
+}
+
+// out = scale times the rows of part, added in order
+__global__ void sphere_add_kernel(const double2* __restrict__ part, int rows, int64_t n, double scale,
+                                  double2* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    double2 s = part[i];
+    for (int k = 1; k < rows; ++k) {
+        const double2 x = part[(int64_t)k * n + i];
+        s.x += x.x;
+        s.y += x.y;
+    }
+    out[i] = make_double2(scale * s.x, scale * s.y);
+}
+
+// flag: a point not outside the sphere of physical radius `radius`
+__global__ void check_outside_kernel(const double3* __restrict__ obs, int64_t n, double radius,
+                                     unsigned* __restrict__ flag) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const double3 p = obs[i];
+    if (!(sqrt(p.x * p.x + p.y * p.y + p.z * p.z) > radius)) atomicOr(flag, 1u);
+}
+
+// the sums of n outputs over all nodes
+template <bool FAR>
+hipError_t sphere_sums(pstd_solver* s, double kw, const double3* where, int64_t n, double scale, double2* out,
+                       hipStream_t stream) {
+    SphereState* sp = s->sphere;
+    // two outputs per thread where they fill the chip by themselves; nodes
+    // split until there are about eight waves per SIMD
+    const int K = n >= 2 * kSumThreads ? 2 : 1;
+    const int64_t bx = (n + K * kSumThreads - 1) / (K * kSumThreads);
+    const int chunks = (sp->n_nodes + kNodeChunk - 1) / kNodeChunk;
+    const int64_t want = (2048 + bx - 1) / bx;
+    const int per = (int)((chunks + std::min<int64_t>(chunks, want) - 1) / std::min<int64_t>(chunks, want)) * kNodeChunk;
+    const int rows = (sp->n_nodes + per - 1) / per;
+    const size_t need = (size_t)rows * n * sizeof(double2);
+    if (sp->part_bytes < need) {
+        (void)hipStreamSynchronize(stream);  // queued sums may still use the old buffer
+        (void)hipFree(sp->part);
+        sp->part = nullptr;
+        sp->part_bytes = 0;
+        const hipError_t e = hipMalloc(&sp->part, need);
+        if (e) return e;
+        sp->part_bytes = need;
+    }
+    const dim3 grid((unsigned)bx, (unsigned)rows);
+    if (K == 2)
+        hipLaunchKernelGGL((sphere_sum_kernel<FAR, 2>), grid, dim3(kSumThreads), 0, stream, sp->pack, sp->n_nodes, per,
+                           sp->R, kw, where, n, s->prob.k0, sp->part);
+    else
+        hipLaunchKernelGGL((sphere_sum_kernel<FAR, 1>), grid, dim3(kSumThreads), 0, stream, sp->pack, sp->n_nodes, per,
+                           sp->R, kw, where, n, s->prob.k0, sp->part);
+    hipLaunchKernelGGL(sphere_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, sp->part, rows, n,
+                       scale, out);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -327,7 +400,8 @@ __global__ __launch_bounds__(256) void sphere_far_kernel(int n_nodes, const doub
 void sphere_free(SphereState* sp) {
     if (!sp) return;
     void* ptrs[] = {sp->node, sp->normal, sp->weight, sp->start, sp->lw,   sp->list,
-                    sp->slot, sp->inc,    sp->sum,    sp->comp,  sp->phasor, sp->stage};
+                    sp->slot, sp->inc,    sp->sum,    sp->comp,  sp->phasor, sp->stage,
+                    sp->pack, sp->part,   sp->flags};
     for (void* p : ptrs) (void)hipFree(p);
     delete sp;
 }
@@ -424,6 +498,8 @@ pstd_status sphere_create(pstd_solver* s) {
         (e = hipMalloc(&sp->sum, sp->n_shell * sizeof(double2))) ||
         (e = hipMalloc(&sp->comp, sp->n_shell * sizeof(double2))) ||
         (e = hipMalloc(&sp->phasor, 2 * (size_t)n_nodes * sizeof(double2))) ||
+        (e = hipMalloc(&sp->pack, 4 * (size_t)n_nodes * sizeof(double2))) ||
+        (e = hipMalloc(&sp->flags, sizeof(unsigned))) ||
         (e = hipMemset(sp->sum, 0, sp->n_shell * sizeof(double2))) ||
         (e = hipMemset(sp->comp, 0, sp->n_shell * sizeof(double2))))
         return solver_hip_fail(s, e, "sphere tables");
@@ -533,11 +609,26 @@ hipError_t sphere_phasors(pstd_solver* s, const SphereOut& o, double2* out, hipS
     hipLaunchKernelGGL(node_kernel, dim3((unsigned)((sp->n_nodes + kNodeWaves - 1) / kNodeWaves)),
                        dim3(64 * kNodeWaves), 0, stream, sp->n_nodes,
                        sp->start, sp->lw, sp->normal, sp->slot, s->prob.n[0], s->prob.n[1], sp->sum + off,
-                       sp->comp + off, sp->inc, o.scale, sp->phasor);
+                       sp->comp + off, sp->inc, o.scale, sp->node, sp->weight, sp->phasor, sp->pack);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && out)
         e = hipMemcpyAsync(out, sp->phasor, 2 * (size_t)sp->n_nodes * sizeof(double2), hipMemcpyDeviceToDevice, stream);
     return e;
+}
+
+hipError_t sphere_outside(pstd_solver* s, const double3* obs, int64_t n_obs, bool* outside, hipStream_t stream) {
+    SphereState* sp = s->sphere;
+    unsigned flag = 0;
+    hipError_t e = hipMemsetAsync(sp->flags, 0, sizeof(unsigned), stream);
+    if (e) return e;
+    hipLaunchKernelGGL(check_outside_kernel, dim3((unsigned)((n_obs + 255) / 256)), dim3(256), 0, stream, obs, n_obs,
+                       s->prob.sphere_radius, sp->flags);
+    if ((e = hipGetLastError()) ||
+        (e = hipMemcpyAsync(&flag, sp->flags, sizeof(flag), hipMemcpyDeviceToHost, stream)) ||
+        (e = hipStreamSynchronize(stream)))
+        return e;
+    *outside = flag == 0;
+    return hipSuccess;
 }
 
 hipError_t sphere_project(pstd_solver* s, const SphereOut& o, const double3* obs, int64_t n_obs, double2* out,
@@ -545,9 +636,7 @@ hipError_t sphere_project(pstd_solver* s, const SphereOut& o, const double3* obs
     SphereState* sp = s->sphere;
     hipError_t e = sphere_phasors(s, o, nullptr, stream);
     if (e || n_obs == 0) return e;
-    hipLaunchKernelGGL(sphere_points_kernel, dim3((unsigned)((n_obs + 255) / 256)), dim3(256), 0, stream, sp->n_nodes,
-                       sp->node, sp->normal, sp->weight, sp->phasor, obs, n_obs, s->prob.k0, o.k, out);
-    return hipGetLastError();
+    return sphere_sums<false>(s, o.k, obs, n_obs, -1.0 / (4 * kPi), out, stream);
 }
 
 hipError_t sphere_far_field(pstd_solver* s, const SphereOut& o, const double3* dirs, int64_t n_dir, double2* out,
@@ -555,9 +644,7 @@ hipError_t sphere_far_field(pstd_solver* s, const SphereOut& o, const double3* d
     SphereState* sp = s->sphere;
     hipError_t e = sphere_phasors(s, o, nullptr, stream);
     if (e || n_dir == 0) return e;
-    hipLaunchKernelGGL(sphere_far_kernel, dim3((unsigned)((n_dir + 255) / 256)), dim3(256), 0, stream, sp->n_nodes,
-                       sp->node, sp->normal, sp->weight, sp->phasor, dirs, n_dir, s->prob.k0, o.k, out);
-    return hipGetLastError();
+    return sphere_sums<true>(s, o.k, dirs, n_dir, -1.0 / (4 * kPi * s->prob.k0), out, stream);
 }
 
 }  // namespace pstd

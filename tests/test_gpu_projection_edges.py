@@ -122,3 +122,42 @@ def test_box_points_counts(P, n, count):
     far = np.vstack([pts[:3], [[3e9, -1e9, 2e9]]])
     got = s.project(far).cpu().numpy()
     assert np.abs(got[:-1] - s.project(pts[:3]).cpu().numpy()).max() <= 1e-13 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("nodes", [(3, 7), (16, 32), (18, 30)])
+@pytest.mark.parametrize("count", [1, 255, 511, 512, 513, 1100])
+def test_sphere_sums_counts(P, nodes, count):
+    """Output counts around one and two outputs per thread, node counts that
+    leave part of the last chunk: up to 540 FP64 terms of a few roundings each,
+    phases of order 10 known to 1e-15: 1e-12 of the largest."""
+    s, sph, (v, d) = sphere_case(P, nodes)
+    rng = np.random.default_rng(5)
+    dirs = directions(count, 4)
+    pts = dirs * rng.uniform(1.3, 9.0, size=(count, 1))
+    far = s.far_field(dirs).cpu().numpy()
+    ref = sph.far_field(v, d, dirs)
+    big = np.abs(sph.far_field(v, d, directions(20, 6))).max()
+    assert np.abs(far - ref).max() <= 1e-12 * max(big, np.abs(ref).max())
+    got = s.project(pts).cpu().numpy()
+    ref = sph.project(v, d, pts * sph.k0)
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+def test_sphere_sums_beyond_the_short_phase_range(P):
+    """A point or vector far out sends its workgroup through the general
+    sincos; its neighbours' values are the ones without it (phases of order 10,
+    both routines to a unit in the last place: 1e-13 of the largest).  A point
+    inside the sphere, or none at all, is refused."""
+    s, sph, _ = sphere_case(P, (16, 32))
+    dirs = directions(8, 4)
+    a = s.project(dirs * 3.0)
+    b = s.project(np.vstack([dirs * 3.0, [[0, 0, 1e12]]]))
+    assert (a - b[:8]).abs().max() <= 1e-13 * a.abs().max()
+    assert torch.isfinite(torch.view_as_real(b)).all()
+    a = s.far_field(dirs)
+    b = s.far_field(np.vstack([dirs, [[0, 1e12, 0]]]))
+    assert (a - b[:8]).abs().max() <= 1e-13 * a.abs().max()
+    for bad in ((0.0, 0.5, 0.0), (np.nan, 3.0, 0.0)):
+        with pytest.raises(P.PstdError) as e:
+            s.project(np.vstack([dirs * 3.0, [bad]]))
+        assert e.value.name == "PSTD_EINVAL"
