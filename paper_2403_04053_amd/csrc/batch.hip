@@ -1,10 +1,15 @@
 // Batched solves: many independent scattering problems (incident directions,
-// energies, potentials, uneven grids) advanced together.  Per axis, the
-// instances are grouped by compiled tile shape; one launch covers every
-// instance of a group (the workgroups look up their instance from a prefix
-// table of tiles), and each instance's step counter lives in device memory,
-// so whole groups of steps are captured once in a HIP graph and replayed.
-// An instance whose own step count is reached does no further work.
+// energies, potentials, uneven grids) advanced together.  The instances are
+// dealt to sets that share the Infinity Cache; a set takes all the steps of a
+// launch group before the next one starts, so its fields stay in the cache
+// from pass to pass and step to step, and the sets run on a few branches side
+// by side, so that one's launch gaps and last workgroups overlap with
+// another's work.  Within a set, per axis, the instances are grouped by
+// compiled tile shape; one launch covers every instance of a group (the
+// workgroups look up their instance from a prefix table of tiles), and each
+// instance's step counter lives in device memory, so whole groups of steps are
+// captured once in a HIP graph and replayed.  An instance whose own step count
+// is reached does no further work.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,6 +23,14 @@
 namespace {
 
 constexpr int kBatchGraphSteps = 8;
+// Branches that run side by side, and the bytes of fields (psi pair and L, 24 B
+// per cell) of the sets on them at a time: under the 256 MB Infinity Cache.
+// Twelve instances of 96-192 points per axis (775 MB), 16 steps: all instances
+// pass by pass 11.55 ms; sets of 64 or 128 MB one after another 8.70; two
+// branches 6.94 (128 MB) to 7.04 (200 MB), three 6.68 (200 MB), 6.70 (128), 6.84
+// (300), four 6.95.  64 instances: 63.4 -> 78.9 Gcell/s.
+constexpr int kBranches = 3;
+constexpr double kSetBytes = 200e6 / kBranches;
 
 thread_local std::string g_batch_error;
 
@@ -31,14 +44,23 @@ struct Group {
     int tiles = 0;
 };
 
+// instances that take a launch group's steps together
+struct Set {
+    std::vector<int> members;
+    std::vector<Group> groups[3];
+    int branch = 0;
+};
+
 }  // namespace
 
 struct pstd_batch {
     std::vector<pstd_solver*> inst;
     hipStream_t stream = nullptr;
     int64_t* ctr = nullptr;  // [count][2]: step, end
-    std::vector<Group> groups[3];
+    std::vector<Set> sets;
     hipStream_t cap_stream = nullptr;
+    hipStream_t branch[kBranches] = {};      // streams of the other branches (capture only; [0] unused)
+    hipEvent_t fork = nullptr, join[kBranches] = {};
     hipGraphExec_t graph = nullptr;
     std::vector<int> gen;  // table generation of each instance when the groups were built
     int nt = 0;            // an instance's fields outgrow the Infinity Cache
@@ -64,13 +86,13 @@ pstd_status bhip(pstd_batch* b, hipError_t e, const char* what) {
     } while (0)
 
 void free_groups(pstd_batch* b) {
-    for (auto& gs : b->groups) {
-        for (auto& g : gs) {
-            (void)hipFree(g.d_desc);
-            (void)hipFree(g.d_off);
-        }
-        gs.clear();
-    }
+    for (Set& set : b->sets)
+        for (auto& gs : set.groups)
+            for (auto& g : gs) {
+                (void)hipFree(g.d_desc);
+                (void)hipFree(g.d_off);
+            }
+    b->sets.clear();
 }
 
 void drop_graph(pstd_batch* b) {
@@ -78,27 +100,11 @@ void drop_graph(pstd_batch* b) {
     b->graph = nullptr;
 }
 
-// (re)build the per-axis launch groups from the instances' current tile
-// shapes and tables
-pstd_status build_groups(pstd_batch* b) {
-    BHIP_TRY(b, hipStreamSynchronize(b->stream));
-    drop_graph(b);  // the graph holds the old descriptor buffers
-    free_groups(b);
-    b->gen.resize(b->inst.size());
-    // non-temporal z-pass loads when an instance alone outgrows the Infinity
-    // Cache (as for a single solve); for many instances that each fit, the
-    // hint measured slower (64 instances of 96-192 per axis: 59.0 -> 57.6
-    // Gcell/s)
-    double largest = 0;
-    for (size_t i = 0; i < b->inst.size(); ++i) {
-        b->gen[i] = b->inst[i]->tab_gen;
-        const pstd_problem& p = b->inst[i]->prob;
-        largest = std::max(largest, 24.0 * p.n[0] * p.n[1] * p.n[2]);
-    }
-    b->nt = largest > pstd::kInfinityCacheBytes ? 1 : 0;
+// the per-axis launch groups of a set
+pstd_status build_set(pstd_batch* b, Set& set) {
     for (int axis = 0; axis < 3; ++axis) {
-        std::vector<Group>& gs = b->groups[axis];
-        for (int i = 0; i < (int)b->inst.size(); ++i) {
+        std::vector<Group>& gs = set.groups[axis];
+        for (int i : set.members) {
             const pstd_solver* s = b->inst[i];
             const bool seg = s->prob.sub_core[axis] > 0;
             const int potx = axis == 1 ? 0 : s->potx;
@@ -131,15 +137,87 @@ pstd_status build_groups(pstd_batch* b) {
     return PSTD_OK;
 }
 
-// `count` consecutive steps of every instance, then one counter advance
-pstd_status launch_batch_steps(pstd_batch* b, hipStream_t stream, int count) {
-    for (int k = 0; k < count; ++k)
-        for (int axis = 0; axis < 3; ++axis)
-            for (const Group& g : b->groups[axis]) {
-                hipError_t e = pstd::launch_variant(g.variant, g.seg, axis, g.d_desc, g.d_off, (int)g.members.size(),
-                                                    g.tiles, k, g.potx, b->nt, stream);
-                if (e != hipSuccess) return bhip(b, e, "batch pass launch");
-            }
+// (re)build the sets and their per-axis launch groups from the instances'
+// current tile shapes and tables
+pstd_status build_groups(pstd_batch* b) {
+    BHIP_TRY(b, hipStreamSynchronize(b->stream));
+    drop_graph(b);  // the graph holds the old descriptor buffers
+    free_groups(b);
+    b->gen.resize(b->inst.size());
+    // non-temporal z-pass loads when an instance alone outgrows the Infinity
+    // Cache (as for a single solve); for many instances that each fit, the
+    // hint measured slower (64 instances of 96-192 per axis: 59.0 -> 57.6
+    // Gcell/s)
+    double largest = 0;
+    for (size_t i = 0; i < b->inst.size(); ++i) {
+        b->gen[i] = b->inst[i]->tab_gen;
+        const pstd_problem& p = b->inst[i]->prob;
+        largest = std::max(largest, 24.0 * p.n[0] * p.n[1] * p.n[2]);
+    }
+    b->nt = largest > pstd::kInfinityCacheBytes ? 1 : 0;
+    // sets: instances of like shape next to each other (so that a set's launches
+    // are few), each set filled to its share of the cache; largest sets first
+    // onto the branch with the least work
+    std::vector<int> order(b->inst.size());
+    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        const int32_t *nx = b->inst[x]->prob.n, *ny = b->inst[y]->prob.n;
+        return std::lexicographical_compare(nx, nx + 3, ny, ny + 3);
+    });
+    std::vector<double> bytes;
+    for (int i : order) {
+        const double size = 24.0 * (double)b->inst[i]->cells;
+        if (bytes.empty() || bytes.back() + size > kSetBytes) {
+            b->sets.emplace_back();
+            bytes.push_back(0);
+        }
+        b->sets.back().members.push_back(i);
+        bytes.back() += size;
+    }
+    double load[kBranches] = {};
+    std::vector<int> by(b->sets.size());
+    for (size_t i = 0; i < by.size(); ++i) by[i] = (int)i;
+    std::stable_sort(by.begin(), by.end(), [&](int x, int y) { return bytes[x] > bytes[y]; });
+    for (int i : by) {
+        const int k = (int)(std::min_element(load, load + kBranches) - load);
+        b->sets[i].branch = k;
+        load[k] += bytes[i];
+    }
+    for (Set& set : b->sets)
+        if (pstd_status st = build_set(b, set)) return st;
+    return PSTD_OK;
+}
+
+// `count` consecutive steps of the sets of one branch, or of all (branch < 0)
+pstd_status launch_branch(pstd_batch* b, int branch, hipStream_t stream, int count) {
+    for (const Set& set : b->sets) {
+        if (branch >= 0 && set.branch != branch) continue;
+        for (int k = 0; k < count; ++k)
+            for (int axis = 0; axis < 3; ++axis)
+                for (const Group& g : set.groups[axis]) {
+                    hipError_t e = pstd::launch_variant(g.variant, g.seg, axis, g.d_desc, g.d_off, (int)g.members.size(),
+                                                        g.tiles, k, g.potx, b->nt, stream);
+                    if (e != hipSuccess) return bhip(b, e, "batch pass launch");
+                }
+    }
+    return PSTD_OK;
+}
+
+// `count` consecutive steps of every instance, then one counter advance;
+// `branches`: the branches side by side (in a capture), else one after another
+pstd_status launch_batch_steps(pstd_batch* b, hipStream_t stream, int count, bool branches) {
+    if (!branches || b->sets.size() < 2) {
+        if (pstd_status st = launch_branch(b, -1, stream, count)) return st;
+    } else {
+        BHIP_TRY(b, hipEventRecord(b->fork, stream));
+        for (int k = 1; k < kBranches; ++k) {
+            BHIP_TRY(b, hipStreamWaitEvent(b->branch[k], b->fork, 0));
+            if (pstd_status st = launch_branch(b, k, b->branch[k], count)) return st;
+            BHIP_TRY(b, hipEventRecord(b->join[k], b->branch[k]));
+        }
+        if (pstd_status st = launch_branch(b, 0, stream, count)) return st;
+        for (int k = 1; k < kBranches; ++k) BHIP_TRY(b, hipStreamWaitEvent(stream, b->join[k], 0));
+    }
     hipError_t e = pstd::launch_advance(b->ctr, (int)b->inst.size(), count, stream);
     if (e != hipSuccess) return bhip(b, e, "batch advance");
     return PSTD_OK;
@@ -148,8 +226,13 @@ pstd_status launch_batch_steps(pstd_batch* b, hipStream_t stream, int count) {
 pstd_status build_batch_graph(pstd_batch* b) {
     if (b->graph) return PSTD_OK;
     if (!b->cap_stream) BHIP_TRY(b, hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
+    if (!b->fork) BHIP_TRY(b, hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
+    for (int k = 1; k < kBranches; ++k) {
+        if (!b->branch[k]) BHIP_TRY(b, hipStreamCreateWithFlags(&b->branch[k], hipStreamNonBlocking));
+        if (!b->join[k]) BHIP_TRY(b, hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming));
+    }
     BHIP_TRY(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-    pstd_status st = launch_batch_steps(b, b->cap_stream, kBatchGraphSteps);
+    pstd_status st = launch_batch_steps(b, b->cap_stream, kBatchGraphSteps, true);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap_stream, &g);
     if (st) {
@@ -274,7 +357,7 @@ pstd_status pstd_batch_run(pstd_batch* b, const int64_t* n_steps_host) {
         for (; left >= kBatchGraphSteps; left -= kBatchGraphSteps) BHIP_TRY(b, hipGraphLaunch(b->graph, b->stream));
     }
     if (left > 0) {
-        pstd_status st = launch_batch_steps(b, b->stream, (int)left);
+        pstd_status st = launch_batch_steps(b, b->stream, (int)left, false);
         if (st) return st;
     }
     for (int i = 0; i < count; ++i) {
@@ -291,6 +374,11 @@ pstd_status pstd_batch_destroy(pstd_batch* b) {
     else (void)hipDeviceSynchronize();
     drop_graph(b);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
+    for (int k = 1; k < kBranches; ++k) {
+        if (b->branch[k]) (void)hipStreamDestroy(b->branch[k]);
+        if (b->join[k]) (void)hipEventDestroy(b->join[k]);
+    }
+    if (b->fork) (void)hipEventDestroy(b->fork);
     free_groups(b);
     for (pstd_solver* s : b->inst) pstd_destroy(s);
     (void)hipFree(b->ctr);
