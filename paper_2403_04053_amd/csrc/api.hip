@@ -432,7 +432,7 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
             for (int i = 1; i < 6; ++i) HIP_TRY(s, hipEventRecord(ev[i], stream));
         return PSTD_OK;
     }
-    const bool xy = pstd::solver_xy(s);
+    const bool segxy = pstd::solver_seg_xy(s), xy = segxy || pstd::solver_xy(s);
     // box surface: groups of a few steps stage their plane values and add them
     // to the sums once, at the group's end (pulsed runs always: solver_args)
     const bool stage = !s->pulse && s->bring[0] && count >= kStageMin;
@@ -446,7 +446,8 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
         args_of(0, a);
         args_of(1, b);
         if (ev) HIP_TRY(s, hipEventRecord(ev[0], stream));
-        hipError_t e = pstd::launch_variant_xy(s->variant[0], a, b, false, koff, stream);
+        hipError_t e = segxy ? pstd::launch_variant_seg_xy(s->variant[0], a, b, koff, stream)
+                             : pstd::launch_variant_xy(s->variant[0], a, b, false, koff, stream);
         if (e != hipSuccess) return hip_fail(s, e, "pass launch");
         if (ev)
             for (int i = 1; i < 4; ++i) HIP_TRY(s, hipEventRecord(ev[i], stream));
@@ -877,7 +878,8 @@ pstd_status solver_autotune(pstd_solver* s, int32_t reps) {
     // FDTD step has one shape)
     if (s->prob.scheme == 1) return PSTD_OK;
     // (solvers with L2 take one shape for x and y, timed in their one launch)
-    for (int axis = s->L2 ? 1 : 0; axis < 3; ++axis) {
+    // (fused segment blocks have one form)
+    for (int axis = solver_seg_xy(s) ? 2 : s->L2 ? 1 : 0; axis < 3; ++axis) {
         const bool xy = s->L2 && axis == 1;
         const bool seg = s->prob.sub_core[axis] > 0;
         int ids[16];

@@ -126,6 +126,11 @@ hipError_t launch_variant_single(int v, bool segmented, int axis, const PassArgs
 // launch, the y term in ay.L2; the z pass of the same step takes L2 too
 hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff,
                              hipStream_t stream);
+// Whether segment blocks of `core` points and local length N along both x and y
+// take the fused x and y passes (core rows and columns on at least half of the
+// pencils of the compiled block); and their launch, in the place of the two
+bool seg_xy_block(int N, int core);
+hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream);
 // The largest fields (psi pair, L and L2, 32 B per cell) whose x and y passes
 // run in one launch: the array more has to stay in the Infinity Cache.
 // Measured, separate passes against one launch: 160 x 160 x 192 (157 MB) 69.0 and

@@ -16,12 +16,13 @@ struct VariantEntry {
     LaunchFn seg;  // null when the shape has no segmented instance
     AdjFn adj;
     XyFn xy;
+    SegXyFn segxy;
 };
 
 const VariantEntry kVariants[] = {
 #define PSTD_ENTRY(N_, A_, B_, M_, P_, S_, PART_)                                                              \
     {PassShape{N_, A_, B_, P_, P_ * (A_ > B_ ? A_ : B_), M_}, &PSTD_FN(plain, N_, A_, B_, M_, P_),                  \
-     (S_) ? &PSTD_FN(seg, N_, A_, B_, M_, P_) : nullptr, &PSTD_FN(adj, N_, A_, B_, M_, P_), &PSTD_FN(xy, N_, A_, B_, M_, P_)},
+     (S_) ? &PSTD_FN(seg, N_, A_, B_, M_, P_) : nullptr, &PSTD_FN(adj, N_, A_, B_, M_, P_), &PSTD_FN(xy, N_, A_, B_, M_, P_), &PSTD_FN(segxy, N_, A_, B_, M_, P_)},
     PSTD_VARIANTS(PSTD_ENTRY)
 #undef PSTD_ENTRY
 };
@@ -78,6 +79,20 @@ hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool
     const int N = v < 0 || v >= kNumVariants ? 0 : kVariants[v].shape.N;
     if (ax.nx != N || ax.ny != N || !ax.L2 || !ay.L2) return hipErrorInvalidValue;
     return kVariants[v].xy(ax, ay, adjoint, koff, stream);
+}
+
+bool seg_xy_block(int N, int core) {
+    const int P = seg_xy_pencils(N);
+    return core <= P && 2 * core > P;
+}
+
+hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream) {
+    if (v < 0 || v >= kNumVariants) return hipErrorInvalidValue;
+    if (ax.seg_core != ay.seg_core || ax.seg_halo != ay.seg_halo ||
+        kVariants[v].shape.N != ax.seg_core + 2 * ax.seg_halo || !seg_xy_block(kVariants[v].shape.N, ax.seg_core) ||
+        ax.nseg * ax.seg_core != ax.nx || ay.nseg * ay.seg_core != ay.ny)
+        return hipErrorInvalidValue;
+    return kVariants[v].segxy(ax, ay, koff, stream);
 }
 
 hipError_t launch_variant_adjoint(int v, int axis, const PassArgs& args, int koff, hipStream_t stream) {

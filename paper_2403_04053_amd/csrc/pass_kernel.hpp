@@ -257,6 +257,35 @@ __device__ __forceinline__ GMEM const T* at_step(GMEM const T* p, int n1, int64_
     return (GMEM const T*)((GMEM const char*)p + (int64_t)n1 * step);
 }
 
+// Geometry of a pencil of a fused segment block (pass_seg_xy_kernel): block
+// (bx, by) of plane z, pencils 0 .. core - 1 are its rows (x) or columns (y)
+struct SegBlock {
+    int bx, by, z;
+};
+
+template <int AXIS>
+__device__ __forceinline__ TileGeo block_geo(const Fields& f, const SegBlock& b, int pA, bool activeA) {
+    TileGeo g;
+    const int C = f.seg_core, H = f.seg_halo;
+    g.px = g.py = g.tx = g.tq = 0;
+    g.valid = activeA && pA < C;
+    const int64_t plane = (int64_t)f.nx * f.ny * b.z;
+    if constexpr (AXIS == 0) {
+        g.seg = b.bx;
+        g.g0 = b.bx * C - H;
+        g.Ng = f.nx;
+        g.estride = 1;
+        g.base = plane + (int64_t)f.nx * (b.by * C + pA) + g.g0;
+    } else {
+        g.seg = b.by;
+        g.g0 = b.by * C - H;
+        g.Ng = f.ny;
+        g.estride = f.nx;
+        g.base = plane + (b.bx * C + pA) + (int64_t)f.nx * g.g0;
+    }
+    return g;
+}
+
 // raw pencil values of one tile; p: the thread's element 0.  A segment's
 // values are zero outside the grid.  Whole-axis pencils lie inside the grid
 // as a whole: threads without one (the last tile's, or idle in stage A) read
@@ -311,11 +340,16 @@ __device__ __forceinline__ int xcd_tile(bool back) {
 
 // The work of one workgroup on one tile of P pencils along AXIS.  OWN: the y
 // pass writes its term to an array of its own (f.L2) instead of adding to L,
-// so that it does not depend on the x pass; the z pass adds both.
-template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool ADJ, bool POTX, bool NTL, bool OWN>
+// so that it does not depend on the x pass; the z pass adds both.  FUSED: the
+// tile is the rows or columns of segment block blk; the x pass leaves its term
+// of the core in ex, where the y pass finds it, and the y pass's field values
+// (pre) were loaded before the x pass.
+template <int N, int N1, int N2, int M1, int P, int AXIS, bool SEG, bool ADJ, bool POTX, bool NTL, bool OWN,
+          bool FUSED = false>
 __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, float2* __restrict__ ex,
                                           float2* __restrict__ s_tw, float* __restrict__ s_kk,
-                                          float2* __restrict__ s_dr) {
+                                          float2* __restrict__ s_dr, SegBlock blk = SegBlock{},
+                                          const float2* pre = nullptr) {
     constexpr int NT = P * (N1 > N2 ? N1 : N2);
     constexpr int ROW = TileLds<N, N1, N2>::ROW;
     constexpr int STRIDE = TileLds<N, N1, N2>::STRIDE;
@@ -344,12 +378,16 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
         r_tw[decltype(i)::value] = f.tw[j];
         r_kk[decltype(i)::value] = f.kk[j];
     });
-    const TileGeo geo = tile_geo<N, P, AXIS, SEG>(f, tile, pA, activeA);
+    TileGeo geo;
+    if constexpr (FUSED) geo = block_geo<AXIS>(f, blk, pA, activeA);
+    else geo = tile_geo<N, P, AXIS, SEG>(f, tile, pA, activeA);
+    constexpr int LROW = P + 1;  // row of s_L
     // this thread's element 0 (a whole pencil's first one for threads without a pencil)
     const int64_t first = SEG || geo.valid ? geo.base + (int64_t)n2 * geo.estride : 0;
     const int64_t step = (int64_t)(N2 * sizeof(float2)) * geo.estride;  // bytes between its elements
     float2 raw[N1];
-    load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi + first, step, geo, n2, raw);
+    if constexpr (FUSED && AXIS == 1) unroll<N1>([&](auto i) { raw[decltype(i)::value] = pre[decltype(i)::value]; });
+    else load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi + first, step, geo, n2, raw);
     unroll<TR>([&](auto i) {
         const int j = min(t + decltype(i)::value * NT, N - 1);
         s_tw[j] = r_tw[decltype(i)::value];
@@ -384,7 +422,17 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
         // (the other way round there cost 2-3 %)
         float2 Lin[N1];
         auto load_L = [&]() {
-            if constexpr (AXIS == 1 && !OWN) {
+            if constexpr (AXIS == 1 && FUSED) {
+                // the x term of this thread's core elements, before the barrier
+                // that precedes the first use of ex here
+                const int C = f.seg_core, H = f.seg_halo;
+                unroll<N1>([&](auto i) {
+                    constexpr int n1 = decltype(i)::value;
+                    const int e = n2 + N2 * n1;
+                    Lin[n1] = make_float2(0.f, 0.f);
+                    if (geo.valid && e >= H && e < H + C) Lin[n1] = ex[(e - H) * LROW + pA];
+                });
+            } else if constexpr (AXIS == 1 && !OWN) {
                 // (the branch on geo.valid keeps these loads here: without it the
                 // compiler issues them with the field loads, 103 instead of 85 VGPRs)
                 GMEM const float2* Lp = f.L + first;
@@ -632,7 +680,9 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    if (!SEG || (e >= H && e < H + C)) *at_step(Lbuf + first, n1, step) = v[n1];
+                    if constexpr (!FUSED) {
+                        if (!SEG || (e >= H && e < H + C)) *at_step(Lbuf + first, n1, step) = v[n1];
+                    }
                 });
             } else if constexpr (AXIS == 1) {
                 unroll<N1>([&](auto i) {
@@ -734,7 +784,11 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                 const int segp = side ? f.seg_plane1 : f.seg_plane0;
                 const int nseg = SEG ? f.nseg : 1;
                 int64_t spt = -1;
-                if constexpr (AXIS == 0) {
+                if constexpr (FUSED) {
+                    if (p < f.seg_core && geo.seg == segp)
+                        spt = AXIS == 0 ? (int64_t)f.ny * blk.z + blk.by * f.seg_core + p
+                                        : (int64_t)f.nx * blk.z + blk.bx * f.seg_core + p;
+                } else if constexpr (AXIS == 0) {
                     const int64_t qq = (int64_t)tile * P + p;
                     if (qq < (int64_t)f.ny * f.nz * nseg && (int)(qq % nseg) == segp) spt = qq / nseg;
                 } else {
@@ -763,6 +817,18 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                     *Cc = cv;
                 }
             }
+        }
+        // fused blocks: the x term of the core rows for the y pass
+        if constexpr (FUSED && AXIS == 0) {
+            __syncthreads();  // ex has been read
+            const int C = f.seg_core, H = f.seg_halo;
+            if (geo.valid)
+                unroll<N1>([&](auto i) {
+                    constexpr int n1 = decltype(i)::value;
+                    const int e = n2 + N2 * n1;
+                    if (e >= H && e < H + C) ex[pA * LROW + e - H] = v[n1];
+                });
+            __syncthreads();
         }
     }
 }
@@ -814,6 +880,40 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_xy_kernel(PassAr
         pass_tile<N, N1, N2, M1, P, 1, false, ADJ, true, false, true>(f, tile, koff, ex, s_tw, s_kk, s_dr);
     }
 }
+
+// Subdomains: the x and y passes of one core block of a plane in one workgroup
+// (x and y segmented alike, the block's C rows and columns as many pencils as
+// P): the x term stays in LDS until the y pass adds its own, so L is written
+// once and psi^n read beyond the L2 once, 8 + 8 instead of 18 + 26 B per cell.
+// 288 x 192 x 240 in cores of 48 with 8-cell halos: 75 to 80 us against 30.3 + 41.0
+// (the step 163 against 180); it is then bound by vector instructions, about 67 us of it.
+template <int N, int N1, int N2, int M1, int P>
+__global__ __launch_bounds__(P * N2) void pass_seg_xy_kernel(PassArgs ax, PassArgs ay, int koff) {
+    static_assert(P + 1 <= TileLds<N, N1, N2>::STRIDE, "the x term fits the exchange buffer");
+    PSTD_TILE_LDS(N, N1, N2, P)
+    const int gt = xcd_tile(false);
+    SegBlock b;
+    b.bx = gt % ax.nseg;
+    b.by = (gt / ax.nseg) % ay.nseg;
+    b.z = gt / (ax.nseg * ay.nseg);
+    const Fields fx = fields<0>(ax);
+    const Fields fy = fields<1>(ay);
+    float2 pre[N1];
+    {
+        const int64_t nstep = fy.ctr[0] + koff;
+        if (nstep >= fy.ctr[1]) return;  // whole workgroup
+        const int t = threadIdx.x, pA = t % P, n2 = t / P;
+        const TileGeo g = block_geo<1>(fy, b, pA, true);
+        load_tile<N, N1, N2, true>(((nstep & 1) ? fy.buf1 : fy.buf0) + g.base + (int64_t)n2 * g.estride,
+                                   (int64_t)(N2 * sizeof(float2)) * g.estride, g, n2, pre);
+    }
+    pass_tile<N, N1, N2, M1, P, 0, true, false, false, false, false, true>(fx, 0, koff, ex, s_tw, s_kk, s_dr, b);
+    pass_tile<N, N1, N2, M1, P, 1, true, false, false, false, false, true>(fy, 0, koff, ex, s_tw, s_kk, s_dr, b, pre);
+}
+
+// pencils of a fused segment block for local length N (0: none; longer blocks
+// leave one workgroup per CU)
+constexpr int seg_xy_pencils(int N) { return N == 32 ? 16 : N == 48 ? 32 : N == 64 ? 48 : 0; }
 
 using LaunchFn = hipError_t (*)(int axis, const PassArgs& single, const PassArgs* descs, const int* off, int ninst,
                                 int tiles, int koff, hipStream_t stream);
@@ -890,6 +990,21 @@ static hipError_t launch_xy_shape(const PassArgs& ax, const PassArgs& ay, bool a
     return hipGetLastError();
 }
 
+// the fused x and y passes of segment blocks (hipErrorInvalidValue: none for N)
+template <int S, int N, int N1, int N2, int M1>
+static hipError_t launch_seg_xy_shape(const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream) {
+    if constexpr (S != 0 && M1 == 0 && seg_xy_pencils(N) > 0) {
+        constexpr int P = seg_xy_pencils(N);
+        static_assert(N1 <= N2, "N2 threads per pencil");
+        hipLaunchKernelGGL((pass_seg_xy_kernel<N, N1, N2, M1, P>), dim3(ax.nseg * ay.nseg * ax.nz), dim3(P * N2), 0,
+                           stream, ax, ay, koff);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+
+using SegXyFn = hipError_t (*)(const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream);
 using XyFn = hipError_t (*)(const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff, hipStream_t stream);
 using AdjFn = hipError_t (*)(int axis, const PassArgs& a, int koff, hipStream_t stream);
 
@@ -908,7 +1023,8 @@ hipError_t launch_segmented_shape(int axis, const PassArgs& single, const PassAr
     hipError_t PSTD_FN(seg, N_, A_, B_, M_, P_)(int, const PassArgs&, const PassArgs*, const int*, int, int, int,   \
                                                hipStream_t);                                                     \
     hipError_t PSTD_FN(adj, N_, A_, B_, M_, P_)(int, const PassArgs&, int, hipStream_t);                               \
-    hipError_t PSTD_FN(xy, N_, A_, B_, M_, P_)(const PassArgs&, const PassArgs&, bool, int, hipStream_t);
+    hipError_t PSTD_FN(xy, N_, A_, B_, M_, P_)(const PassArgs&, const PassArgs&, bool, int, hipStream_t);              \
+    hipError_t PSTD_FN(segxy, N_, A_, B_, M_, P_)(const PassArgs&, const PassArgs&, int, hipStream_t);
 #define PSTD_DEFINE_SHAPE(N_, A_, B_, M_, P_, S_)                                                                   \
     hipError_t PSTD_FN(plain, N_, A_, B_, M_, P_)(int axis, const PassArgs& single, const PassArgs* descs,            \
                                                  const int* off, int ninst, int tiles, int koff, hipStream_t stream) { \
@@ -924,6 +1040,9 @@ hipError_t launch_segmented_shape(int axis, const PassArgs& single, const PassAr
     hipError_t PSTD_FN(xy, N_, A_, B_, M_, P_)(const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff,        \
                                               hipStream_t stream) {                                                \
         return launch_xy_shape<N_, A_, B_, M_, P_>(ax, ay, adjoint, koff, stream);                                    \
+    }                                                                                                              \
+    hipError_t PSTD_FN(segxy, N_, A_, B_, M_, P_)(const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream) { \
+        return launch_seg_xy_shape<S_, N_, A_, B_, M_>(ax, ay, koff, stream);                                         \
     }
 
 }  // namespace pstd

@@ -80,6 +80,12 @@ void solver_args(const pstd_solver* s, int axis, PassArgs& a);
 void solver_account_steps(pstd_solver* s, int64_t from, int64_t to);
 pstd_status solver_autotune(pstd_solver* s, int32_t reps);
 void solver_drop_graph(pstd_solver* s);
+// the x and y passes of segment blocks alike along both axes run fused
+inline bool solver_seg_xy(const pstd_solver* s) {
+    const pstd_problem& p = s->prob;
+    return !s->in_batch && p.sub_core[0] > 0 && p.sub_core[0] == p.sub_core[1] &&
+           s->variant[0] == s->variant[1] && seg_xy_block(p.sub_core[0] + 2 * p.sub_halo, p.sub_core[0]);
+}
 // the x and y passes run in one launch (solver_args then sets PassArgs::L2)
 inline bool solver_xy(const pstd_solver* s) { return s->L2 && s->variant[0] == s->variant[1]; }
 // the misfit forward run no longer matches the solver state

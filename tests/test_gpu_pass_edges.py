@@ -39,6 +39,27 @@ def test_xy_launch_equals_separate_passes(P, n, real):
     assert torch.equal(one.phasors(), inst.phasors())
 
 
+@pytest.mark.parametrize("core,halo,n", [(16, 8, (48, 32, 20)), (12, 10, (36, 24, 24)), (32, 8, (64, 96, 20)),
+                                         (20, 14, (60, 40, 20)), (48, 8, (48, 96, 24)), (28, 18, (84, 56, 20))])
+def test_fused_segment_blocks_equal_separate_passes(P, core, halo, n):
+    """Blocks that fill the compiled pencils and ones that leave some idle, one
+    block along an axis and several, with the box planes in first and last blocks;
+    the sums are the same operations in the same order: equal to the bit."""
+    prob, V = synth.tiny(n=n, P=3, transition=2, v0=0.5, radius_cells=3, steps=5, dft=(1, 4), theta=0.7, phi=0.3)
+    prob = prob.replace(ramp_periods=0.1, sub_core=(core, core, 0), sub_halo=halo, sub_taper=3)
+    a, b = synth.random_state(n, 1), synth.random_state(n, 2)
+    one = P.Solver(prob)
+    many = P.Batch([prob])
+    inst = many.instance(0)
+    for s in (one, inst):
+        s.set_potential(V)
+        s.set_state(a, b, 1)
+    one.run(5)
+    many.run(5)
+    assert torch.equal(one.psi(), inst.psi()) and torch.equal(one.psi(1), inst.psi(1))
+    assert torch.equal(one.phasors(), inst.phasors())
+
+
 @pytest.mark.parametrize("core", [(0, 16, 16), (16, 0, 16), (16, 16, 0), (0, 0, 16), (16, 0, 0)])
 def test_potential_term_with_segments_along_some_axes(P, core):
     """One step with V minus one without it is -2i dtau Gamma v psi^n at every
