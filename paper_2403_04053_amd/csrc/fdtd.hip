@@ -13,12 +13,14 @@
 // e^{pm i kh_a l dxb_a}: the same form as the taper source of the spectral
 // scheme, so the same per-axis tables carry it.
 //
-// A workgroup owns a 32 x 8 tile of (x, y) columns and a run of 16 z planes.
+// A workgroup owns a 32 x kFY tile of (x, y) columns and a run of z planes.
 // Each thread keeps the nine values psi(z-4 .. z+4) of its column in VGPRs
 // (the z stencil) and the plane z of the tile with a 4-cell halo is staged
-// in LDS (the x and y stencils).  The loads of plane z + 1 (the halo cells,
-// the next column value, psi^{n-1} and V) are issued right after plane z is
-// staged, so they are in flight while plane z is computed.
+// in LDS (the x and y stencils), in two buffers so that one barrier per plane
+// is enough.  The loads of plane z + 2 (the halo cells, the next column value,
+// psi^{n-1} and V) are issued right after plane z is staged, so they are in
+// flight while planes z and z + 1 are computed; the z factors come from LDS,
+// because a load of them from memory would return behind all of those.
 // The grid is periodic (indices wrap), like the spectral passes.
 #include "dft.hpp"
 #include "internal.hpp"
@@ -28,11 +30,10 @@ namespace pstd {
 namespace {
 
 constexpr int kFX = 32;   // tile x (one wave row)
-constexpr int kFY = 8;    // tile y
 constexpr int kFH = 4;    // stencil reach
-constexpr int kFZ = 16;   // z planes per workgroup
+constexpr int kCUs = 256;
+constexpr int kFZ = 16;   // z planes per workgroup at most
 constexpr int kSX = kFX + 2 * kFH;
-constexpr int kSY = kFY + 2 * kFH;
 
 __device__ __forceinline__ int wrap(int i, int n) {
     i %= n;
@@ -41,14 +42,24 @@ __device__ __forceinline__ int wrap(int i, int n) {
 
 typedef float float2_vec __attribute__((ext_vector_type(2)));
 
-// Five waves per SIMD: the prefetched plane needs about 96 VGPRs, and the
-// register cap of six or more waves serialises its loads or spills.  NTL:
-// psi^{n-1}, read here for the last time, comes in with non-temporal loads
-// (chosen for fields beyond the Infinity Cache, which then keeps the
+// Bound by the arithmetic and the LDS reads of a plane in turn with its
+// barrier: about 90 vector and 57 scalar instructions and 21 LDS accesses per
+// wave and plane, with psi 8 B read 1.5 times (runs overlap by eight planes)
+// and 20 B of other traffic per cell next to it (160^3: 18 us of copy time).
+// Everything that a plane loads has a register set of its own, three deep, so
+// that no copy of a value just loaded waits for it.  16 planes unrolled: the
+// column rotates by names instead of moves.  160^3: 27.2 -> 23.5 us, 288^3
+// 181 -> 146 us, 98 x 134 x 150 23.6 -> 17.0, 48 x 64 x 80 16.1 -> 6.9.
+// NTL: psi^{n-1}, read here for the last time, comes in with non-temporal
+// loads (chosen for fields beyond the Infinity Cache, which then keeps the
 // psi^{n+1} this step writes for the next).
-template <bool NTL>
-__global__ __launch_bounds__(kFX * kFY) __attribute__((amdgpu_waves_per_eu(5))) void fdtd_kernel(FdtdArgs a, int koff) {
-    __shared__ float2 s[kSY][kSX + 1];
+template <bool NTL, int kFY>
+__global__ __launch_bounds__(kFX * kFY) __attribute__((amdgpu_waves_per_eu(4))) void fdtd_kernel(FdtdArgs a, int run,
+                                                                                                  int koff) {
+    constexpr int kSY = kFY + 2 * kFH;
+    __shared__ float2 s[2][kSY * (kSX + 1) + 32];
+    __shared__ float2 s_zt[kFZ], s_dz[kFZ];
+    __shared__ float s_gam[kFZ];
     const int tx = threadIdx.x, ty = threadIdx.y;
     const int t = ty * kFX + tx;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -68,16 +79,24 @@ __global__ __launch_bounds__(kFX * kFY) __attribute__((amdgpu_waves_per_eu(5))) 
     const int x = bx + tx, y = by + ty;
     const bool valid = x < nx && y < ny;
     const int xw = wrap(x, nx), yw = wrap(y, ny);
-    const int64_t col = xw + (int64_t)nx * yw;
+    // a plane holds fewer than 2^31 cells
+    const int col = xw + nx * yw;
     const int64_t plane = (int64_t)nx * ny;
-    const int z0 = bz * kFZ;
-    const int z1 = min(z0 + kFZ, nz);
+    const int z0 = bz * run;
+    const int z1 = min(z0 + run, nz);
 
-    // the column psi(z0-4 .. z0+4)
-    float2 q[2 * kFH + 1];
-    unroll<2 * kFH + 1>([&](auto i) {
+    if (t < z1 - z0) {
+        s_zt[t] = a.zt[2][z0 + t];
+        s_dz[t] = a.dz[2][z0 + t];
+        s_gam[t] = a.gam[2][z0 + t];
+    }
+    // the column psi(z0-4 .. z0+5); at plane z, q[(r + z - z0) mod Q] holds
+    // psi(z - 4 + r)
+    constexpr int Q = 2 * kFH + 3;
+    float2 q[Q];
+    unroll<Q - 1>([&](auto i) {
         constexpr int r = decltype(i)::value;
-        q[r] = psi[col + plane * wrap(z0 - kFH + r, nz)];
+        q[r] = (psi + plane * wrap(z0 - kFH + r, nz))[col];
     });
     // per-column factors of the mask and of the wall terms
     const float2 Zx = a.zt[0][xw], Dx = a.dz[0][xw];
@@ -87,77 +106,82 @@ __global__ __launch_bounds__(kFX * kFY) __attribute__((amdgpu_waves_per_eu(5))) 
     const float gxy = a.gam[0][xw] * a.gam[1][yw];
     const float2 sigma = a.sigma_tab[nstep];
 
-    // this thread's halo cells of the staged tile (at most three: 384 halo
-    // cells over 256 threads), fixed for the run: LDS slot and column offset
-    constexpr int kSlots = (kSY * kSX + kFX * kFY - 1) / (kFX * kFY);
+    // this thread's halo cells of the staged tile (no corners), fixed for the
+    // run: LDS slot and column offset
+    constexpr int kHaloY = 2 * kFH * kFX, kHalo = kHaloY + 2 * kFH * kFY;
+    constexpr int kSlots = (kHalo + kFX * kFY - 1) / (kFX * kFY);
     int hslot[kSlots];
-    int hcol[kSlots];  // a plane holds fewer than 2^31 cells
+    int hcol[kSlots];
     unroll<kSlots>([&](auto i) {
         constexpr int j = decltype(i)::value;
         const int e = t + j * kFX * kFY;
-        const int r = e / kSX, c = e % kSX;
-        const bool halo = e < kSY * kSX && !(r >= kFH && r < kFH + kFY && c >= kFH && c < kFH + kFX);
-        hslot[j] = halo ? e : -1;
-        hcol[j] = halo ? wrap(bx + c - kFH, nx) + nx * wrap(by + r - kFH, ny) : 0;
-    });
-    // loads of plane z, issued one plane ahead: the halo cells and the
-    // epilogue operands psi^{n-1} and V of this thread's cell
-    float2 hv[kSlots];
-    float2 po_n = make_float2(0.f, 0.f);
-    float vv_n = 0.f;
-    auto load_plane = [&](int z) {
-        unroll<kSlots>([&](auto i) {
-            constexpr int j = decltype(i)::value;
-            if (hslot[j] >= 0) hv[j] = psi[hcol[j] + plane * z];
-        });
-        if (valid) {
-            const int64_t ad = x + (int64_t)nx * y + plane * z;
-            if constexpr (NTL) {
-                const float2_vec v = __builtin_nontemporal_load((const float2_vec*)(old + ad));
-                po_n = make_float2(v.x, v.y);
-            } else {
-                po_n = old[ad];
-            }
-            vv_n = a.v2[ad];
+        int r, c;
+        if (e < kHaloY) {
+            r = e / kFX, c = kFH + e % kFX;
+            if (r >= kFH) r += kFY;
+        } else {
+            r = kFH + (e - kHaloY) / (2 * kFH), c = (e - kHaloY) % (2 * kFH);
+            if (c >= kFH) c += kFX;
         }
-    };
-    if (z0 < z1) load_plane(z0);
-
-    for (int z = z0; z < z1; ++z) {
-        // stage plane z: the own column value and the prefetched halo
-        s[ty + kFH][tx + kFH] = q[kFH];
+        hslot[j] = e < kHalo ? r * (kSX + 1) + c : kSY * (kSX + 1) + (t & 31);  // of the padded rows; past the tile for none
+        hcol[j] = e < kHalo ? wrap(bx + c - kFH, nx) + nx * wrap(by + r - kFH, ny) : 0;
+    });
+    // loads of plane z, issued two planes ahead: the halo cells and the
+    // epilogue operands psi^{n-1} and V of its cell.  Past the run (mask 0) the
+    // first cell of the last plane stands in: a branch would cost waits.
+    float2 hv[3][kSlots], po[3];
+    float vv[3];
+    auto load_plane = [&](auto set, int z, int mask) {
+        constexpr int b = decltype(set)::value;
+        const float2* pz = psi + plane * z;
         unroll<kSlots>([&](auto i) {
             constexpr int j = decltype(i)::value;
-            if (hslot[j] >= 0) s[hslot[j] / kSX][hslot[j] % kSX] = hv[j];
+            hv[b][j] = pz[hcol[j] & mask];
         });
-        const float2 po = po_n;
-        const float vv = vv_n;
+        const int c = col & mask;
+        if constexpr (NTL) {
+            const float2_vec v = __builtin_nontemporal_load((const float2_vec*)(old + plane * z) + c);
+            po[b] = make_float2(v.x, v.y);
+        } else {
+            po[b] = (old + plane * z)[c];
+        }
+        vv[b] = (a.v2 + plane * z)[c];
+    };
+    load_plane(std::integral_constant<int, 0>{}, z0, -1);
+    load_plane(std::integral_constant<int, 1>{}, min(z0 + 1, z1 - 1), -1);
+
+    int zn = wrap(z0 + kFH + 2, nz);
+    unroll<kFZ>([&](auto i) {
+        constexpr int o = decltype(i)::value;  // the plane's place in the run
+        const int z = z0 + o;
+        if (z >= z1) return;
+        // stage plane z: the own column value and the prefetched halo
+        float2* sp = s[o & 1] + (ty + kFH) * (kSX + 1) + tx + kFH;
+        *sp = q[(o + kFH) % Q];
+        unroll<kSlots>([&](auto i) {
+            constexpr int j = decltype(i)::value;
+            s[o & 1][hslot[j]] = hv[o % 3][j];
+        });
         __syncthreads();
-        if (z + 1 < z1) load_plane(z + 1);  // in flight during this plane's arithmetic
-        const float2 qn = psi[col + plane * wrap(z + kFH + 1, nz)];
+        load_plane(std::integral_constant<int, (o + 2) % 3>{}, min(z + 2, z1 - 1), z + 2 < z1 ? -1 : 0);
+        q[(o + Q - 1) % Q] = (psi + plane * zn)[col];
+        zn = zn + 1 == nz ? 0 : zn + 1;
         if (valid) {
-            const float2 c0 = q[kFH];
+            const float2 c0 = q[(o + kFH) % Q];
             float2 k = cscale(c0, a.kc);
             unroll<kFH>([&](auto i) {
                 constexpr int l = decltype(i)::value + 1;
-                k = cadd(k, cscale(cadd(s[ty + kFH][tx + kFH - l], s[ty + kFH][tx + kFH + l]), a.k[0][l - 1]));
-                k = cadd(k, cscale(cadd(s[ty + kFH - l][tx + kFH], s[ty + kFH + l][tx + kFH]), a.k[1][l - 1]));
-                k = cadd(k, cscale(cadd(q[kFH - l], q[kFH + l]), a.k[2][l - 1]));
+                k = cadd(k, cscale(cadd(sp[-l], sp[l]), a.k[0][l - 1]));
+                k = cadd(k, cscale(cadd(sp[-l * (kSX + 1)], sp[l * (kSX + 1)]), a.k[1][l - 1]));
+                k = cadd(k, cscale(cadd(q[(o + kFH - l) % Q], q[(o + kFH + l) % Q]), a.k[2][l - 1]));
             });
-            const int64_t ad = x + (int64_t)nx * y + plane * z;
-            const float2 src = cadd(cmul(SA, a.zt[2][z]), cmul(SB, a.dz[2][z]));
-            const float2 qq = cadd(cadd(k, cscale(c0, vv)), cmul(sigma, src));
-            const float g = gxy * a.gam[2][z];
+            const float2 src = cadd(cmul(SA, s_zt[o]), cmul(SB, s_dz[o]));
+            const float2 qq = cadd(cadd(k, cscale(c0, vv[o % 3])), cmul(sigma, src));
+            const float g = gxy * s_gam[o];
             // psi^{n+1} = Gamma (psi^{n-1} - i q)
-            old[ad] = make_float2(g * (po.x + qq.y), g * (po.y - qq.x));
+            (old + plane * z)[col] = make_float2(g * (po[o % 3].x + qq.y), g * (po[o % 3].y - qq.x));
         }
-        __syncthreads();  // the plane is read before the next one is staged
-        unroll<2 * kFH>([&](auto i) {
-            constexpr int r = decltype(i)::value;
-            q[r] = q[r + 1];
-        });
-        q[2 * kFH] = qn;
-    }
+    });
 }
 
 }  // namespace
@@ -165,13 +189,24 @@ __global__ __launch_bounds__(kFX * kFY) __attribute__((amdgpu_waves_per_eu(5))) 
 const double kFdtdAlpha[5] = {-205.0 / 72.0, 8.0 / 5.0, -1.0 / 5.0, 8.0 / 315.0, -1.0 / 560.0};
 
 hipError_t launch_fdtd(const FdtdArgs& a, int koff, hipStream_t stream) {
-    const int tiles = ((a.nx + kFX - 1) / kFX) * ((a.ny + kFY - 1) / kFY) * ((a.nz + kFZ - 1) / kFZ);
     // psi pair and V: 20 B per cell
     const bool ntl = 20.0 * (double)a.nx * a.ny * a.nz > kInfinityCacheBytes;
+    const int gx = (a.nx + kFX - 1) / kFX, gy = (a.ny + 7) / 8;
+    // Four workgroups of 256 threads per CU, in one round: shorter runs start
+    // more workgroups on a small grid, longer ones load fewer planes twice.
+    // 48 x 64 x 80: 12.7 us with runs of 16, 6.85 with 3, 8.6 with 1;
+    // 98 x 134 x 150: 19.6 with 16, 17.0 with 10, 18.1 with 6; 160^3: 24.0
+    // with 16, 26.0 with 10.
+    const int run = (int)std::min<int64_t>(kFZ, std::max<int64_t>(3, ((int64_t)a.nz * gx * gy + 4 * kCUs - 1) / (4 * kCUs)));
+    // Tiles of 16 rows load fewer halo cells; where the runs are long and no
+    // row is padded for it (288^3: 145.9 against 149.7 us, 160^3: 23.5 against
+    // 24.0; 98 x 134 x 150: 21.2 against 19.6)
+    const bool tall = run == kFZ && gy % 2 == 0;
+    const dim3 grid((unsigned)(gx * (tall ? gy / 2 : gy) * ((a.nz + run - 1) / run))), block(kFX, tall ? 16 : 8);
     if (ntl)
-        hipLaunchKernelGGL(fdtd_kernel<true>, dim3((unsigned)tiles), dim3(kFX, kFY), 0, stream, a, koff);
+        hipLaunchKernelGGL((tall ? fdtd_kernel<true, 16> : fdtd_kernel<true, 8>), grid, block, 0, stream, a, run, koff);
     else
-        hipLaunchKernelGGL(fdtd_kernel<false>, dim3((unsigned)tiles), dim3(kFX, kFY), 0, stream, a, koff);
+        hipLaunchKernelGGL((tall ? fdtd_kernel<false, 16> : fdtd_kernel<false, 8>), grid, block, 0, stream, a, run, koff);
     return hipGetLastError();
 }
 
