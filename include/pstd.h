@@ -367,8 +367,8 @@ pstd_status pstd_misfit_forward(pstd_solver* s, int64_t n_steps, const double* o
 
 /* dJ/dV (float32, energy^-1 per cell times energy^2 of J: d J / d V_c in the
  * units of V, layout [k][j][i]) of the last pstd_misfit_forward.  Recomputes
- * each segment from its checkpoint and runs the adjoint steps backwards
- * (about two forward steps of work per step).  The gradient covers every
+ * each segment but the last from its checkpoint and runs the adjoint steps
+ * backwards (about two forward steps of work per step).  The gradient covers every
  * cell; pstd_set_potential accepts V only where the taper is one, so callers
  * mask the rest.  Leaves the solver in the state the forward run ended in and
  * may be called again.  Synchronises.  ESTATE: no forward run, or the solver

@@ -11,7 +11,8 @@
 // Backward, segments last to first:
 //   - restore the segment's checkpoint and recompute its states with the
 //     surface DFT switched off, each step also storing psi^{n+1} in the
-//     segment store;
+//     segment store (the last segment's are there already: the forward run
+//     stored them as it stepped);
 //   - run the adjoint steps of the segment.  With chi^m = conj(Gamma mu^m)
 //     (mu the Lagrange multipliers of the step equations) the recurrence is
 //       chi^m = Gamma (chi^{m+2} - i [A chi^{m+1} + i conj(e_m)]),
@@ -59,6 +60,10 @@ struct AdjointState {
     int* dft_adj = nullptr;              // [N] m inside the window
     const float2** fwd_adj = nullptr;    // [N] psi^{m-1}
     int64_t* ctr_adj = nullptr;
+    // graphs of kAdjGraphSteps recompute and adjoint steps, captured by the first
+    // segment long enough to replay them and kept until the solver's own goes
+    hipGraphExec_t grec = nullptr, gadj = nullptr;
+    int64_t in_store = -1;               // segment whose states the store holds
     bool valid = false;                  // a forward run matches the solver state
 };
 
@@ -79,12 +84,19 @@ pstd_status hfail(pstd_solver* s, hipError_t e, const char* what) { return pstd:
         if (_e != hipSuccess) return hfail((s), _e, #call); \
     } while (0)
 
+void drop_graphs(AdjointState* a) {
+    if (a->grec) (void)hipGraphExecDestroy(a->grec);
+    if (a->gadj) (void)hipGraphExecDestroy(a->gadj);
+    a->grec = a->gadj = nullptr;
+}
+
 void free_adjoint(AdjointState* a) {
     if (!a) return;
     void* ptrs[] = {a->ck,     a->last,   a->store,   a->chi[0], a->chi[1], a->g32,     a->g64,
                     a->obs,    a->target, a->psi_obs, a->seed,   a->J,      a->inj,     a->dft_off,
                     a->stash,  a->w_adj,  a->dft_adj, (void*)a->fwd_adj,     a->ctr_adj};
     for (void* p : ptrs) (void)hipFree(p);
+    drop_graphs(a);
     delete a;
 }
 
@@ -129,6 +141,35 @@ __global__ void set_ctr_kernel(int64_t* ctr, int64_t n, int64_t end) {
 hipError_t set_ctr(int64_t* ctr, int64_t n, int64_t end, hipStream_t stream) {
     hipLaunchKernelGGL(set_ctr_kernel, dim3(1), dim3(64), 0, stream, ctr, n, end);
     return hipGetLastError();
+}
+
+// the step tables, which N, S and the problem fix
+hipError_t upload_step_tables(const pstd_solver* s, AdjointState* a) {
+    const int64_t N = a->N, S = a->S, cells = a->cells;
+    std::vector<int> off(N, 0), on(N);
+    std::vector<float2*> stash(N, nullptr);
+    std::vector<double2> w(N);
+    std::vector<const float2*> fwd(N);
+    for (int64_t n = 0; n < N; ++n) {
+        const int64_t n0 = (n / S) * S;
+        if (n + 1 - n0 < S && n + 1 < N) stash[n] = a->store + (size_t)(n - n0) * cells;
+    }
+    for (int64_t k = 0; k < N; ++k) {
+        const int64_t m = N - k;
+        const double tau = m * s->dtau;
+        w[k] = make_double2(-std::sin(tau), std::cos(tau));  // i exp(i tau_m)
+        on[k] = (m >= s->prob.dft_begin && m < std::min<int64_t>(s->prob.dft_end, N)) ? 1 : 0;
+        const int64_t j = m - 1, seg = j / S, j0 = seg * S;
+        fwd[k] = j == j0 ? a->ck + ((size_t)seg * 2 + 1) * cells : a->store + (size_t)(j - j0 - 1) * cells;
+    }
+    hipError_t e;
+    if ((e = hipMemcpy(a->dft_off, off.data(), N * sizeof(int), hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(a->stash, stash.data(), N * sizeof(float2*), hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(a->w_adj, w.data(), N * sizeof(double2), hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(a->dft_adj, on.data(), N * sizeof(int), hipMemcpyHostToDevice)) ||
+        (e = hipMemcpy(a->fwd_adj, fwd.data(), N * sizeof(const float2*), hipMemcpyHostToDevice)))
+        return e;
+    return hipSuccess;
 }
 
 // descriptors of the recompute steps (forward passes, no surface DFT, stash)
@@ -225,12 +266,20 @@ pstd_status capture(pstd_solver* s, F&& body, hipGraphExec_t* out) {
     return PSTD_OK;
 }
 
-// `count` steps: whole graphs, then single launches
+// `count` steps: whole graphs, then single launches.  Segments shorter than a
+// graph (sqrt(n_steps) checkpoints up to 256 steps) capture none.  With both
+// graphs captured and the step tables sent by every backward call, and the last
+// segment stepped again, a misfit and its gradient took 13.1 ms, now 12.7 (96^3,
+// 128 steps); the first call of a solver 79 ms, now 21.
 template <class F>
-pstd_status run_steps(pstd_solver* s, hipGraphExec_t graph, int64_t count, F&& eager) {
+pstd_status run_steps(pstd_solver* s, hipGraphExec_t* graph, int64_t count, F&& launch) {
     int64_t left = count;
-    for (; left >= kAdjGraphSteps; left -= kAdjGraphSteps) ADJ_TRY(s, hipGraphLaunch(graph, s->stream));
-    if (left > 0) return eager((int)left);
+    if (left >= kAdjGraphSteps && !*graph) {
+        pstd_status st = capture(s, [&](hipStream_t cs) { return launch(cs, kAdjGraphSteps); }, graph);
+        if (st) return st;
+    }
+    for (; left >= kAdjGraphSteps; left -= kAdjGraphSteps) ADJ_TRY(s, hipGraphLaunch(*graph, s->stream));
+    if (left > 0) return launch(s->stream, (int)left);
     return PSTD_OK;
 }
 
@@ -245,6 +294,10 @@ namespace pstd {
 
 void adjoint_invalidate(pstd_solver* s) {
     if (s && s->adj) s->adj->valid = false;
+}
+
+void adjoint_drop_graphs(pstd_solver* s) {
+    if (s->adj) drop_graphs(s->adj);
 }
 
 void adjoint_free(pstd_solver* s) {
@@ -303,6 +356,10 @@ pstd_status pstd_misfit_forward(pstd_solver* s, int64_t n_steps, const double* o
             pstd::adjoint_free(s);
             return hfail(s, e, "hipMalloc adjoint state");
         }
+        if ((e = upload_step_tables(s, a))) {
+            pstd::adjoint_free(s);
+            return hfail(s, e, "adjoint step tables");
+        }
     }
     a->valid = false;
     ADJ_TRY(s, hipMemcpyAsync(a->obs, obs_dev, n_obs * sizeof(double3), hipMemcpyDeviceToDevice, s->stream));
@@ -321,9 +378,12 @@ pstd_status pstd_misfit_forward(pstd_solver* s, int64_t n_steps, const double* o
         float2* slot = a->ck + (size_t)k * 2 * cells;
         ADJ_TRY(s, hipMemcpyAsync(slot, s->buf[(n0 + 1) & 1], cells * sizeof(float2), hipMemcpyDeviceToDevice, s->stream));
         ADJ_TRY(s, hipMemcpyAsync(slot + cells, s->buf[n0 & 1], cells * sizeof(float2), hipMemcpyDeviceToDevice, s->stream));
-        st = pstd_run(s, std::min(S, n_steps - n0));
+        // the last segment's states go to the store as they are stepped, so
+        // the backward run need not step them again
+        st = k + 1 < nck ? pstd_run(s, S) : pstd::solver_run_stashed(s, n_steps - n0, a->stash);
         if (st) return st;
     }
+    a->in_store = nck - 1;
     ADJ_TRY(s, hipMemcpyAsync(a->last, s->buf[(n_steps + 1) & 1], cells * sizeof(float2), hipMemcpyDeviceToDevice, s->stream));
     ADJ_TRY(s, hipMemcpyAsync(a->last + cells, s->buf[n_steps & 1], cells * sizeof(float2), hipMemcpyDeviceToDevice,
                               s->stream));
@@ -353,49 +413,17 @@ pstd_status pstd_misfit_backward(pstd_solver* s, float* dJdV_dev, int64_t n_cell
                                              a->n_obs, a->seed, a->inj, s->stream, &msg);
         if (e) return msg.empty() ? hfail(s, e, "project_adjoint") : fail(s, PSTD_EINVAL, msg);
     }
-    // step tables
-    {
-        std::vector<int> off(N, 0), on(N);
-        std::vector<float2*> stash(N, nullptr);
-        std::vector<double2> w(N);
-        std::vector<const float2*> fwd(N);
-        for (int64_t n = 0; n < N; ++n) {
-            const int64_t n0 = (n / S) * S;
-            if (n + 1 - n0 < S && n + 1 < N) stash[n] = a->store + (size_t)(n - n0) * cells;
-        }
-        for (int64_t k = 0; k < N; ++k) {
-            const int64_t m = N - k;
-            const double tau = m * s->dtau;
-            w[k] = make_double2(-std::sin(tau), std::cos(tau));  // i exp(i tau_m)
-            on[k] = (m >= s->prob.dft_begin && m < std::min<int64_t>(s->prob.dft_end, N)) ? 1 : 0;
-            const int64_t j = m - 1, seg = j / S, j0 = seg * S;
-            fwd[k] = j == j0 ? a->ck + ((size_t)seg * 2 + 1) * cells : a->store + (size_t)(j - j0 - 1) * cells;
-        }
-        ADJ_TRY(s, hipStreamSynchronize(s->stream));
-        ADJ_TRY(s, hipMemcpy(a->dft_off, off.data(), N * sizeof(int), hipMemcpyHostToDevice));
-        ADJ_TRY(s, hipMemcpy(a->stash, stash.data(), N * sizeof(float2*), hipMemcpyHostToDevice));
-        ADJ_TRY(s, hipMemcpy(a->w_adj, w.data(), N * sizeof(double2), hipMemcpyHostToDevice));
-        ADJ_TRY(s, hipMemcpy(a->dft_adj, on.data(), N * sizeof(int), hipMemcpyHostToDevice));
-        ADJ_TRY(s, hipMemcpy(a->fwd_adj, fwd.data(), N * sizeof(const float2*), hipMemcpyHostToDevice));
-    }
     ADJ_TRY(s, hipMemsetAsync(a->chi[0], 0, cells * sizeof(float2), s->stream));
     ADJ_TRY(s, hipMemsetAsync(a->chi[1], 0, cells * sizeof(float2), s->stream));
     ADJ_TRY(s, hipMemsetAsync(a->g32, 0, cells * sizeof(float), s->stream));
     ADJ_TRY(s, hipMemsetAsync(a->g64, 0, cells * sizeof(double), s->stream));
-    hipGraphExec_t grec = nullptr, gadj = nullptr;
-    auto done = [&](pstd_status st) {
-        if (grec) (void)hipGraphExecDestroy(grec);
-        if (gadj) (void)hipGraphExecDestroy(gadj);
-        return st;
-    };
     pstd_status st;
-    if ((st = capture(s, [&](hipStream_t cs) { return launch_rec(s, a, cs, kAdjGraphSteps); }, &grec))) return done(st);
-    if ((st = capture(s, [&](hipStream_t cs) { return launch_adj(s, a, cs, kAdjGraphSteps); }, &gadj))) return done(st);
     for (int64_t k = a->nck - 1; k >= 0; --k) {
         const int64_t n0 = k * S, n1 = std::min(n0 + S, N);
         // states psi^{n0+1} .. psi^{n1-1} into the segment store
         const int64_t nrec = n1 - 1 - n0;
-        if (nrec > 0) {
+        if (nrec > 0 && a->in_store != k) {
+            a->in_store = -1;
             const float2* slot = a->ck + (size_t)k * 2 * cells;
             hipError_t e;
             if ((e = hipMemcpyAsync(s->buf[(n0 + 1) & 1], slot, cells * sizeof(float2), hipMemcpyDeviceToDevice,
@@ -403,29 +431,30 @@ pstd_status pstd_misfit_backward(pstd_solver* s, float* dJdV_dev, int64_t n_cell
                 (e = hipMemcpyAsync(s->buf[n0 & 1], slot + cells, cells * sizeof(float2), hipMemcpyDeviceToDevice,
                                     s->stream)) ||
                 (e = set_ctr(s->ctr, n0, n0 + nrec, s->stream)))
-                return done(hfail(s, e, "segment restore"));
-            st = run_steps(s, grec, nrec, [&](int c) { return launch_rec(s, a, s->stream, c); });
-            if (st) return done(st);
+                return hfail(s, e, "segment restore");
+            st = run_steps(s, &a->grec, nrec, [&](hipStream_t cs, int c) { return launch_rec(s, a, cs, c); });
+            if (st) return st;
+            a->in_store = k;
         }
         // adjoint steps m = n1 .. n0 + 1  (k' = N - m)
         hipError_t e = set_ctr(a->ctr_adj, N - n1, N - n0, s->stream);
-        if (e) return done(hfail(s, e, "adjoint counters"));
-        st = run_steps(s, gadj, n1 - n0, [&](int c) { return launch_adj(s, a, s->stream, c); });
-        if (st) return done(st);
+        if (e) return hfail(s, e, "adjoint counters");
+        st = run_steps(s, &a->gadj, n1 - n0, [&](hipStream_t cs, int c) { return launch_adj(s, a, cs, c); });
+        if (st) return st;
         e = pstd::launch_fold(a->g64, a->g32, cells, s->stream);
-        if (e) return done(hfail(s, e, "fold"));
+        if (e) return hfail(s, e, "fold");
     }
     hipError_t e = pstd::launch_scale_out(a->g64, 4.0 * s->dtau / s->E0, dJdV_dev, cells, s->stream);
-    if (e) return done(hfail(s, e, "gradient"));
+    if (e) return hfail(s, e, "gradient");
     // back to the state at the end of the forward run
     if ((e = hipMemcpyAsync(s->buf[(N + 1) & 1], a->last, cells * sizeof(float2), hipMemcpyDeviceToDevice, s->stream)) ||
         (e = hipMemcpyAsync(s->buf[N & 1], a->last + cells, cells * sizeof(float2), hipMemcpyDeviceToDevice,
                             s->stream)) ||
         (e = set_ctr(s->ctr, N, std::numeric_limits<int64_t>::max(), s->stream)))
-        return done(hfail(s, e, "state restore"));
+        return hfail(s, e, "state restore");
     e = hipStreamSynchronize(s->stream);
-    if (e) return done(hfail(s, e, "backward"));
-    return done(PSTD_OK);
+    if (e) return hfail(s, e, "backward");
+    return PSTD_OK;
 }
 
 }  // extern "C"

@@ -401,7 +401,8 @@ pstd::FdtdArgs fdtd_args(const pstd_solver* s) {
     return a;
 }
 
-pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int count, hipEvent_t* ev) {
+pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int count, hipEvent_t* ev,
+                          float2* const* stash = nullptr) {
     if (s->pulse) {
         // the packet's table of the next step, this step's layer source (into
         // psi^{n-1}, before the z pass), and psi^n on the shell into the
@@ -439,6 +440,7 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
     auto args_of = [&](int axis, pstd::PassArgs& a) {
         pstd::solver_args(s, axis, a);
         if (stage) a.bstage = s->bring[axis];
+        a.stash_tab = stash;
     };
     if (xy) {
         // the x and y passes in one launch; its time goes to the x slot of the timers
@@ -495,9 +497,10 @@ void ensure_box_ring(pstd_solver* s) {
 }
 
 // `count` consecutive steps, then one counter advance
-pstd_status launch_steps(pstd_solver* s, hipStream_t stream, int count, hipEvent_t* ev) {
+pstd_status launch_steps(pstd_solver* s, hipStream_t stream, int count, hipEvent_t* ev,
+                         float2* const* stash = nullptr) {
     for (int k = 0; k < count; ++k) {
-        pstd_status st = launch_passes(s, stream, k, count, ev);
+        pstd_status st = launch_passes(s, stream, k, count, ev, stash);
         if (st) return st;
     }
     hipError_t e = pstd::launch_advance(s->ctr, 1, count, stream);
@@ -641,9 +644,21 @@ void solver_account_steps(pstd_solver* s, int64_t from, int64_t to) {
     }
 }
 
+pstd_status solver_run_stashed(pstd_solver* s, int64_t n_steps, float2* const* stash) {
+    pstd_status st = solver_ensure_tables(s, s->step + n_steps);
+    if (st) return st;
+    if (n_steps >= kStageMin) ensure_box_ring(s);
+    for (int64_t left = n_steps; left > 0; left -= kGraphSteps)
+        if ((st = launch_steps(s, s->stream, (int)std::min<int64_t>(left, kGraphSteps), nullptr, stash))) return st;
+    solver_account_steps(s, s->step, s->step + n_steps);
+    s->step += n_steps;
+    return PSTD_OK;
+}
+
 void solver_drop_graph(pstd_solver* s) {
     if (s->graph) (void)hipGraphExecDestroy(s->graph);
     s->graph = nullptr;
+    adjoint_drop_graphs(s);
 }
 
 pstd_status solver_create(const pstd_problem* p, hipStream_t stream, int64_t* ext_ctr, pstd_solver** out) {

@@ -91,6 +91,9 @@ inline bool solver_xy(const pstd_solver* s) { return s->L2 && s->variant[0] == s
 // the misfit forward run no longer matches the solver state
 void adjoint_invalidate(pstd_solver* s);
 void adjoint_free(pstd_solver* s);
+void adjoint_drop_graphs(pstd_solver* s);
+// n_steps steps as pstd_run, each also storing psi^{n+1} at stash[n] unless that is null
+pstd_status solver_run_stashed(pstd_solver* s, int64_t n_steps, float2* const* stash);
 // taper factor of axis a at index i with its first and second derivatives
 // in the reduced coordinate (Eq. zeta_y)
 void solver_taper(const pstd_problem& p, int a, double dxb, int i, double* z, double* z1, double* z2);
