@@ -133,10 +133,13 @@ bool seg_xy_block(int N, int core);
 hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream);
 // The largest fields (psi pair, L and L2, 32 B per cell) whose x and y passes
 // run in one launch: the array more has to stay in the Infinity Cache.
-// Measured, separate passes against one launch: 160 x 160 x 192 (157 MB) 69.0 and
-// 61.5 us per step, 180^3 (187 MB) 81.5 and 75.8, 192^3 (226 MB) 90.6 and
-// 102.1, 256^3 (537 MB) 224 and 229.
-constexpr double kXyLaunchBytes = 200e6;
+// Measured, separate passes against one launch, us per step: 160^3 (131 MB) 56.6
+// and 51.4, 180^3 (187) 79.9 and 74.5, 256 x 256 x 100 (210) 83.4 and 73.2, with
+// a box surface 160 x 160 x 256 (210) 91 and 84, 192 x 192 x 180 (212) 91.7 and
+// 87.9; 192^3 (226) 89.3 and 83.9, but with a box surface 96.8 and 96.6 and with a
+// complex absorber 94.5 and 92 in one process, 104 in another; 256 x 256 x 128
+// (268) 103 and 115, 256^3 (537) 223 and 251.
+constexpr double kXyLaunchBytes = 215e6;
 // Adjoint step pass (plain pencils, one instance)
 hipError_t launch_variant_adjoint(int v, int axis, const PassArgs& args, int koff, hipStream_t stream);
 // acc64[i] += acc32[i]; acc32[i] = 0

@@ -862,9 +862,10 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_kernel(PassArgs 
 // pencils): x tiles and y tiles of the same planes by turns, so that loads,
 // transforms and stores of tiles at different stages overlap and psi^n is
 // read beyond the L2 once (24 instead of 40 B per cell of the two passes, 8 B
-// more in the z pass).  160^3: 23.2 us against 14.0 + 16.8 us and a launch
-// between them, z pass 22.8 -> 28.0 us, step 59.3 -> 52.7 us; 48^3: 16.1 ->
-// 12.4 us.
+// more in the z pass).  160^3: 21.6 us against 13.9 + 16.8 us and a launch
+// between them, z pass 22.4 -> 25.7 us, step 56.6 -> 51.4 us; 48^3: 15.9 ->
+// 12.0 us.  Bound by the vector instructions (66 per value, about 14 us of it at
+// 160^3) and the 101 MB (14 us) next to each other.
 template <int N, int N1, int N2, int M1, int P, bool ADJ>
 __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_xy_kernel(PassArgs ax, PassArgs ay, int koff) {
     PSTD_TILE_LDS(N, N1, N2, P)
