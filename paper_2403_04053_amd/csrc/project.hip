@@ -347,13 +347,17 @@ struct FarArgs {
 // sum_jk C_jk T_j(r_c) T_k(r_b) of one axis's two faces for 16 directions per
 // wave: the sum over k is a product of [16 directions x Kb] by [Kb x 16 j] for
 // each of the eight numbers (side, field, re/im) on the FP64 matrix cores,
-// T_k advancing by four k per step as a rotation in the lane that feeds it; the sum over j is taken from the accumulators with the
-// faces' phases.  grid.y = axis * jsplit + part: few directions split the j
-// tiles; row y of part receives the sums.  Bound by the matrix cores (three
-// axes of about 92 x 96 coefficients: 65160 directions in 560 us, 0.35 ms of it
-// at their full rate; 3 waves per SIMD although 22 registers spill, 790 us at 2).
-// The former path, a complex product per 8192 directions and face with the
-// factors themselves, took 7.3 ms in all.
+// T_k advancing by four k per step as a rotation in the lane that feeds it; the
+// sum over j is taken from the accumulators with the faces' phases.  grid.y = axis
+// * jsplit + part: few directions split the j tiles; row y of part receives the
+// sums.  Bound by the matrix cores (three axes of about 92 x 96 coefficients: 65160
+// directions in 545 us, 0.35 ms of it at their full rate; 3 waves per SIMD although
+// 11 registers spill, 790 us at 2; 32 directions per wave, half the coefficient
+// loads, at 2 waves without spills 583 against 587 us per call) and by what a wave
+// computes first: with a direction's angle, rotation and phase in one lane instead
+// of sixteen a call takes 571 instead of 587 us, 64^3 planes 260 instead of 278.  The
+// former path, a complex product per 8192 directions and face with the factors
+// themselves, took 7.3 ms in all.
 constexpr int kFarWaves = 4;
 
 // cos(k (pi/2 - a)) = T_k(sin a) and its companion -sin(k (pi/2 - a)) in *sn,
@@ -390,22 +394,28 @@ __global__ __launch_bounds__(64 * kFarWaves, 3) void far_eval_kernel(const doubl
     const int tiles = ev.Kcp / 16, per = (tiles + f.jsplit - 1) / f.jsplit;
     const int t0 = js * per, t1 = min(tiles, t0 + per);
     double tc[4], ts[4], c16[4], s16[4], ra[4], orr[4], oi[4];
-    double2 wlo[4], whi[4];
+    double2 w[4];
+    {
+        // a direction's angle, rotation and phase in one lane of each row of 16,
+        // handed to the lanes that receive it
+        const double3 v = dirs[min(d0 + li, nd - 1)];
+        const double t = angle(comp(v, c)), rn = comp(v, a);
+        double sn, cs, sr, cr, err;
+        sincos(16.0 * t, &sr, &cr);
+        const double ph = two_product(rn, ev.half, &err);
+        sincos_sum(ph, fma(rn, ev.half_err, err), &sn, &cs);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const double3 v = dirs[min(d0 + 4 * r + lk, nd - 1)];
-        const double t = angle(comp(v, c));
-        cheb_start(16 * t0 + li, t, &ts[r], &tc[r]);
-        sincos(16.0 * t, &s16[r], &c16[r]);
-        ra[r] = comp(v, a);
-        double sn, cs;
-        double err;
-        const double ph = two_product(ra[r], ev.half, &err);
-        sincos_sum(ph, fma(ra[r], ev.half_err, err), &sn, &cs);
-        wlo[r] = make_double2(ev.pref * cs, ev.pref * sn);    // exp(+i ra half), low face
-        whi[r] = make_double2(-ev.pref * cs, ev.pref * sn);   // -exp(-i ra half)
-        orr[r] = 0;
-        oi[r] = 0;
+        for (int r = 0; r < 4; ++r) {
+            const int from = 4 * r + lk;
+            cheb_start(16 * t0 + li, __shfl(t, from, 64), &ts[r], &tc[r]);
+            c16[r] = __shfl(cr, from, 64);
+            s16[r] = __shfl(sr, from, 64);
+            ra[r] = __shfl(rn, from, 64);
+            // pref exp(i ra half) of the low face; the high face's is -conj of it
+            w[r] = make_double2(ev.pref * __shfl(cs, from, 64), ev.pref * __shfl(sn, from, 64));
+            orr[r] = 0;
+            oi[r] = 0;
+        }
     }
     for (int tile = t0; tile < t1; ++tile) {
         v4d acc[8];
@@ -413,16 +423,10 @@ __global__ __launch_bounds__(64 * kFarWaves, 3) void far_eval_kernel(const doubl
         for (int q = 0; q < 8; ++q) acc[q] = v4d{0, 0, 0, 0};
         const double2* __restrict__ cf = reinterpret_cast<const double2*>(ev.coef) + ((int64_t)lk * ev.Kcp + tile * 16 + li) * 4;
         double cc = c0, ss = s0;
-        // the coefficients of a step are loaded one step ahead (the last step
-        // loads its own again)
-        double2 n0 = cf[0], n1 = cf[1], n2 = cf[2], n3 = cf[3];
         for (int k = 0; k < ev.Kbp; k += 4) {
-            const double2 x0 = n0, x1 = n1, x2 = n2, x3 = n3;
-            if (k + 4 < ev.Kbp) cf += (int64_t)16 * ev.Kcp;
-            n0 = cf[0];
-            n1 = cf[1];
-            n2 = cf[2];
-            n3 = cf[3];
+            // (loaded a step ahead by force: 595 instead of 587 us)
+            const double2 x0 = cf[0], x1 = cf[1], x2 = cf[2], x3 = cf[3];
+            cf += (int64_t)16 * ev.Kcp;
             acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x0.x, acc[0], 0, 0, 0);
             acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x0.y, acc[1], 0, 0, 0);
             acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(cc, x1.x, acc[2], 0, 0, 0);
@@ -440,8 +444,8 @@ __global__ __launch_bounds__(64 * kFarWaves, 3) void far_eval_kernel(const doubl
             // dpsi + i r_a psi of the low and the high face
             const double lr = acc[2][r] - ra[r] * acc[1][r], lm = acc[3][r] + ra[r] * acc[0][r];
             const double hr = acc[6][r] - ra[r] * acc[5][r], hm = acc[7][r] + ra[r] * acc[4][r];
-            orr[r] += tc[r] * (wlo[r].x * lr - wlo[r].y * lm + whi[r].x * hr - whi[r].y * hm);
-            oi[r] += tc[r] * (wlo[r].x * lm + wlo[r].y * lr + whi[r].x * hm + whi[r].y * hr);
+            orr[r] += tc[r] * (w[r].x * (lr - hr) - w[r].y * (lm + hm));
+            oi[r] += tc[r] * (w[r].x * (lm - hm) + w[r].y * (lr + hr));
             const double cn = tc[r] * c16[r] - ts[r] * s16[r];
             ts[r] = tc[r] * s16[r] + ts[r] * c16[r];
             tc[r] = cn;
