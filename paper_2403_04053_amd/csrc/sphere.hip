@@ -338,8 +338,7 @@ __global__ __launch_bounds__(kSumThreads) void sphere_sum_kernel(const double2* 
 }
 
 // out = scale times the rows of part, added in order
-__global__ void sphere_add_kernel(const double2* __restrict__ part, int rows, int64_t n, double scale,
-                                  double2* __restrict__ out) {
+__global__ void sphere_add_kernel(const double2* part, int rows, int64_t n, double scale, double2* out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double2 s = part[i];
@@ -371,26 +370,36 @@ hipError_t sphere_sums(pstd_solver* s, double kw, const double3* where, int64_t 
     const int64_t bx = (n + K * kSumThreads - 1) / (K * kSumThreads);
     const int chunks = (sp->n_nodes + kNodeChunk - 1) / kNodeChunk;
     const int64_t want = (2048 + bx - 1) / bx;
-    const int per = (int)((chunks + std::min<int64_t>(chunks, want) - 1) / std::min<int64_t>(chunks, want)) * kNodeChunk;
-    const int rows = (sp->n_nodes + per - 1) / per;
+    int per = (int)((chunks + std::min<int64_t>(chunks, want) - 1) / std::min<int64_t>(chunks, want)) * kNodeChunk;
+    int rows = (sp->n_nodes + per - 1) / per;
     const size_t need = (size_t)rows * n * sizeof(double2);
-    if (sp->part_bytes < need) {
-        (void)hipStreamSynchronize(stream);  // queued sums may still use the old buffer
-        (void)hipFree(sp->part);
-        sp->part = nullptr;
-        sp->part_bytes = 0;
-        const hipError_t e = hipMalloc(&sp->part, need);
-        if (e) return e;
-        sp->part_bytes = need;
+    if (rows > 1) {
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        const bool eager = hipStreamIsCapturing(stream, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone;
+        if (eager && sp->part_bytes < need) {
+            (void)hipStreamSynchronize(stream);  // queued sums may still use the old buffer
+            (void)hipFree(sp->part);
+            sp->part = nullptr;
+            sp->part_bytes = hipMalloc(&sp->part, need) == hipSuccess ? need : 0;
+            if (!sp->part_bytes) (void)hipGetLastError();
+        }
+        // without room, or where a caller's graph would keep the buffer's address,
+        // the nodes in one row
+        if (!eager || sp->part_bytes < need) {
+            per = chunks * kNodeChunk;
+            rows = 1;
+        }
     }
+    // one row is summed in the outputs themselves
+    double2* part = rows > 1 ? sp->part : out;
     const dim3 grid((unsigned)bx, (unsigned)rows);
     if (K == 2)
         hipLaunchKernelGGL((sphere_sum_kernel<FAR, 2>), grid, dim3(kSumThreads), 0, stream, sp->pack, sp->n_nodes, per,
-                           sp->R, kw, where, n, s->prob.k0, sp->part);
+                           sp->R, kw, where, n, s->prob.k0, part);
     else
         hipLaunchKernelGGL((sphere_sum_kernel<FAR, 1>), grid, dim3(kSumThreads), 0, stream, sp->pack, sp->n_nodes, per,
-                           sp->R, kw, where, n, s->prob.k0, sp->part);
-    hipLaunchKernelGGL(sphere_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, sp->part, rows, n,
+                           sp->R, kw, where, n, s->prob.k0, part);
+    hipLaunchKernelGGL(sphere_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, part, rows, n,
                        scale, out);
     return hipGetLastError();
 }
