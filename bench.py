@@ -60,8 +60,8 @@ KERNEL_SOURCES = ("paper_2403_04053_amd/csrc/pass_kernel.hpp", "paper_2403_04053
 # The shell DFT of the spherical surface (r = 5, 64 x 128 nodes) on the same
 # workload, per launch of a pair of steps, valid for the sphere sources whose
 # SHA-256 is SHELL_TRAFFIC_SRC_SHA256.
-SHELL_TRAFFIC_SRC_SHA256 = "5672ff86e938ce49280ffa906cd3727df5642cbe3b50d9a855bc0339d203e1e8"
-SHELL_TRAFFIC_KIB = (16015, 5252)
+SHELL_TRAFFIC_SRC_SHA256 = "a5d7df5852590cfea0700be3e86e8917e3838de7030a6d1064a326413461f754"
+SHELL_TRAFFIC_KIB = (11305, 5252)
 SHELL_SOURCES = ("paper_2403_04053_amd/csrc/sphere.hip",)
 
 # The same for the FDTD kernel on the 160^3 grid (key: grid edge), valid for
