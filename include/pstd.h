@@ -280,7 +280,9 @@ pstd_status pstd_project(pstd_solver* s, const double* obs_xyz_dev, int64_t n_ob
  * for n_dir unit directions (double[3] each): the cell formula in the limit
  * of Eq. FDTDfarfieldapprox (with surface_kind 1, the limit of the sphere's
  * Kirchhoff sum).  Output complex128.  n_dir = 0 does nothing and returns
- * PSTD_OK (the pointers may then be null). */
+ * PSTD_OK (the pointers may then be null).  A caller may capture it (any
+ * number of directions) once pstd_far_field or pstd_project has run; with the
+ * box surface a capture before that is refused with EHIP and stays whole. */
 pstd_status pstd_far_field(pstd_solver* s, const double* dir_dev, int64_t n_dir, double* f_out_dev);
 
 /*

@@ -482,9 +482,7 @@ void ensure_box_ring(pstd_solver* s) {
     if (s->bring[0] || s->no_ring || s->pulse || s->in_batch || s->prob.surface_kind != 0 || s->prob.scheme != 0 ||
         s->prob.dft_end <= s->prob.dft_begin)
         return;
-    // (nothing can be allocated while a caller captures the stream)
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s->stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return;
+    if (pstd::stream_capturing(s->stream)) return;
     size_t total = 0, off[3];
     for (int a = 0; a < 3; ++a) {
         off[a] = total;

@@ -150,6 +150,14 @@ int norm_scratch_doubles();
 hipError_t launch_norm(const float2* psi, int64_t n, double* scratch, hipStream_t stream);
 // out[i] = (float)(scale * acc64[i])
 hipError_t launch_scale_out(const double* acc64, double scale, float* out, int64_t n, hipStream_t stream);
+// Whether a caller captures the stream (or that cannot be told): nothing can be
+// allocated, freed or waited for then
+inline bool stream_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
 // advance the step counters of count instances by `by` steps, never past
 // their end (ctr[2i] = step, ctr[2i+1] = end)
 hipError_t launch_advance(int64_t* ctr, int count, int by, hipStream_t stream);

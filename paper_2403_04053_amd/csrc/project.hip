@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "fp64_math.hpp"
+#include "internal.hpp"
 #include "project.hpp"
 
 namespace pstd {
@@ -1044,7 +1045,7 @@ struct ProjectState {
     double2* phasors = nullptr;   // [face][2][plane]
     double2* work = nullptr;      // scratch
     size_t work_bytes = 0;
-    double2* part = nullptr;      // per-split partial sums of the point and direction kernels
+    double2* part = nullptr;      // per-split partial sums of the point kernels
     size_t part_bytes = 0;
     double2* low = nullptr;       // adjoint: the splits' sums
     size_t low_bytes = 0;
@@ -1054,9 +1055,14 @@ struct ProjectState {
     double2* near_tab = nullptr;  // per axis [t][cell][N]: sinc-Taylor expansion of the cell integral
     double* econ = nullptr;       // economisation table
     double2* far_tab = nullptr;   // per axis [K][N]: Chebyshev coefficients of the far factor
+    // the far field's scratch, of one size for any number of directions and its own,
+    // so that a far field captured by a caller finds it and no later call moves it
+    double2* far_work = nullptr;  // coefficients, products, far_wide_kernel's values
+    double2* far_part = nullptr;  // [rows][direction]: far_eval_kernel's sums
     int64_t near_off[4] = {0, 0, 0, 0};
     int64_t far_off[4] = {0, 0, 0, 0};
     int K[3] = {0, 0, 0};
+    int64_t coef_off[4] = {0, 0, 0, 0}, far_y = 0, far_c = 0, far_wide = 0;  // in far_work
     int64_t face_off[7] = {0, 0, 0, 0, 0, 0, 0};
     int64_t total = 0;
 };
@@ -1201,8 +1207,18 @@ hipError_t near_tables(ProjectState* s, const pstd_problem& p, hipStream_t strea
     return hipSuccess;
 }
 
+// Directions of one launch, and the values of far_part: rows of a launch are 3
+// jsplit, jsplit at most the waves that 2048 lack, so rows times directions stay
+// under 3 kFarChunk + 2048 * 16
+constexpr int64_t kFarChunk = 1 << 16;
+constexpr int64_t kFarPart = 3 * kFarChunk + 2048 * 16;
+
+int far_kbp(const ProjectState* s, int a) { return (s->K[face_axis_b(a)] + 3) / 4 * 4; }
+int far_kcp(const ProjectState* s, int a) { return (s->K[face_axis_c(a)] + 15) / 16 * 16; }
+
 // The far tables of the three axes: per axis [K][N], the Chebyshev
-// coefficients of the centred factor with the transform folded in (D G W)
+// coefficients of the centred factor with the transform folded in (D G W); and
+// the far field's scratch.  Allocates on the first call only.
 hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3], hipStream_t stream) {
     if (s->far_tab) return hipSuccess;
     int64_t total = 0;
@@ -1213,10 +1229,28 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
         total += K * N;
         work = std::max(work, (size_t)(2 * K * N + K * K + N * N) * sizeof(double2));
     }
+    s->far_y = s->far_c = 0;
+    for (int a = 0; a < 3; ++a) {
+        const int b = face_axis_b(a), c = face_axis_c(a);
+        s->coef_off[a + 1] = s->coef_off[a] + (int64_t)far_kbp(s, a) * far_kcp(s, a) * 4;
+        s->far_y = std::max(s->far_y, (int64_t)4 * p.n[c] * s->K[b]);
+        s->far_c = std::max(s->far_c, (int64_t)4 * s->K[c] * s->K[b]);
+    }
+    s->far_wide = (int64_t)kWideGroups * 2 * ((int64_t)p.n[0] + p.n[1] + p.n[2]);
     TRY(ensure(&s->work, &s->work_bytes, work));
-    double2* tab = nullptr;
-    TRY(hipMalloc(&tab, (size_t)total * sizeof(double2)));
-    hipError_t e = hipSuccess;
+    double2 *tab = nullptr, *fwork = nullptr, *part = nullptr;
+    auto undo = [&](hipError_t e) {
+        (void)hipStreamSynchronize(stream);
+        (void)hipFree(tab);
+        (void)hipFree(fwork);
+        (void)hipFree(part);
+        return e;
+    };
+    hipError_t e;
+    if ((e = hipMalloc(&tab, (size_t)total * sizeof(double2))) ||
+        (e = hipMalloc(&fwork, (size_t)(s->coef_off[3] + s->far_y + s->far_c + s->far_wide) * sizeof(double2))) ||
+        (e = hipMalloc(&part, (size_t)kFarPart * sizeof(double2))))
+        return undo(e);
     for (int a = 0; a < 3 && !e; ++a) {
         const int N = p.n[a], K = s->K[a];
         double2* G = s->work;
@@ -1230,11 +1264,9 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
         e = zgemm(K, N, K, ZOp{D, K}, ZOp{G, N}, DG, N, 0, 0, 1, 1, {}, stream);
         if (!e) e = zgemm(K, N, N, ZOp{DG, N}, ZOp{W, N}, tab + s->far_off[a], N, 0, 0, 1, 1, {}, stream);
     }
-    if (e) {
-        (void)hipStreamSynchronize(stream);
-        (void)hipFree(tab);
-        return e;
-    }
+    if (e) return undo(e);
+    s->far_work = fwork;
+    s->far_part = part;
     s->far_tab = tab;
     return hipSuccess;
 }
@@ -1287,28 +1319,23 @@ hipError_t check_points(ProjectState* s, const pstd_problem& p, const double dxb
 hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb[3], double2* const acc[3],
                      const int64_t points[3], PhasorScale scale, const double3* dirs, int64_t n_dir, double2* out,
                      hipStream_t stream, std::string* msg) {
+    // a caller's capture allows no allocation: refused before anything is done,
+    // unless an earlier call (far field or points) has made the tables
+    if (stream_capturing(stream) && !(*pst && (*pst)->far_tab)) return hipErrorStreamCaptureUnsupported;
     TRY(prepare(pst, p, acc, points, scale, stream));
     ProjectState* s = *pst;
     TRY(far_tables(s, p, dxb, stream));
     // coefficients of every axis's two faces: C = B_c P B_b^T
-    const int64_t Ns = (int64_t)p.n[0] + p.n[1] + p.n[2];
-    int64_t coef_off[4] = {0}, ybytes = 0, cbytes = 0;
+    const int64_t* coef_off = s->coef_off;
     int Kbp[3], Kcp[3];
     for (int a = 0; a < 3; ++a) {
-        const int b = face_axis_b(a), c = face_axis_c(a);
-        Kbp[a] = (s->K[b] + 3) / 4 * 4;
-        Kcp[a] = (s->K[c] + 15) / 16 * 16;
-        coef_off[a + 1] = coef_off[a] + (int64_t)Kbp[a] * Kcp[a] * 4;
-        ybytes = std::max(ybytes, (int64_t)4 * p.n[c] * s->K[b]);
-        cbytes = std::max(cbytes, (int64_t)4 * s->K[c] * s->K[b]);
+        Kbp[a] = far_kbp(s, a);
+        Kcp[a] = far_kcp(s, a);
     }
-    const int64_t chunk = 1 << 20;  // directions of one launch: bounds the rows of part
-    const int64_t wide = (int64_t)kWideGroups * 2 * Ns;
-    TRY(ensure(&s->work, &s->work_bytes, (size_t)(coef_off[3] + ybytes + cbytes + wide) * sizeof(double2)));
-    double2* coef = s->work;
+    double2* coef = s->far_work;
     double2* Y = coef + coef_off[3];
-    double2* C = Y + ybytes;
-    double2* scratch = C + cbytes;
+    double2* C = Y + s->far_y;
+    double2* scratch = C + s->far_c;
     FarArgs args{};
     FarWide fw{};
     fw.planes = s->phasors;
@@ -1331,18 +1358,18 @@ hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb
                              std::fma(0.5 * dxb[a], p.surf_hi[a] - p.surf_lo[a], -fw.ax[a].half), fw.pref[a]};
         mid[a] = fw.ax[a].mid;
     }
-    for (int64_t d0 = 0; d0 < n_dir; d0 += chunk) {
-        const int64_t nd = std::min(chunk, n_dir - d0);
+    for (int64_t d0 = 0; d0 < n_dir; d0 += kFarChunk) {
+        const int64_t nd = std::min(kFarChunk, n_dir - d0);
         // j tiles split until there are two waves per SIMD
         const int64_t waves = 3 * ((nd + 15) / 16);
         const int tiles = std::min(std::min(Kcp[0], Kcp[1]), Kcp[2]) / 16;
         args.jsplit = (int)std::max<int64_t>(1, std::min<int64_t>(tiles, (2048 + waves - 1) / waves));
         const int rows = 3 * args.jsplit;
-        TRY(ensure(&s->part, &s->part_bytes, (size_t)rows * nd * sizeof(double2)));
+        if (rows * nd > kFarPart) return hipErrorInvalidValue;
         hipLaunchKernelGGL(far_eval_kernel, dim3(blocks_of(nd, 16 * kFarWaves), rows), dim3(64 * kFarWaves), 0, stream,
-                           dirs + d0, nd, args, s->part);
+                           dirs + d0, nd, args, s->far_part);
         hipLaunchKernelGGL(far_sum_kernel, dim3(blocks_of(nd)), dim3(256), 0, stream, dirs + d0, nd,
-                           make_double3(mid[0], mid[1], mid[2]), s->part, rows, out + d0);
+                           make_double3(mid[0], mid[1], mid[2]), s->far_part, rows, out + d0);
         hipLaunchKernelGGL(far_wide_kernel, dim3(std::min<unsigned>(kWideGroups, blocks_of(nd))), dim3(256), 0, stream,
                            dirs + d0, nd, fw, scratch, out + d0);
     }
@@ -1362,6 +1389,8 @@ hipError_t project_points(ProjectState** pst, const pstd_problem& p, const doubl
         return hipErrorInvalidValue;
     }
     TRY(near_tables(s, p, stream));
+    // a far field can be captured from here on (without memory for it, not)
+    if (far_tables(s, p, dxb, stream)) (void)hipGetLastError();
     for (int f = 0; f < 6; ++f) {
         const FaceGeo g = face_geo(p, dxb, f);
         const int Nb = p.n[g.b], Nc = p.n[g.c], L = g.L, M = g.M;
@@ -1453,7 +1482,8 @@ hipError_t project_adjoint(ProjectState** pst, const pstd_problem& p, const doub
 
 void project_free(ProjectState* s) {
     if (!s) return;
-    void* ptrs[] = {s->phasors, s->work, s->part, s->low, s->flags, s->near_tab, s->econ, s->far_tab};
+    void* ptrs[] = {s->phasors, s->work, s->part, s->low, s->flags, s->near_tab, s->econ, s->far_tab,
+                    s->far_work, s->far_part};
     for (void* q : ptrs) (void)hipFree(q);
     delete s;
 }

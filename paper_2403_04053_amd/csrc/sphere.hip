@@ -374,8 +374,7 @@ hipError_t sphere_sums(pstd_solver* s, double kw, const double3* where, int64_t 
     int rows = (sp->n_nodes + per - 1) / per;
     const size_t need = (size_t)rows * n * sizeof(double2);
     if (rows > 1) {
-        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-        const bool eager = hipStreamIsCapturing(stream, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone;
+        const bool eager = !stream_capturing(stream);
         if (eager && sp->part_bytes < need) {
             (void)hipStreamSynchronize(stream);  // queued sums may still use the old buffer
             (void)hipFree(sp->part);
