@@ -308,6 +308,15 @@ __device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ p, int
     }
 }
 
+// Entry of a per-element table (length N) for element n1 of a thread.  In the y
+// and z passes threads idle in stage A, where N1 > N2, count on past n2 = N2 - 1:
+// they take the last entry instead of one past the table.
+template <int N, int N1, int N2>
+__host__ __device__ constexpr int row_entry(int n2, int n1) {
+    const int e = n2 + N2 * n1;
+    return N1 > N2 && e > N - 1 ? N - 1 : e;
+}
+
 // LDS layout of one tile of P pencils
 template <int N, int N1, int N2>
 struct TileLds {
@@ -475,7 +484,7 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
             float2 ny = make_float2(0.f, 0.f);  // sum of (-1)^e v_e
             unroll<N1>([&](auto i) {
                 constexpr int n1 = decltype(i)::value;
-                const float2 r = drow(n2 + N2 * n1);
+                const float2 r = drow(row_entry<N, N1, N2>(n2, n1));
                 dlo = make_float2(fmaf(r.x, v[n1].x, dlo.x), fmaf(r.x, v[n1].y, dlo.y));
                 dhi = make_float2(fmaf(r.y, v[n1].x, dhi.x), fmaf(r.y, v[n1].y, dhi.y));
                 if constexpr (alt(n1) > 0) ny = cadd(ny, v[n1]);
@@ -627,7 +636,7 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
                 unroll<N1>([&](auto i) {
                     constexpr int n1 = decltype(i)::value;
                     const int e = n2 + N2 * n1;
-                    const float2 r = drow(e);
+                    const float2 r = drow(row_entry<N, N1, N2>(n2, n1));
                     float2 x = make_float2(fmaf(r.x, hdl.x, r.y * hdh.x), fmaf(r.x, hdl.y, r.y * hdh.y));
                     if constexpr (alt(n1) > 0) x = cadd(x, hn);
                     else x = csub(x, hn);

@@ -27,3 +27,12 @@ def program(tmp_path_factory):
 def test_host_code(program, what):
     p = subprocess.run([program, what], capture_output=True, text=True, timeout=120)
     assert p.returncode == 0, p.stdout[-4000:] + p.stderr[-2000:]
+
+
+def test_row_entries_of_every_tile_shape(tmp_path):
+    exe = str(tmp_path / "row_entries")
+    subprocess.run(["hipcc", "-std=c++17", "--offload-host-only", "-I",
+                    os.path.join(ROOT, "paper_2403_04053_amd", "csrc"), os.path.join(HERE, "host", "row_entries.hip"),
+                    "-o", exe], check=True, env=dict(os.environ, TMPDIR=str(tmp_path)))
+    p = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, p.stdout
