@@ -85,14 +85,14 @@ pstd_status bhip(pstd_batch* b, hipError_t e, const char* what) {
         if (_e != hipSuccess) return bhip((b), _e, #call);   \
     } while (0)
 
-void free_groups(pstd_batch* b) {
-    for (Set& set : b->sets)
+void free_groups(std::vector<Set>& sets) {
+    for (Set& set : sets)
         for (auto& gs : set.groups)
             for (auto& g : gs) {
                 (void)hipFree(g.d_desc);
                 (void)hipFree(g.d_off);
             }
-    b->sets.clear();
+    sets.clear();
 }
 
 void drop_graph(pstd_batch* b) {
@@ -138,23 +138,23 @@ pstd_status build_set(pstd_batch* b, Set& set) {
 }
 
 // (re)build the sets and their per-axis launch groups from the instances'
-// current tile shapes and tables
+// current tile shapes and tables.  The old ones go when the new ones are whole: a
+// failure leaves them and their table generations, so that a run that needs new
+// ones builds them again.
 pstd_status build_groups(pstd_batch* b) {
     BHIP_TRY(b, hipStreamSynchronize(b->stream));
-    drop_graph(b);  // the graph holds the old descriptor buffers
-    free_groups(b);
-    b->gen.resize(b->inst.size());
+    std::vector<Set> sets;
+    std::vector<int> gen(b->inst.size());
     // non-temporal z-pass loads when an instance alone outgrows the Infinity
     // Cache (as for a single solve); for many instances that each fit, the
     // hint measured slower (64 instances of 96-192 per axis: 59.0 -> 57.6
     // Gcell/s)
     double largest = 0;
     for (size_t i = 0; i < b->inst.size(); ++i) {
-        b->gen[i] = b->inst[i]->tab_gen;
+        gen[i] = b->inst[i]->tab_gen;
         const pstd_problem& p = b->inst[i]->prob;
         largest = std::max(largest, 24.0 * p.n[0] * p.n[1] * p.n[2]);
     }
-    b->nt = largest > pstd::kInfinityCacheBytes ? 1 : 0;
     // sets: instances of like shape next to each other (so that a set's launches
     // are few), each set filled to its share of the cache; largest sets first
     // onto the branch with the least work
@@ -168,23 +168,31 @@ pstd_status build_groups(pstd_batch* b) {
     for (int i : order) {
         const double size = 24.0 * (double)b->inst[i]->cells;
         if (bytes.empty() || bytes.back() + size > kSetBytes) {
-            b->sets.emplace_back();
+            sets.emplace_back();
             bytes.push_back(0);
         }
-        b->sets.back().members.push_back(i);
+        sets.back().members.push_back(i);
         bytes.back() += size;
     }
     double load[kBranches] = {};
-    std::vector<int> by(b->sets.size());
+    std::vector<int> by(sets.size());
     for (size_t i = 0; i < by.size(); ++i) by[i] = (int)i;
     std::stable_sort(by.begin(), by.end(), [&](int x, int y) { return bytes[x] > bytes[y]; });
     for (int i : by) {
         const int k = (int)(std::min_element(load, load + kBranches) - load);
-        b->sets[i].branch = k;
+        sets[i].branch = k;
         load[k] += bytes[i];
     }
-    for (Set& set : b->sets)
-        if (pstd_status st = build_set(b, set)) return st;
+    for (Set& set : sets)
+        if (pstd_status st = build_set(b, set)) {
+            free_groups(sets);
+            return st;
+        }
+    drop_graph(b);  // it holds the old descriptor buffers
+    free_groups(b->sets);
+    b->sets.swap(sets);
+    b->gen.swap(gen);
+    b->nt = largest > pstd::kInfinityCacheBytes ? 1 : 0;
     return PSTD_OK;
 }
 
@@ -379,7 +387,7 @@ pstd_status pstd_batch_destroy(pstd_batch* b) {
         if (b->join[k]) (void)hipEventDestroy(b->join[k]);
     }
     if (b->fork) (void)hipEventDestroy(b->fork);
-    free_groups(b);
+    free_groups(b->sets);
     for (pstd_solver* s : b->inst) pstd_destroy(s);
     (void)hipFree(b->ctr);
     delete b;

@@ -216,7 +216,12 @@ namespace {
 pstd_problem problem(int n = 48) {
     pstd_problem p;
     pstd_problem_init_defaults(&p);
-    for (int a = 0; a < 3; ++a) p.n[a] = n;
+    for (int a = 0; a < 3; ++a) {
+        p.n[a] = n;
+        p.tfsf[a][2] += n - 48;
+        p.tfsf[a][3] += n - 48;
+        p.surf_hi[a] += n - 48;
+    }
     p.dft_begin = 0;
     p.dft_end = 100;
     return p;
@@ -280,11 +285,57 @@ void far_field_captured() {
     CHECK(g_live.empty());
 }
 
+// Batches whose launch groups cannot be rebuilt for want of memory: the run fails,
+// and the next one, with memory again, launches every instance with tables that
+// are allocated.
+void batch_rebuild() {
+    hipStream_t st;
+    hipStreamCreateWithFlags(&st, 0);
+    const std::vector<pstd_problem> p = {problem(48), problem(64), problem(160), problem(48)};
+    const std::vector<int64_t> once(p.size(), 3), grow(p.size(), 3000);
+    int failed = 0;
+    for (int k = 0;; ++k) {
+        pstd_batch* b = nullptr;
+        CHECK(pstd_batch_create(p.data(), (int32_t)p.size(), st, &b) == PSTD_OK);
+        CHECK(pstd_batch_run(b, once.data()) == PSTD_OK);
+        std::map<std::string, int> instances;  // launched, by kernel
+        int launches = 0;
+        g_on_launch = [&](const std::string& name, dim3, void** a) {
+            if (!has(name, "pass_kernel")) return;
+            const void *desc = *(void**)a[1], *off = *(void**)a[2];
+            const int n = *(int*)a[3];
+            CHECK(n > 0 && room(desc) > 0 && room(off) >= (int64_t)(n + 1) * (int64_t)sizeof(int));
+            instances[name] += n;
+            ++launches;
+        };
+        g_fail_in = k;
+        const bool grown = pstd_batch_run(b, grow.data()) == PSTD_OK;  // the step tables grow, and the groups with them
+        CHECK(grown == (g_fail_in >= 0));
+        g_fail_in = -1;
+        if (!grown) {
+            ++failed;
+            CHECK(launches == 0);
+        }
+        (void)hipGetLastError();
+        instances.clear();
+        CHECK(pstd_batch_run(b, once.data()) == PSTD_OK);
+        int total = 0;
+        for (const auto& i : instances) total += i.second;
+        CHECK(total == 3 * 3 * (int)p.size());  // steps, passes, instances
+        g_on_launch = nullptr;
+        CHECK(pstd_batch_destroy(b) == PSTD_OK);
+        CHECK(g_live.empty());
+        if (grown) break;
+    }
+    CHECK(failed > (int)p.size());
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "far_field_captured") far_field_captured();
+    else if (what == "batch_rebuild") batch_rebuild();
     else return 2;
     std::printf("%d failures\n", g_failures);
     return g_failures ? 1 : 0;
