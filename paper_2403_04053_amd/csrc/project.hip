@@ -267,12 +267,13 @@ __device__ __forceinline__ void sincos_sum(double p, double e, double* sn, doubl
 // pi b'/N - d r/2, b' the signed index of m, x_l = (l - N/2 + 1/2) d.  With the
 // closed form of the geometric sum that is (-1)^b' sin(M theta) / theta times the
 // phase of the middle, M = hi - lo.  centred: without the factor exp(-i r mid).
-// theta is carried with its rounding error, as are the faces' phases and the
-// directions' angles: a rounded product of 50 radians is off by 3.5e-15.  RMS error
-// of a far field against 80-bit sums, of its RMS: 160^3 2.7e-15 (4.4e-15 with
-// rounded products, 2.9e-15 with sums of the factors direction by direction),
-// 192 x 144 x 128 2.7e-15 (4.7, 3.2), 64 x 96 x 108 1.7e-15 (2.5, 1.8).
-__device__ __forceinline__ double2 far_factor(const FarAxis& ax, double r, int m, bool centred) {
+// theta is carried with its rounding error, as are the nodes r + r_low, the faces'
+// phases and the directions' angles: a rounded product of 50 radians is off by
+// 3.5e-15, a rounded node moves it by 2e-15.  RMS error of far fields of random planes
+// against 80-bit sums, of their RMS (with rounded nodes; with the factors themselves
+// and rounded products, direction by direction): 160^3 2.0e-15 (3.4, 3.9), 64 x 96 x 108
+// 1.5e-15 (2.6, 2.5), 288 x 48 x 64 at 3 points per wavelength 6.4e-15 (14.9, 15.1).
+__device__ __forceinline__ double2 far_factor(const FarAxis& ax, double r, double r_low, int m, bool centred) {
     const int bp = m < ax.N / 2 ? m : m - ax.N;
     const int M = ax.hi - ax.lo;
     constexpr double kPiLow = 1.2246467991473532e-16;  // pi - kPi
@@ -282,7 +283,7 @@ __device__ __forceinline__ double2 far_factor(const FarAxis& ax, double r, int m
     const double l1 = (fma(-t1, ax.N, p1) + fma(kPiLow, bp, e1)) / ax.N;
     const double t2 = two_product(r, 0.5 * ax.d, &e2);
     const double th = t1 - t2, v = th - t1;
-    const double tl = ((t1 - (th - v)) - (t2 + v)) + (l1 - e2);
+    const double tl = ((t1 - (th - v)) - (t2 + v)) + (l1 - fma(r_low, 0.5 * ax.d, e2));
     double em;
     const double pm = two_product(M, th, &em);
     double sm, cm;
@@ -304,12 +305,13 @@ __device__ __forceinline__ double2 far_factor(const FarAxis& ax, double r, int m
     return make_double2(mag * cs, mag * sn);
 }
 
-// G[j][m]: the centred factor at the Chebyshev nodes r_j = cos(pi (j + 1/2) / K)
-__global__ void far_nodes_kernel(FarAxis ax, int K, double2* __restrict__ G) {
+// G[j][m]: the centred factor at the Chebyshev nodes r_j = cos(pi (j + 1/2) / K),
+// node[j] as a rounded value and the rest of it (80-bit values of the host)
+__global__ void far_nodes_kernel(FarAxis ax, int K, const double2* __restrict__ node, double2* __restrict__ G) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= (int64_t)K * ax.N) return;
     const int m = (int)(id % ax.N), j = (int)(id / ax.N);
-    G[id] = far_factor(ax, cospi((j + 0.5) / K), m, true);
+    G[id] = far_factor(ax, node[j].x, node[j].y, m, true);
 }
 
 // D[k][j]: values at the K nodes to Chebyshev coefficients
@@ -514,7 +516,7 @@ __global__ __launch_bounds__(256) void far_wide_kernel(const double3* __restrict
             const double rr[3] = {rh.x, rh.y, rh.z};
             __syncthreads();
             for (int a = 0; a < 3; ++a)
-                for (int m = t; m < f.ax[a].N; m += 256) g[off[a] + m] = far_factor(f.ax[a], rr[a], m, false);
+                for (int m = t; m < f.ax[a].N; m += 256) g[off[a] + m] = far_factor(f.ax[a], rr[a], 0.0, m, false);
             __syncthreads();
             for (int a = 0; a < 3; ++a) {
                 const int N = f.ax[a].N;
@@ -1223,12 +1225,20 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
     if (s->far_tab) return hipSuccess;
     int64_t total = 0;
     size_t work = 0;
+    std::vector<double2> nodes;
+    int64_t node_off[3];
     for (int a = 0; a < 3; ++a) {
         const int64_t N = p.n[a], K = s->K[a] = far_terms(far_axis(p, dxb, a).half);
         s->far_off[a] = total;
         total += K * N;
         work = std::max(work, (size_t)(2 * K * N + K * K + N * N) * sizeof(double2));
+        node_off[a] = (int64_t)nodes.size();
+        for (int64_t j = 0; j < K; ++j) {
+            const long double r = std::cos(3.14159265358979323846264L * (j + 0.5L) / K);
+            nodes.push_back(make_double2((double)r, (double)(r - (double)r)));
+        }
     }
+    work += nodes.size() * sizeof(double2);
     s->far_y = s->far_c = 0;
     for (int a = 0; a < 3; ++a) {
         const int b = face_axis_b(a), c = face_axis_c(a);
@@ -1249,16 +1259,19 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
     hipError_t e;
     if ((e = hipMalloc(&tab, (size_t)total * sizeof(double2))) ||
         (e = hipMalloc(&fwork, (size_t)(s->coef_off[3] + s->far_y + s->far_c + s->far_wide) * sizeof(double2))) ||
-        (e = hipMalloc(&part, (size_t)kFarPart * sizeof(double2))))
+        (e = hipMalloc(&part, (size_t)kFarPart * sizeof(double2))) ||
+        (e = hipStreamSynchronize(stream)) ||  // the scratch may be in use
+        (e = hipMemcpy(s->work, nodes.data(), nodes.size() * sizeof(double2), hipMemcpyHostToDevice)))
         return undo(e);
+    const double2* node = s->work;
     for (int a = 0; a < 3 && !e; ++a) {
         const int N = p.n[a], K = s->K[a];
-        double2* G = s->work;
+        double2* G = s->work + nodes.size();
         double2* DG = G + (int64_t)K * N;
         double2* D = DG + (int64_t)K * N;
         double2* W = D + (int64_t)K * K;
         hipLaunchKernelGGL(far_nodes_kernel, dim3(blocks_of((int64_t)K * N)), dim3(256), 0, stream, far_axis(p, dxb, a),
-                           K, G);
+                           K, node + node_off[a], G);
         hipLaunchKernelGGL(far_dct_kernel, dim3(blocks_of((int64_t)K * K)), dim3(256), 0, stream, K, D);
         hipLaunchKernelGGL(dft_matrix_kernel, dim3(blocks_of((int64_t)N * N)), dim3(256), 0, stream, N, W);
         e = zgemm(K, N, K, ZOp{D, K}, ZOp{G, N}, DG, N, 0, 0, 1, 1, {}, stream);
