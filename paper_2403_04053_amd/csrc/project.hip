@@ -479,87 +479,146 @@ __global__ void far_sum_kernel(const double3* __restrict__ dirs, int64_t nd, dou
 }
 
 // Directions with a component beyond 1 (no unit vector, but the formula holds
-// for any): each by a workgroup from the factors themselves.  A workgroup
-// looks over 256 directions; scratch: 2 (Nx + Ny + Nz) values per workgroup.
+// for any): from the factors themselves.  A workgroup looks over `per` directions
+// and takes those blocks of 16 that hold such a one, a block as the rows of products
+// on the FP64 matrix cores: the factors g of an axis, folded with its transform to h
+// = g W, then h_c P of the four planes of an axis's faces, and the sum over b with
+// h_b and the faces' phases in the accumulators' lanes.  A block costs the same with
+// one such direction as with 16.  Bound by the latency of the planes' loads (five
+// per 16 products).
 constexpr double kFarLimit = 1.0 + 4.0e-16;
-constexpr int kWideGroups = 64;
+constexpr int kWideGroups = 256;  // workgroups at most, each with scratch of its own
+constexpr int kWideWaves = 8;
 
 struct FarWide {
     FarAxis ax[3];
     double pref[3];
     const double2* planes;  // phasors, [face][psi, dpsi][plane]
+    const double2* tw;      // per axis exp(-2 pi i j / N)
+    int longest;            // axis length
 };
 
-__global__ __launch_bounds__(256) void far_wide_kernel(const double3* __restrict__ dirs, int64_t nd, FarWide f,
-                                                       double2* __restrict__ scratch, double2* __restrict__ out) {
-    __shared__ int todo[256];
-    __shared__ int count;
-    __shared__ double red[2][256];
-    const int t = threadIdx.x;
-    const int Ns = f.ax[0].N + f.ax[1].N + f.ax[2].N;
-    double2* g = scratch + (int64_t)blockIdx.x * 2 * Ns;
-    double2* h = g + Ns;
+// scratch of one workgroup: h of the three axes, [index][direction], and g
+__host__ __device__ inline int64_t wide_scratch(const FarWide& f) {
+    return 16 * ((int64_t)f.ax[0].N + f.ax[1].N + f.ax[2].N + f.longest);
+}
+
+// c += a b, complex, on 16 x 16 x 4 tiles
+__device__ __forceinline__ void zmfma(double2 a, double2 b, v4d& re, v4d& im) {
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im, 0, 0, 0);
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im, 0, 0, 0);
+}
+
+__global__ __launch_bounds__(64 * kWideWaves) void far_wide_kernel(const double3* __restrict__ dirs, int64_t nd, int per,
+                                                                   FarWide f, double2* scratch,
+                                                                   double2* __restrict__ out) {
+    __shared__ int todo[16];          // blocks of 16 that hold such a direction
+    __shared__ double rr[3][16];      // the block's directions
+    __shared__ double2 ph[6][16];     // pref times the phase of each face
+    __shared__ double2 part[kWideWaves][16];
+    constexpr int NT = 64 * kWideWaves;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, li = lane & 15, lk = lane >> 4;
+    const int64_t base = (int64_t)blockIdx.x * per;
+    auto wide = [](double3 r) { return fabs(r.x) > kFarLimit || fabs(r.y) > kFarLimit || fabs(r.z) > kFarLimit; };
+    if (t < 16) todo[t] = 0;
+    __syncthreads();
+    if (t < per && base + t < nd && wide(dirs[base + t])) todo[t >> 4] = 1;
+    __syncthreads();
+    double2* h = scratch + (int64_t)blockIdx.x * wide_scratch(f);
+    double2* g = h + 16 * ((int64_t)f.ax[0].N + f.ax[1].N + f.ax[2].N);
     const int off[3] = {0, f.ax[0].N, f.ax[0].N + f.ax[1].N};
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < nd; base += (int64_t)gridDim.x * 256) {
+    for (int blk = 0; blk * 16 < per; ++blk) {
+        if (!todo[blk]) continue;
+        const int64_t d0 = base + blk * 16;
         __syncthreads();
-        if (t == 0) count = 0;
-        __syncthreads();
-        if (base + t < nd) {
-            const double3 r = dirs[base + t];
-            if (fabs(r.x) > kFarLimit || fabs(r.y) > kFarLimit || fabs(r.z) > kFarLimit) todo[atomicAdd(&count, 1)] = t;
+        if (t < 16) {
+            const double3 r = dirs[min(d0 + t, nd - 1)];
+            const double v[3] = {r.x, r.y, r.z};
+            for (int face = 0; face < 6; ++face) {
+                const int a = face / 2, side = face % 2;
+                double sn, cs;
+                sincos(-v[a] * (f.ax[a].mid + (side ? f.ax[a].half : -f.ax[a].half)), &sn, &cs);
+                const double w = side ? -f.pref[a] : f.pref[a];
+                ph[face][t] = make_double2(w * cs, w * sn);
+                rr[a][t] = v[a];
+            }
         }
         __syncthreads();
-        const int n = count;
-        for (int q = 0; q < n; ++q) {
-            const int64_t d = base + todo[q];
-            const double3 rh = dirs[d];
-            const double rr[3] = {rh.x, rh.y, rh.z};
+        for (int a = 0; a < 3; ++a) {
+            const int N = f.ax[a].N;
+            for (int e = t; e < 16 * N; e += NT) g[e] = far_factor(f.ax[a], rr[a][e & 15], 0.0, e >> 4, false);
             __syncthreads();
-            for (int a = 0; a < 3; ++a)
-                for (int m = t; m < f.ax[a].N; m += 256) g[off[a] + m] = far_factor(f.ax[a], rr[a], 0.0, m, false);
-            __syncthreads();
-            for (int a = 0; a < 3; ++a) {
-                const int N = f.ax[a].N;
-                for (int i = t; i < N; i += 256) {
-                    double2 s = make_double2(0, 0);
-                    for (int m = 0; m < N; ++m) {
-                        double sn, cs;
-                        sincospi(-2.0 * (double)(((int64_t)m * i) % N) / N, &sn, &cs);
-                        s = zadd(s, zmul(g[off[a] + m], make_double2(cs, sn)));
-                    }
-                    h[off[a] + i] = s;
+            for (int j0 = wave * 16; j0 < N; j0 += 16 * kWideWaves) {
+                const int j = j0 + li;
+                v4d re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+                int idx = (int)((int64_t)lk * j % N);
+                const int hop = (int)((int64_t)4 * j % N);
+                for (int k = lk; k - lk < N; k += 4) {
+                    const double2 x = k < N ? g[k * 16 + li] : make_double2(0, 0);
+                    zmfma(x, f.tw[off[a] + idx], re, im);
+                    idx += hop;
+                    if (idx >= N) idx -= N;
                 }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (j < N) h[(int64_t)(off[a] + j) * 16 + 4 * r + lk] = make_double2(re[r], im[r]);
             }
             __syncthreads();
-            double2 acc = make_double2(0, 0);
-            const double2* pl = f.planes;
-            for (int face = 0; face < 6; ++face) {
-                const int a = face / 2, side = face % 2, b = face_axis_b(a), c = face_axis_c(a);
-                const int Nb = f.ax[b].N, Nc = f.ax[c].N;
-                const int64_t np = (int64_t)Nb * Nc;
-                double2 s = make_double2(0, 0);
-                for (int64_t i = t; i < np; i += 256) {
-                    const double2 v = pl[i], dv = pl[np + i];
-                    const double2 x = make_double2(dv.x - rr[a] * v.y, dv.y + rr[a] * v.x);
-                    s = zadd(s, zmul(zmul(h[off[b] + i % Nb], h[off[c] + i / Nb]), x));
+        }
+        // tiles of 16 columns b of the three axes' planes, dealt to the waves
+        double2 sum[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sum[r] = make_double2(0, 0);
+        int job = 0;
+        const double2* pl = f.planes;
+        for (int a = 0; a < 3; ++a) {
+            const int b = face_axis_b(a), c = face_axis_c(a);
+            const int Nb = f.ax[b].N, Nc = f.ax[c].N;
+            const int64_t np = (int64_t)Nb * Nc;
+            const double2 *hb = h + (int64_t)off[b] * 16, *hc = h + (int64_t)off[c] * 16;
+            for (int j0 = 0; j0 < Nb; j0 += 16, ++job) {
+                if (job % kWideWaves != wave) continue;
+                const int j = min(j0 + li, Nb - 1);
+                v4d re[4], im[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    re[q] = v4d{0, 0, 0, 0};
+                    im[q] = v4d{0, 0, 0, 0};
                 }
-                double sn, cs;
-                sincos(-rr[a] * (f.ax[a].mid + (side ? f.ax[a].half : -f.ax[a].half)), &sn, &cs);
-                const double w = side ? -f.pref[a] : f.pref[a];
-                acc = zadd(acc, zmul(s, make_double2(w * cs, w * sn)));
-                pl += 2 * np;
-            }
-            red[0][t] = acc.x;
-            red[1][t] = acc.y;
-            __syncthreads();
-            for (int w = 128; w > 0; w >>= 1) {
-                if (t < w) {
-                    red[0][t] += red[0][t + w];
-                    red[1][t] += red[1][t + w];
+                for (int k = lk; k - lk < Nc; k += 4) {
+                    const int kc = min(k, Nc - 1);
+                    const double2 x = k < Nc ? hc[kc * 16 + li] : make_double2(0, 0);
+                    const double2* y = pl + (int64_t)kc * Nb + j;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) zmfma(x, y[q * np], re[q], im[q]);
                 }
-                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = 4 * r + lk;
+                    const double ra = rr[a][i];
+                    // dpsi + i r_a psi of the low and the high face
+                    const double2 lo = zmul(ph[2 * a][i], make_double2(re[1][r] - ra * im[0][r], im[1][r] + ra * re[0][r]));
+                    const double2 hi = zmul(ph[2 * a + 1][i], make_double2(re[3][r] - ra * im[2][r], im[3][r] + ra * re[2][r]));
+                    if (j0 + li < Nb) sum[r] = zadd(sum[r], zmul(hb[(int64_t)j * 16 + i], zadd(lo, hi)));
+                }
             }
-            if (t == 0) out[d] = make_double2(red[0][0], red[1][0]);
+            pl += 4 * np;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            for (int o = 8; o > 0; o >>= 1) {
+                sum[r].x += __shfl_xor(sum[r].x, o, 64);
+                sum[r].y += __shfl_xor(sum[r].y, o, 64);
+            }
+            if (li == 0) part[wave][4 * r + lk] = sum[r];
+        }
+        __syncthreads();
+        if (t < 16 && d0 + t < nd && wide(dirs[d0 + t])) {
+            double2 s = part[0][t];
+            for (int w = 1; w < kWideWaves; ++w) s = zadd(s, part[w][t]);
+            out[d0 + t] = s;
         }
     }
 }
@@ -1059,12 +1118,13 @@ struct ProjectState {
     double2* far_tab = nullptr;   // per axis [K][N]: Chebyshev coefficients of the far factor
     // the far field's scratch, of one size for any number of directions and its own,
     // so that a far field captured by a caller finds it and no later call moves it
-    double2* far_work = nullptr;  // coefficients, products, far_wide_kernel's values
+    double2* far_work = nullptr;  // coefficients, products, far_wide_kernel's scratch
     double2* far_part = nullptr;  // [rows][direction]: far_eval_kernel's sums
     int64_t near_off[4] = {0, 0, 0, 0};
     int64_t far_off[4] = {0, 0, 0, 0};
     int K[3] = {0, 0, 0};
-    int64_t coef_off[4] = {0, 0, 0, 0}, far_y = 0, far_c = 0, far_wide = 0;  // in far_work
+    int64_t coef_off[4] = {0, 0, 0, 0}, far_y = 0, far_c = 0;  // in far_work
+    FarWide wide{};
     int64_t face_off[7] = {0, 0, 0, 0, 0, 0, 0};
     int64_t total = 0;
 };
@@ -1213,6 +1273,7 @@ hipError_t near_tables(ProjectState* s, const pstd_problem& p, hipStream_t strea
 // jsplit, jsplit at most the waves that 2048 lack, so rows times directions stay
 // under 3 kFarChunk + 2048 * 16
 constexpr int64_t kFarChunk = 1 << 16;
+static_assert(kFarChunk <= 256 * kWideGroups, "a workgroup of far_wide_kernel looks over 256 directions at most");
 constexpr int64_t kFarPart = 3 * kFarChunk + 2048 * 16;
 
 int far_kbp(const ProjectState* s, int a) { return (s->K[face_axis_b(a)] + 3) / 4 * 4; }
@@ -1246,7 +1307,19 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
         s->far_y = std::max(s->far_y, (int64_t)4 * p.n[c] * s->K[b]);
         s->far_c = std::max(s->far_c, (int64_t)4 * s->K[c] * s->K[b]);
     }
-    s->far_wide = (int64_t)kWideGroups * 2 * ((int64_t)p.n[0] + p.n[1] + p.n[2]);
+    FarWide& fw = s->wide;
+    for (int a = 0; a < 3; ++a) {
+        fw.ax[a] = far_axis(p, dxb, a);
+        fw.longest = std::max(fw.longest, fw.ax[a].N);
+        fw.pref[a] = dxb[face_axis_b(a)] * dxb[face_axis_c(a)] /
+                     (4 * kPi * p.n[face_axis_b(a)] * p.n[face_axis_c(a)]) / p.k0;
+    }
+    std::vector<double2> tw;
+    for (int a = 0; a < 3; ++a)
+        for (int j = 0; j < p.n[a]; ++j) {
+            const long double x = 2 * 3.14159265358979323846264L * j / p.n[a];
+            tw.push_back(make_double2((double)std::cos(x), (double)-std::sin(x)));
+        }
     TRY(ensure(&s->work, &s->work_bytes, work));
     double2 *tab = nullptr, *fwork = nullptr, *part = nullptr;
     auto undo = [&](hipError_t e) {
@@ -1257,8 +1330,10 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
         return e;
     };
     hipError_t e;
-    if ((e = hipMalloc(&tab, (size_t)total * sizeof(double2))) ||
-        (e = hipMalloc(&fwork, (size_t)(s->coef_off[3] + s->far_y + s->far_c + s->far_wide) * sizeof(double2))) ||
+    if ((e = hipMalloc(&tab, (size_t)(total + tw.size()) * sizeof(double2))) ||
+        (e = hipMemcpy(tab + total, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice)) ||
+        (e = hipMalloc(&fwork, (size_t)(s->coef_off[3] + s->far_y + s->far_c + kWideGroups * wide_scratch(fw)) *
+                                   sizeof(double2))) ||
         (e = hipMalloc(&part, (size_t)kFarPart * sizeof(double2))) ||
         (e = hipStreamSynchronize(stream)) ||  // the scratch may be in use
         (e = hipMemcpy(s->work, nodes.data(), nodes.size() * sizeof(double2), hipMemcpyHostToDevice)))
@@ -1281,6 +1356,8 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
     s->far_work = fwork;
     s->far_part = part;
     s->far_tab = tab;
+    fw.tw = tab + total;
+    fw.planes = s->phasors;
     return hipSuccess;
 }
 
@@ -1350,8 +1427,7 @@ hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb
     double2* C = Y + s->far_y;
     double2* scratch = C + s->far_c;
     FarArgs args{};
-    FarWide fw{};
-    fw.planes = s->phasors;
+    const FarWide& fw = s->wide;
     double mid[3];
     for (int a = 0; a < 3; ++a) {
         const int b = face_axis_b(a), c = face_axis_c(a);
@@ -1365,8 +1441,6 @@ hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb
         const int64_t n = (int64_t)Kbp[a] * Kcp[a] * 4;
         hipLaunchKernelGGL(far_pack_kernel, dim3(blocks_of(n)), dim3(256), 0, stream, Kb, Kc, Kbp[a], Kcp[a], C,
                            coef + coef_off[a]);
-        fw.ax[a] = far_axis(p, dxb, a);
-        fw.pref[a] = dxb[b] * dxb[c] / (4 * kPi * Nb * Nc) / p.k0;
         args.ax[a] = FarEval{reinterpret_cast<const double*>(coef + coef_off[a]), Kbp[a], Kcp[a], fw.ax[a].half,
                              std::fma(0.5 * dxb[a], p.surf_hi[a] - p.surf_lo[a], -fw.ax[a].half), fw.pref[a]};
         mid[a] = fw.ax[a].mid;
@@ -1383,8 +1457,9 @@ hipError_t far_field(ProjectState** pst, const pstd_problem& p, const double dxb
                            dirs + d0, nd, args, s->far_part);
         hipLaunchKernelGGL(far_sum_kernel, dim3(blocks_of(nd)), dim3(256), 0, stream, dirs + d0, nd,
                            make_double3(mid[0], mid[1], mid[2]), s->far_part, rows, out + d0);
-        hipLaunchKernelGGL(far_wide_kernel, dim3(std::min<unsigned>(kWideGroups, blocks_of(nd))), dim3(256), 0, stream,
-                           dirs + d0, nd, fw, scratch, out + d0);
+        const int per = (int)((nd + 16 * kWideGroups - 1) / (16 * kWideGroups)) * 16;
+        hipLaunchKernelGGL(far_wide_kernel, dim3(blocks_of(nd, per)), dim3(64 * kWideWaves), 0, stream, dirs + d0, nd, per,
+                           fw, scratch, out + d0);
     }
     return hipGetLastError();
 }
