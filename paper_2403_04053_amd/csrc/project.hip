@@ -485,7 +485,9 @@ __global__ void far_sum_kernel(const double3* __restrict__ dirs, int64_t nd, dou
 // = g W, then h_c P of the four planes of an axis's faces, and the sum over b with
 // h_b and the faces' phases in the accumulators' lanes.  A block costs the same with
 // one such direction as with 16.  Bound by the latency of the planes' loads (five
-// per 16 products).
+// per 16 products).  64 and 65160 such vectors: 64^3 0.14 and 1.28 ms, 160^3 0.49 and
+// 6.6 ms (a workgroup per direction on the vector units: 5.0 and 79, 21 and 335 ms; the
+// factors' products for every call, as it once was: 0.58 and 2.7, 1.4 and 7.3 ms).
 constexpr double kFarLimit = 1.0 + 4.0e-16;
 constexpr int kWideGroups = 256;  // workgroups at most, each with scratch of its own
 constexpr int kWideWaves = 8;
