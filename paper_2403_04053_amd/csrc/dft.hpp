@@ -87,7 +87,11 @@ __device__ __forceinline__ float2 twmul(float2 x) {
     } else {
         constexpr float c = (float)cx::cosr(R, j);
         constexpr float s = (float)(S * cx::sinr(R, j));
-        return make_float2(x.x * c - x.y * s, x.x * s + x.y * c);
+        // Turns by an odd eighth (c = s but for signs, each product used twice) in FMAs of
+        // their own: left to the compiler they round differently from kernel to kernel, and
+        // the x and y passes in one launch then differ from separate ones
+        if constexpr (8 * j % R == 0) return make_float2(fmaf(x.x, c, -(x.y * s)), fmaf(x.x, s, x.y * c));
+        else return make_float2(x.x * c - x.y * s, x.x * s + x.y * c);
     }
 }
 
