@@ -330,12 +330,38 @@ void batch_rebuild() {
     CHECK(failed > (int)p.size());
 }
 
+// Short runs of a batch beyond the cache go pass by pass over all instances; from
+// twelve such launches on, by sets on the branches.
+void batch_short_runs() {
+    hipStream_t st;
+    hipStreamCreateWithFlags(&st, 0);
+    const std::vector<pstd_problem> p(4, problem(160));
+    pstd_batch* b = nullptr;
+    CHECK(pstd_batch_create(p.data(), (int32_t)p.size(), st, &b) == PSTD_OK);
+    for (int steps = 1; steps <= 5; ++steps) {
+        int launches = 0, instances = 0;
+        g_on_launch = [&](const std::string& name, dim3, void** a) {
+            if (!has(name, "pass_kernel")) return;
+            ++launches;
+            instances += *(int*)a[3];
+        };
+        const std::vector<int64_t> n(p.size(), steps);
+        CHECK(pstd_batch_run(b, n.data()) == PSTD_OK);
+        std::printf("%d steps: %d launches\n", steps, launches);
+        CHECK(launches == (steps < 4 ? 3 * steps : 12 * steps));
+        CHECK(instances == 12 * steps);
+    }
+    g_on_launch = nullptr;
+    CHECK(pstd_batch_destroy(b) == PSTD_OK);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "far_field_captured") far_field_captured();
     else if (what == "batch_rebuild") batch_rebuild();
+    else if (what == "batch_short_runs") batch_short_runs();
     else return 2;
     std::printf("%d failures\n", g_failures);
     return g_failures ? 1 : 0;
