@@ -350,9 +350,12 @@ __global__ void sphere_add_kernel(const double2* part, int rows, int64_t n, doub
     out[i] = make_double2(scale * s.x, scale * s.y);
 }
 
-// flag: a point not outside the sphere of physical radius `radius`
+// flag: a point not outside the sphere of physical radius `radius`.  Rounded as
+// the host would, product by product: with the sum in FMAs points on the sphere to
+// the last digit are taken that are refused, and the reverse.
 __global__ void check_outside_kernel(const double3* __restrict__ obs, int64_t n, double radius,
                                      unsigned* __restrict__ flag) {
+#pragma clang fp contract(off)
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double3 p = obs[i];
