@@ -176,7 +176,8 @@ pstd_status pstd_run_timed(pstd_solver* s, int64_t n_steps, double* pass_ms_host
  * not touched.  Candidates are compared in compiled order and a later one
  * replaces the current choice only when it is at least 3 % faster, so timing
  * noise does not flip the choice between runs.  Solvers whose x and y passes
- * run in one launch take one shape for both.  Also captures the step graph
+ * run in one launch take one shape for both; fused segment blocks are compared
+ * with the two passes.  Also captures the step graph
  * of the chosen shapes, so that the next pstd_run does not.  Synchronises.
  * ENOMEM if the scratch cannot be allocated. */
 pstd_status pstd_autotune(pstd_solver* s, int32_t reps);
@@ -202,19 +203,26 @@ pstd_status pstd_check_state_noalloc(pstd_solver* s, double* norm2_out_host);
 /* Average duration (microseconds) of one launch of the pass along `axis`
  * with its current tile shape: `reps` back-to-back launches on scratch
  * buffers of the solver's size, bracketed by HIP events on the solver's
- * stream (the same timing the autotuner uses).  The solver's state is not
- * touched.  Synchronises. */
+ * stream (the same timing the autotuner uses).  Where a step runs the x and y
+ * passes in one launch, axis 0 and axis 1 both give that launch.  Plane values
+ * of a box surface are staged as in runs of four steps or more.  The solver's
+ * state is not touched.  Synchronises. */
 pstd_status pstd_pass_time(pstd_solver* s, int32_t axis, int32_t reps, double* us_out_host);
 
 /* Tile shape used by the pass along axis (0, 1, 2): info_host[5] =
  * {N, N1, N2, pencils per workgroup, M1}; M1 > 0 when stage B (the N2-point
  * DFTs) is split as N2 = M1 * (N2 / M1) over all N2 threads of a pencil, 0
- * otherwise.  Host only. */
+ * otherwise; -1 on axes 0 and 1 where the x and y passes of segment blocks run
+ * fused, a form of its own that takes that many pencils.  Host only. */
 pstd_status pstd_tile_info(const pstd_solver* s, int32_t axis, int32_t* info_host);
 
 /* Use the compiled tile shape of axis `axis` with stage-A factor n1,
- * `pencils` pencils per workgroup and stage-B split m1 (0: none).
- * EUNSUPPORTED if there is none.  Synchronises. */
+ * `pencils` pencils per workgroup and stage-B split m1 (0: none).  m1 = -1 with
+ * the figures of pstd_tile_info: the fused x and y passes, on both axes (blocks
+ * alike along x and y whose core fits the pencils); any other shape on axis 0 or
+ * 1 takes the two passes apart.  Solvers that run whole x and y pencils in one
+ * launch do so while both axes have the same shape.  EUNSUPPORTED if there is
+ * none.  Synchronises. */
 pstd_status pstd_set_tile(pstd_solver* s, int32_t axis, int32_t n1, int32_t pencils, int32_t m1);
 
 /* Compiled tile shapes for pass length n (segmented != 0: subdomain mode):

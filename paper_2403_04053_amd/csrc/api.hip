@@ -476,12 +476,17 @@ pstd_status launch_passes(pstd_solver* s, hipStream_t stream, int koff, int coun
     return PSTD_OK;
 }
 
+// whether runs of the solver stage the box surface's plane values in a ring of
+// its own, memory allowing
+bool stages_box(const pstd_solver* s) {
+    return !s->no_ring && !s->pulse && !s->in_batch && s->prob.surface_kind == 0 && s->prob.scheme == 0 &&
+           s->prob.dft_end > s->prob.dft_begin;
+}
+
 // The ring of staged plane values, had on the first run that can use it;
 // without memory for it the passes add each step to the sums themselves
 void ensure_box_ring(pstd_solver* s) {
-    if (s->bring[0] || s->no_ring || s->pulse || s->in_batch || s->prob.surface_kind != 0 || s->prob.scheme != 0 ||
-        s->prob.dft_end <= s->prob.dft_begin)
-        return;
+    if (s->bring[0] || !stages_box(s)) return;
     if (pstd::stream_capturing(s->stream)) return;
     size_t total = 0, off[3];
     for (int a = 0; a < 3; ++a) {
@@ -719,6 +724,7 @@ pstd_status solver_create(const pstd_problem* p, hipStream_t stream, int64_t* ex
     for (int a = 0; a < 3; ++a)
         if ((e = hipMalloc(&s->acc[a], 8 * s->points[a] * sizeof(double2)))) return cleanup(hip_fail(s, e, "hipMalloc acc"));
     for (int a = 0; a < 3; ++a) pass_variants(local_len(*p, a), p->sub_core[a] > 0, &s->variant[a], 1);
+    s->seg_fused = solver_seg_xy_fits(s) && seg_xy_block(local_len(*p, 0), p->sub_core[0]);
     if ((st = build_tables(s))) return cleanup(st);
     if (ext_ctr && p->surface_kind != 0)
         return cleanup(fail(s, PSTD_EUNSUPPORTED, "batch instances integrate over the box surface only"));
@@ -789,12 +795,17 @@ pstd_status solver_create(const pstd_problem* p, hipStream_t stream, int64_t* ex
 // Time `reps` back-to-back launches of each given tile shape of one axis on
 // scratch state of the solver's size (the solver's own state is untouched);
 // ms_out[k] receives the average milliseconds per launch of shape ids[k].
-// axis kAxisXY: the x and y passes in one launch.
-constexpr int kAxisXY = -1;
+// axis kAxisXY, kAxisSegXY: the x and y passes in one launch, of whole pencils
+// and of segment blocks.  Plane values of the box surface are staged where the
+// solver's runs stage them.
+constexpr int kAxisXY = -1, kAxisSegXY = -2;
 pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t reps, float* ms_out) {
     float2 *tb0 = nullptr, *tb1 = nullptr, *tL = nullptr, *tL2 = nullptr;
     double2 *tacc = nullptr, *tacc_y = nullptr;
-    const int ax0 = axis == kAxisXY ? 0 : axis;
+    const bool both = axis < 0;
+    const int ax0 = both ? 0 : axis;
+    const bool stage = stages_box(s);
+    float2 *tring = nullptr, *tring_y = nullptr;
     const bool own = axis == kAxisXY || (axis == 2 && solver_xy(s));
     int64_t* tctr = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -805,6 +816,8 @@ pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t
         (void)hipFree(tL2);
         (void)hipFree(tacc);
         (void)hipFree(tacc_y);
+        (void)hipFree(tring);
+        (void)hipFree(tring_y);
         (void)hipFree(tctr);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
@@ -813,8 +826,10 @@ pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t
     if ((e = hipMalloc(&tb0, s->cells * sizeof(float2))) || (e = hipMalloc(&tb1, s->cells * sizeof(float2))) ||
         (e = hipMalloc(&tL, s->cells * sizeof(float2))) || (e = hipMalloc(&tctr, 2 * sizeof(int64_t))) ||
         (own && (e = hipMalloc(&tL2, s->cells * sizeof(float2)))) ||
-        (axis == kAxisXY && (e = hipMalloc(&tacc_y, 8 * s->points[1] * sizeof(double2)))) ||
-        (axis == kAxisXY && (e = hipMemset(tacc_y, 0, 8 * s->points[1] * sizeof(double2)))) ||
+        (both && (e = hipMalloc(&tacc_y, 8 * s->points[1] * sizeof(double2)))) ||
+        (both && (e = hipMemset(tacc_y, 0, 8 * s->points[1] * sizeof(double2)))) ||
+        (stage && (e = hipMalloc(&tring, 4 * s->points[ax0] * sizeof(float2)))) ||
+        (stage && both && (e = hipMalloc(&tring_y, 4 * s->points[1] * sizeof(float2)))) ||
         (e = hipMalloc(&tacc, 8 * s->points[ax0] * sizeof(double2))) || (e = hipEventCreate(&e0)) ||
         (e = hipEventCreate(&e1)) || (e = hipMemset(tb0, 0, s->cells * sizeof(float2))) ||
         (e = hipMemset(tb1, 0, s->cells * sizeof(float2))) ||
@@ -855,7 +870,7 @@ pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t
     for (int k = 0; k < n; ++k) ms_out[k] = std::numeric_limits<float>::max();
     for (int round = 0; round < 2; ++round)
     for (int k = 0; k < n && !e; ++k) {
-        auto args_of = [&](int ax, double2* acc) {
+        auto args_of = [&](int ax, double2* acc, float2* ring) {
             PassArgs a;
             const int keep = s->variant[ax];
             s->variant[ax] = ids[k];
@@ -866,14 +881,16 @@ pstd_status time_shapes(pstd_solver* s, int axis, const int* ids, int n, int32_t
             a.L = tL;
             a.L2 = tL2;
             a.acc = acc;
+            if (stage) a.bstage = ring;
             a.ctr = tctr;
             return a;
         };
-        const PassArgs a = args_of(ax0, tacc);
-        const PassArgs ay = axis == kAxisXY ? args_of(1, tacc_y) : PassArgs{};
+        const PassArgs a = args_of(ax0, tacc, tring);
+        const PassArgs ay = both ? args_of(1, tacc_y, tring_y) : PassArgs{};
         auto launch = [&]() {
-            return axis == kAxisXY ? launch_variant_xy(ids[k], a, ay, false, 0, s->stream)
-                                   : launch_variant_single(ids[k], seg, axis, a, 0, s->stream);
+            return axis == kAxisXY      ? launch_variant_xy(ids[k], a, ay, false, 0, s->stream)
+                   : axis == kAxisSegXY ? launch_variant_seg_xy(ids[k], a, ay, 0, s->stream)
+                                        : launch_variant_single(ids[k], seg, axis, a, 0, s->stream);
         };
         float ms = 0;
         e = launch();
@@ -894,22 +911,31 @@ pstd_status solver_autotune(pstd_solver* s, int32_t reps) {
     // FDTD step has one shape)
     if (s->prob.scheme == 1) return PSTD_OK;
     // (solvers with L2 take one shape for x and y, timed in their one launch)
-    // (fused segment blocks have one form)
-    for (int axis = solver_seg_xy(s) ? 2 : s->L2 ? 1 : 0; axis < 3; ++axis) {
+    float in_pass[3] = {0, 0, 0};
+    for (int axis = s->L2 ? 1 : 0; axis < 3; ++axis) {
         const bool xy = s->L2 && axis == 1;
         const bool seg = s->prob.sub_core[axis] > 0;
         int ids[16];
         float ms[16];
         const int nv = std::min(16, pass_variants(local_len(s->prob, axis), seg, ids, 16));
         if (xy) s->variant[0] = s->variant[1];
-        if (nv <= 1) continue;
+        if (nv <= 1 && !(solver_seg_xy_fits(s) && axis < 2)) continue;
         pstd_status st = time_shapes(s, xy ? kAxisXY : axis, ids, nv, reps, ms);
         if (st) return st;
         int best = 0;
         for (int k = 1; k < nv; ++k)
             if (ms[k] < 0.97f * ms[best]) best = k;  // a later shape must win clearly: stable choices
         s->variant[axis] = ids[best];
+        in_pass[axis] = ms[best];
         if (xy) s->variant[0] = ids[best];
+    }
+    // segment blocks: x and y fused, which has one form, against the two; the other
+    // way than now must win as clearly
+    if (solver_seg_xy_fits(s)) {
+        float fused = 0;
+        if (pstd_status st = time_shapes(s, kAxisSegXY, &s->variant[0], 1, reps, &fused)) return st;
+        const float two = in_pass[0] + in_pass[1];
+        s->seg_fused = s->seg_fused ? !(two < 0.97f * fused) : fused < 0.97f * two;
     }
     solver_drop_graph(s);
     return PSTD_OK;
@@ -1140,10 +1166,15 @@ pstd_status pstd_check_state_noalloc(pstd_solver* s, double* norm2_out) {
     return check_state_with(s, d, norm2_out);
 }
 
+// M1 of the fused x and y passes in pstd_tile_info and pstd_set_tile
+static constexpr int kFusedM1 = -1;
+
 pstd_status pstd_pass_time(pstd_solver* s, int32_t axis, int32_t reps, double* us_out) {
     if (!s || !us_out || axis < 0 || axis > 2 || reps < 1) return PSTD_EINVAL;
     float ms = 0;
-    pstd_status st = time_shapes(s, axis, &s->variant[axis], 1, reps, &ms);
+    // x and y in one launch: that launch, for either
+    const int what = axis == 2 ? 2 : solver_seg_xy(s) ? kAxisSegXY : solver_xy(s) ? kAxisXY : axis;
+    pstd_status st = time_shapes(s, what, &s->variant[axis], 1, reps, &ms);
     if (st) return st;
     *us_out = 1e3 * ms;
     return PSTD_OK;
@@ -1165,6 +1196,10 @@ pstd_status pstd_tile_info(const pstd_solver* s, int32_t axis, int32_t* info_hos
     info_host[2] = sh.N2;
     info_host[3] = sh.P;
     info_host[4] = sh.M1;
+    if (axis < 2 && solver_seg_xy(s)) {
+        info_host[3] = seg_xy_pencils_of(sh.N);
+        info_host[4] = kFusedM1;
+    }
     return PSTD_OK;
 }
 
@@ -1175,9 +1210,13 @@ pstd_status pstd_set_tile(pstd_solver* s, int32_t axis, int32_t n1, int32_t penc
     const int nv = std::min(16, pass_variants(local_len(s->prob, axis), seg, ids, 16));
     for (int k = 0; k < nv; ++k) {
         const PassShape sh = variant_shape(ids[k]);
-        if (sh.N1 == n1 && sh.P == pencils && sh.M1 == m1) {
+        // the fused x and y passes of segment blocks count as a shape of both axes; any
+        // other shape on one of them takes the two passes apart
+        const bool fused = m1 == kFusedM1 && axis < 2 && solver_seg_xy_fits(s) && sh.M1 == 0;
+        if (sh.N1 == n1 && (fused ? pencils == seg_xy_pencils_of(sh.N) : sh.P == pencils && sh.M1 == m1)) {
             HIP_TRY(s, hipStreamSynchronize(s->stream));
-            s->variant[axis] = ids[k];
+            if (!fused) s->variant[axis] = ids[k];
+            if (axis < 2) s->seg_fused = fused;
             solver_drop_graph(s);
             return PSTD_OK;
         }

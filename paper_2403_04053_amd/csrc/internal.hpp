@@ -126,9 +126,11 @@ hipError_t launch_variant_single(int v, bool segmented, int axis, const PassArgs
 // launch, the y term in ay.L2; the z pass of the same step takes L2 too
 hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool adjoint, int koff,
                              hipStream_t stream);
-// Whether segment blocks of `core` points and local length N along both x and y
-// take the fused x and y passes (core rows and columns on at least half of the
-// pencils of the compiled block); and their launch, in the place of the two
+// Pencils of the fused x and y passes of segment blocks of local length N (0: none);
+// whether blocks of `core` points take them unless the caller chooses (the autotuner
+// compares, pstd_set_tile sets); and their launch, in the place of the two.  The core
+// rows and columns have to fit the pencils.
+int seg_xy_pencils_of(int N);
 bool seg_xy_block(int N, int core);
 hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream);
 // The largest fields (psi pair, L and L2, 32 B per cell) whose x and y passes

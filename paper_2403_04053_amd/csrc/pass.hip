@@ -81,6 +81,8 @@ hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool
     return kVariants[v].xy(ax, ay, adjoint, koff, stream);
 }
 
+int seg_xy_pencils_of(int N) { return seg_xy_pencils(N); }
+
 bool seg_xy_block(int N, int core) {
     const int P = seg_xy_pencils(N);
     return core <= P && 2 * core > P;
@@ -89,7 +91,7 @@ bool seg_xy_block(int N, int core) {
 hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream) {
     if (v < 0 || v >= kNumVariants) return hipErrorInvalidValue;
     if (ax.seg_core != ay.seg_core || ax.seg_halo != ay.seg_halo ||
-        kVariants[v].shape.N != ax.seg_core + 2 * ax.seg_halo || !seg_xy_block(kVariants[v].shape.N, ax.seg_core) ||
+        kVariants[v].shape.N != ax.seg_core + 2 * ax.seg_halo || ax.seg_core > seg_xy_pencils(kVariants[v].shape.N) ||
         ax.nseg * ax.seg_core != ax.nx || ay.nseg * ay.seg_core != ay.ny)
         return hipErrorInvalidValue;
     return kVariants[v].segxy(ax, ay, koff, stream);

@@ -46,6 +46,7 @@ struct pstd_solver {
     bool no_ring = false;         // no memory for it
     int64_t points[3] = {0, 0, 0};
     int variant[3] = {0, 0, 0};   // tile shape of each axis pass
+    bool seg_fused = false;       // segment blocks: x and y fused, where they can be (solver_seg_xy_fits)
     // per-step tables, steps [0, tab_cap)
     float2* sigma_tab = nullptr;
     double2* w_tab = nullptr;
@@ -80,12 +81,13 @@ void solver_args(const pstd_solver* s, int axis, PassArgs& a);
 void solver_account_steps(pstd_solver* s, int64_t from, int64_t to);
 pstd_status solver_autotune(pstd_solver* s, int32_t reps);
 void solver_drop_graph(pstd_solver* s);
-// the x and y passes of segment blocks alike along both axes run fused
-inline bool solver_seg_xy(const pstd_solver* s) {
+// the x and y passes of segment blocks alike along both axes can run fused; and do
+inline bool solver_seg_xy_fits(const pstd_solver* s) {
     const pstd_problem& p = s->prob;
     return !s->in_batch && p.sub_core[0] > 0 && p.sub_core[0] == p.sub_core[1] &&
-           s->variant[0] == s->variant[1] && seg_xy_block(p.sub_core[0] + 2 * p.sub_halo, p.sub_core[0]);
+           p.sub_core[0] <= seg_xy_pencils_of(p.sub_core[0] + 2 * p.sub_halo);
 }
+inline bool solver_seg_xy(const pstd_solver* s) { return s->seg_fused && solver_seg_xy_fits(s); }
 // the x and y passes run in one launch (solver_args then sets PassArgs::L2)
 inline bool solver_xy(const pstd_solver* s) { return s->L2 && s->variant[0] == s->variant[1]; }
 // the misfit forward run no longer matches the solver state

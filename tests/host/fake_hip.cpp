@@ -22,6 +22,7 @@ namespace {
 std::map<char*, size_t> g_live;       // allocations
 std::set<hipStream_t> g_capturing;
 int g_fail_in = -1;                   // allocations until one fails (-1: none does)
+std::vector<size_t>* g_sizes = nullptr;  // of allocations, where noted
 int g_violations = 0;                 // calls that a capture does not allow
 std::function<void(const std::string&, dim3, void**)> g_on_launch;
 
@@ -69,6 +70,7 @@ hipError_t hipMalloc(void** p, size_t n) {
         return g_last = hipErrorOutOfMemory;
     }
     if (g_fail_in > 0) --g_fail_in;
+    if (g_sizes) g_sizes->push_back(n);
     *p = std::calloc(1, n ? n : 1);
     g_live[(char*)*p] = n;
     return hipSuccess;
@@ -355,6 +357,76 @@ void batch_short_runs() {
     CHECK(pstd_batch_destroy(b) == PSTD_OK);
 }
 
+// What is timed for an axis is the launch that a step makes, with the plane values
+// staged as it stages them; and a tile shape set on an axis is the one that runs.
+void timed_launches() {
+    hipStream_t st;
+    hipStreamCreateWithFlags(&st, 0);
+    std::set<std::string> seen;
+    g_on_launch = [&](const std::string& name, dim3, void**) {
+        for (const char* k : {"pass_xy_kernel", "pass_seg_xy_kernel", "pass_kernel"})
+            if (has(name, k)) {
+                seen.insert(k);
+                break;
+            }
+    };
+    using Names = std::set<std::string>;
+    auto launched = [&](auto&& call) {
+        seen.clear();
+        CHECK(call() == PSTD_OK);
+        return seen;
+    };
+    double us;
+    {
+        const pstd_problem p = problem();
+        pstd_solver* s = nullptr;
+        CHECK(pstd_create(&p, st, &s) == PSTD_OK);
+        for (int axis = 0; axis < 2; ++axis)
+            CHECK(launched([&] { return pstd_pass_time(s, axis, 3, &us); }) == Names{"pass_xy_kernel"});
+        CHECK(launched([&] { return pstd_pass_time(s, 2, 3, &us); }) == Names{"pass_kernel"});
+        std::vector<size_t> sizes;
+        g_sizes = &sizes;
+        CHECK(pstd_autotune(s, 2) == PSTD_OK);
+        g_sizes = nullptr;
+        int rings = 0;
+        for (size_t n : sizes) rings += n == 4 * 48 * 48 * 2 * sizeof(float);
+        CHECK(rings == 3);  // x and y, and z
+        CHECK(launched([&] { return pstd_set_tile(s, 0, 8, 32, 0); }).empty());  // x alone
+        CHECK(launched([&] { return pstd_run(s, 1); }) == Names{"pass_kernel"});
+        CHECK(launched([&] { return pstd_pass_time(s, 0, 3, &us); }) == Names{"pass_kernel"});
+        CHECK(pstd_set_tile(s, 1, 8, 32, 0) == PSTD_OK);
+        CHECK((launched([&] { return pstd_run(s, 1); }) == Names{"pass_kernel", "pass_xy_kernel"}));
+        CHECK(pstd_destroy(s) == PSTD_OK);
+    }
+    {
+        pstd_problem p = problem(96);
+        for (int a = 0; a < 3; ++a) p.sub_core[a] = 48;
+        p.sub_halo = 8;
+        p.sub_taper = 3;
+        pstd_solver* s = nullptr;
+        CHECK(pstd_create(&p, st, &s) == PSTD_OK);
+        const Names fused{"pass_kernel", "pass_seg_xy_kernel"}, apart{"pass_kernel"};
+        int32_t was[3][5], info[5];
+        for (int axis = 0; axis < 3; ++axis) CHECK(pstd_tile_info(s, axis, was[axis]) == PSTD_OK);
+        CHECK(was[0][0] == 64 && was[0][3] == 48 && was[0][4] == -1 && was[1][4] == -1 && was[2][4] == 0);
+        CHECK(launched([&] { return pstd_run(s, 1); }) == fused);
+        CHECK(launched([&] { return pstd_pass_time(s, 1, 3, &us); }) == Names{"pass_seg_xy_kernel"});
+        CHECK(pstd_set_tile(s, 0, 8, 16, 0) == PSTD_OK);
+        CHECK(pstd_tile_info(s, 0, info) == PSTD_OK && info[3] == 16 && info[4] == 0);
+        CHECK(launched([&] { return pstd_run(s, 1); }) == apart);
+        CHECK(pstd_set_tile(s, 1, 8, 16, 0) == PSTD_OK);  // the same on both
+        CHECK(launched([&] { return pstd_run(s, 1); }) == apart);
+        CHECK(launched([&] { return pstd_pass_time(s, 1, 3, &us); }) == apart);
+        // the shapes noted before bring the noted form back
+        for (int axis = 0; axis < 3; ++axis)
+            CHECK(pstd_set_tile(s, axis, was[axis][1], was[axis][3], was[axis][4]) == PSTD_OK);
+        CHECK(launched([&] { return pstd_run(s, 1); }) == fused);
+        CHECK(pstd_set_tile(s, 2, 8, 48, -1) == PSTD_EUNSUPPORTED);
+        CHECK(pstd_destroy(s) == PSTD_OK);
+    }
+    g_on_launch = nullptr;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -362,6 +434,7 @@ int main(int argc, char** argv) {
     if (what == "far_field_captured") far_field_captured();
     else if (what == "batch_rebuild") batch_rebuild();
     else if (what == "batch_short_runs") batch_short_runs();
+    else if (what == "timed_launches") timed_launches();
     else return 2;
     std::printf("%d failures\n", g_failures);
     return g_failures ? 1 : 0;

@@ -23,7 +23,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["far_field_captured", "batch_rebuild", "batch_short_runs"])
+@pytest.mark.parametrize("what", ["far_field_captured", "batch_rebuild", "batch_short_runs", "timed_launches"])
 def test_host_code(program, what):
     p = subprocess.run([program, what], capture_output=True, text=True, timeout=120)
     assert p.returncode == 0, p.stdout[-4000:] + p.stderr[-2000:]
