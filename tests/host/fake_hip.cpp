@@ -424,6 +424,17 @@ void timed_launches() {
         CHECK(pstd_set_tile(s, 2, 8, 48, -1) == PSTD_EUNSUPPORTED);
         CHECK(pstd_destroy(s) == PSTD_OK);
     }
+    {
+        // a core that fits the pencils of the fused form and leaves too many idle
+        pstd_problem p = problem(96);
+        for (int a = 0; a < 3; ++a) p.sub_core[a] = 32;
+        p.sub_halo = 16;
+        p.sub_taper = 3;
+        pstd_solver* s = nullptr;
+        CHECK(pstd_create(&p, st, &s) == PSTD_OK);
+        CHECK(launched([&] { return pstd_run(s, 1); }) == Names{"pass_kernel"});
+        CHECK(pstd_destroy(s) == PSTD_OK);
+    }
     g_on_launch = nullptr;
 }
 
