@@ -276,7 +276,10 @@ pstd_status pstd_get_sphere_phasors(pstd_solver* s, double* out_dev, int64_t n);
 
 /* Scattered wave Psi(r) at n_obs points (physical xyz, double[3] each) by the
  * box integral of Eqs. bottomPsi_lm ... leftrightPsi_ln summed by Eq. Psi,
- * with each sinc expanded to 8th order in its shift.  Output complex128,
+ * with each sinc expanded to 8th order in its shift; of the products of the two
+ * expansions those of total degree 9 to 16 are taken as polynomials of degree 8,
+ * which leaves the error of the expansions as it is (about a^9 / 10! of a cell's
+ * sum, a the reduced half spacing; within 1 %).  Output complex128,
  * relative to a unit-amplitude incident wave.  Points must lie outside the
  * box (outside the sphere with surface_kind 1, which sums the Kirchhoff
  * integral over the sphere's nodes instead).  ESTATE before any window

@@ -9,8 +9,8 @@
 namespace pstd {
 
 // r = sqrt(x) and inv = 1 / r for positive normal x: the hardware's reciprocal
-// square root (about 2^-27) after one coupled Newton step of both, and one
-// residual correction of each.
+// square root (about 2^-27) after one step of Goldschmidt's coupled iteration of
+// both, and one residual correction of each.
 __device__ __forceinline__ void sqrt_rsqrt(double x, double* r, double* inv) {
     double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
@@ -25,8 +25,9 @@ __device__ __forceinline__ void sqrt_rsqrt(double x, double* r, double* inv) {
     *r = g;
 }
 
-// Largest |x| fast_sincos takes: n = x 2 / pi then has at most 28 bits and the
-// three-part reduction below leaves an error under 2^-60.
+// Largest |x| fast_sincos takes: n = x 2 / pi then has at most 28 bits, the first
+// fused product of the reduction below is exact, and the second rounds r once more:
+// r is off by at most 2^-54.
 constexpr double kFastSincosLimit = 2.0e8;
 
 // sin and cos of |x| <= kFastSincosLimit: x = n pi/2 + r with pi/2 in three

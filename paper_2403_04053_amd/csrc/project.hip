@@ -661,13 +661,26 @@ __global__ void check_points_kernel(const double3* __restrict__ obs, int64_t n, 
     if (f) atomicOr(flags, f);
 }
 
+// Share of the product of degrees (hp, hq) in the low term (p, q): e, its entry of E,
+// times A^(hp - p) B^(hq - q)
+__device__ __forceinline__ double econ_weight(double e, double A, double B, int p, int q, int hp, int hq) {
+    for (int t = p; t < hp; ++t) e *= A;
+    for (int t = hp; t < p; ++t) e /= A;
+    for (int t = q; t < hq; ++t) e *= B;
+    for (int t = hq; t < q; ++t) e /= B;
+    return e;
+}
+
 // Economised terms Q[cell][field][low_row(p) + q], p + q <= 8, from the full
 // products Qg[field][p][q][cell]: on the cells' disk (alpha_b / A)^2 +
 // (alpha_c / B)^2 <= 1, A = d_b / 2, B = d_c / 2, a monomial of degree 9 to 16 is
 // replaced by its least-squares polynomial of degree 8 (E, for the unit
-// disk), which leaves under 1/50 of the degree-9 terms, themselves the size
-// of what the 8th-order series drops.  45 terms per field and cell instead
-// of 81.
+// disk).  That leaves 1/11 to 1/32 of the largest value of a degree-9 monomial and
+// 1/5 to 1/30 of one of degree 10 to 16.  Evaluated over the disk and all spectral
+// indexes for 3 to 20 points per wavelength, A = B, the sums with E are within 1/35 of
+// a^9 / 10!, the 9th-order term that the series drops (a = A), of those without, and
+// their largest error against the exact sincs within 0.7 % of theirs (B = 0.6 A: 1.4 %
+// below).  45 terms per field and cell instead of 81.
 __global__ void economise_kernel(const double2* __restrict__ Qg, int64_t ncell, const double* __restrict__ E, double A,
                                  double Bs, double2* __restrict__ Q) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -684,12 +697,7 @@ __global__ void economise_kernel(const double2* __restrict__ Qg, int64_t ncell, 
         for (int hq = kTerms - hp; hq < kTerms; ++hq, ++h) {
             const double e = E[h * kLow + k];
             if (e == 0.0) continue;
-            // scale A^(hp - p) B^(hq - q)
-            double w = e;
-            for (int t = p; t < hp; ++t) w *= A;
-            for (int t = hp; t < p; ++t) w /= A;
-            for (int t = q; t < hq; ++t) w *= Bs;
-            for (int t = hq; t < q; ++t) w /= Bs;
+            const double w = econ_weight(e, A, Bs, p, q, hp, hq);
             const double2 x = g[(int64_t)(hp * kTerms + hq) * ncell];
             s.x += w * x.x;
             s.y += w * x.y;
@@ -719,11 +727,7 @@ __global__ void economise_adjoint_kernel(const double2* __restrict__ low, int64_
                 const int k = low_row(p) + q;
                 const double e = E[h * kLow + k];
                 if (e == 0.0) continue;
-                double w = e;
-                for (int t = p; t < hp; ++t) w *= A;
-                for (int t = hp; t < p; ++t) w /= A;
-                for (int t = q; t < hq; ++t) w *= Bs;
-                for (int t = hq; t < q; ++t) w /= Bs;
+                const double w = econ_weight(e, A, Bs, p, q, hp, hq);
                 const double2 x = g[(int64_t)k * ncell];
                 s.x += w * x.x;
                 s.y += w * x.y;
