@@ -62,3 +62,35 @@ def test_captured_box_far_field(warm):
         assert torch.isfinite(torch.view_as_real(want)).all() and want.abs().max() > 0
         assert (far * (3 / s.step) - want).abs().max() <= 1e-14 * want.abs().max()
     s.close()
+
+
+@pytest.mark.parametrize("surface", ["box", "sphere"])
+def test_captured_run_leaves_the_sums_of_an_eager_one(surface):
+    """Eight steps captured before the solver has run more than one, replayed between
+    eager runs of four (from the first of which a box surface stages its plane values,
+    while the graph goes on adding each to the sums): the same terms in the same order,
+    so states and surface sums are equal to the bit, behind the saved state's header of
+    80 bytes (the host counts captured steps once)."""
+    import paper_2403_04053_amd as P
+    prob = problem(surface)
+    stream = torch.cuda.Stream()
+    a, b = synth.random_state(prob.n, 1), synth.random_state(prob.n, 2)
+    one, two = P.Solver(prob, stream=stream), P.Solver(prob, stream=stream)
+    for s in (one, two):
+        s.set_state(a, b, 0)
+        s.run(1)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        one.run(8)
+    for _ in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        one.run(4)
+        two.run(8)
+        two.run(4)
+        stream.synchronize()
+        x, y = one.save_state(), two.save_state()
+        assert torch.equal(x[80:], y[80:])
+    for s in (one, two):
+        s.close()
