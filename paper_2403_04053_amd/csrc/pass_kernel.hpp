@@ -291,10 +291,14 @@ __device__ __forceinline__ TileGeo block_geo(const Fields& f, const SegBlock& b,
 // as a whole: threads without one (the last tile's, or idle in stage A) read
 // the pencil of the grid's first cell, whose values they
 // carry through the transforms and never store, so that no branch parts a
-// wave's loads from what was issued before them.
-template <int N, int N1, int N2, bool SEG, bool NTL = false>
+// wave's loads from what was issued before them.  CELL: the grid's first cell is
+// read in the place of a segment's cells outside, for the same reason (core 24 in 64,
+// 144^3: x pass 15.5 us with a branch per element, 14.1 so, y 16.9 and 16.0); without
+// it each element is branched around (the fused passes, which hold two such tiles:
+// 288 x 192 x 240 65.8 us, 72.5 with it).
+template <int N, int N1, int N2, bool SEG, bool NTL = false, bool CELL = false>
 __device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ p, int64_t step, const TileGeo& g, int n2,
-                                          float2 (&x)[N1]) {
+                                          float2 (&x)[N1], GMEM const float2* cell = nullptr) {
     static_assert(N == N1 * N2, "pencil factors");
     if constexpr (!SEG) {
         unroll<N1>([&](auto i) { x[decltype(i)::value] = load_last<NTL>(at_step(p, decltype(i)::value, step)); });
@@ -302,8 +306,15 @@ __device__ __forceinline__ void load_tile(GMEM const float2* __restrict__ p, int
         unroll<N1>([&](auto i) {
             constexpr int n1 = decltype(i)::value;
             const int e = g.g0 + n2 + N2 * n1;
-            x[n1] = make_float2(0.f, 0.f);
-            if (g.valid && e >= 0 && e < g.Ng) x[n1] = load_last<NTL>(at_step(p, n1, step));
+            const bool in = g.valid && e >= 0 && e < g.Ng;
+            if constexpr (CELL) {
+                GMEM const float2* q = at_step(p, n1, step);
+                const float2 v = load_last<NTL>(in ? q : cell);
+                x[n1] = in ? v : make_float2(0.f, 0.f);
+            } else {
+                x[n1] = make_float2(0.f, 0.f);
+                if (in) x[n1] = load_last<NTL>(at_step(p, n1, step));
+            }
         });
     }
 }
@@ -396,7 +407,8 @@ __device__ __forceinline__ void pass_tile(const Fields& f, int tile, int koff, f
     const int64_t step = (int64_t)(N2 * sizeof(float2)) * geo.estride;  // bytes between its elements
     float2 raw[N1];
     if constexpr (FUSED && AXIS == 1) unroll<N1>([&](auto i) { raw[decltype(i)::value] = pre[decltype(i)::value]; });
-    else load_tile<N, N1, N2, SEG, NTL && AXIS == 2>(psi + first, step, geo, n2, raw);
+    else if constexpr (FUSED) load_tile<N, N1, N2, SEG>(psi + first, step, geo, n2, raw);
+    else load_tile<N, N1, N2, SEG, NTL && AXIS == 2, true>(psi + first, step, geo, n2, raw, psi);
     unroll<TR>([&](auto i) {
         const int j = min(t + decltype(i)::value * NT, N - 1);
         s_tw[j] = r_tw[decltype(i)::value];
