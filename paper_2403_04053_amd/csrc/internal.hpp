@@ -130,11 +130,10 @@ hipError_t launch_variant_xy(int v, const PassArgs& ax, const PassArgs& ay, bool
 // whether blocks of `core` points take them unless the caller chooses (the autotuner
 // compares, pstd_set_tile sets); and their launch, in the place of the two.  The core
 // rows and columns have to fit the pencils, and idle ones cost what busy ones do:
-// the line is at four fifths of them.  Steps fused and as two passes, us, blocks
-// along x and y, 160 planes: core 48 of 48 pencils 74.4 and 80.0, 44 66.1 and 69.4, 40
-// 60.6 and 61.6, 36 58.3 and 56.3, 32 73.8 and 62.9; 32 of 32 54.1 and 61.0, 28 63.6 and
-// 67.9, 26 60.8 and 63.0, 24 57.8 and 57.2; 16 of 16 60.5 and 62.5, 14 56.4 and 57.4, 12
-// 67.2 and 61.9.
+// the line is at nine tenths of them.  Steps fused and as two passes, us, blocks
+// along x and y, 160 planes: core 48 of 48 pencils 74.2 and 78.0, 44 66.4 and 66.7, 40
+// 62.2 and 59.8, 36 58.6 and 54.5, 32 74.0 and 61.2; 32 of 32 54.1 and 58.8, 30 52.4 and
+// 56.1, 28 64.4 and 64.3, 24 57.8 and 54.9; 16 of 16 57.2 and 59.4, 14 57.2 and 54.4.
 int seg_xy_pencils_of(int N);
 bool seg_xy_block(int N, int core);
 hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream);

@@ -85,7 +85,7 @@ int seg_xy_pencils_of(int N) { return seg_xy_pencils(N); }
 
 bool seg_xy_block(int N, int core) {
     const int P = seg_xy_pencils(N);
-    return core <= P && 5 * core >= 4 * P;
+    return core <= P && 10 * core >= 9 * P;
 }
 
 hipError_t launch_variant_seg_xy(int v, const PassArgs& ax, const PassArgs& ay, int koff, hipStream_t stream) {
