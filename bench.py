@@ -84,9 +84,12 @@ def kernel_src_sha256(sources=KERNEL_SOURCES):
 
 def step_kernels(s, n_steps):
     """{kernel: ms per step} of run_timed: a launch of x and y together is in
-    the x slot, and the y slot then holds the gap between two events."""
+    the x slot, and the y slot then holds the gap between two events (segment
+    blocks keep one sum of both terms, which the plain z pass reads)."""
     x, y, z = (ms / n_steps for ms in s.run_timed(n_steps))
-    return {"xy": x, "z+": z} if y < 0.3 * x else {"x": x, "y": y, "z": z}
+    if y >= 0.3 * x:
+        return {"x": x, "y": y, "z": z}
+    return {"xy": x, "z" if s.problem.sub_core[0] > 0 else "z+": z}
 
 
 def kernel_axis(kernel):

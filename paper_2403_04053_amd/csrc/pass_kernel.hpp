@@ -907,8 +907,10 @@ __global__ __launch_bounds__(P * (N1 > N2 ? N1 : N2)) void pass_xy_kernel(PassAr
 // (x and y segmented alike, the block's C rows and columns as many pencils as
 // P): the x term stays in LDS until the y pass adds its own, so L is written
 // once and psi^n read beyond the L2 once, 8 + 8 instead of 18 + 26 B per cell.
-// 288 x 192 x 240 in cores of 48 with 8-cell halos: 75 to 80 us against 30.3 + 41.0
-// (the step 163 against 180); it is then bound by vector instructions, about 67 us of it.
+// 288 x 192 x 240 in cores of 48 with 8-cell halos: 66 us back to back, 83 in the step,
+// against 29.6 + 40.8 and 48 + 50 of two launches (the step 164 against 182).  33.3 M
+// wave instructions, 54 us of issue (the core rows and the core columns, 64 points for
+// 48 each: 1.33 x the core's), beside 212 MB, 40 us; neither is reached.
 template <int N, int N1, int N2, int M1, int P>
 __global__ __launch_bounds__(P * N2) void pass_seg_xy_kernel(PassArgs ax, PassArgs ay, int koff) {
     static_assert(P + 1 <= TileLds<N, N1, N2>::STRIDE, "the x term fits the exchange buffer");

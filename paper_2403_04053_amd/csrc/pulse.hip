@@ -66,7 +66,6 @@ constexpr double kPi = 3.141592653589793238462643383279502884;
 constexpr int kLag = 8;
 constexpr int kModeChunk = 256;
 
-// compensated (Neumaier) summation step
 // in-place radix-2 DFT, forward (e^{-i 2 pi l j / N}), N a power of two
 void fft_pow2(std::vector<std::complex<double>>& a) {
     const size_t n = a.size();
