@@ -1122,8 +1122,9 @@ struct ProjectState {
     double2* near_tab = nullptr;  // per axis [t][cell][N]: sinc-Taylor expansion of the cell integral
     double* econ = nullptr;       // economisation table
     double2* far_tab = nullptr;   // per axis [K][N]: Chebyshev coefficients of the far factor
-    // the far field's scratch, of one size for any number of directions and its own,
-    // so that a far field captured by a caller finds it and no later call moves it
+    // the far field's scratch, behind the tables: of one size for any number of
+    // directions and its own, so that a far field captured by a caller finds it and no
+    // later call moves it
     double2* far_work = nullptr;  // coefficients, products, far_wide_kernel's scratch
     double2* far_part = nullptr;  // [rows][direction]: far_eval_kernel's sums
     int64_t near_off[4] = {0, 0, 0, 0};
@@ -1285,27 +1286,37 @@ constexpr int64_t kFarPart = 3 * kFarChunk + 2048 * 16;
 int far_kbp(const ProjectState* s, int a) { return (s->K[face_axis_b(a)] + 3) / 4 * 4; }
 int far_kcp(const ProjectState* s, int a) { return (s->K[face_axis_c(a)] + 15) / 16 * 16; }
 
-// The far tables of the three axes: per axis [K][N], the Chebyshev
-// coefficients of the centred factor with the transform folded in (D G W); and
-// the far field's scratch.  Allocates on the first call only.
+// The far tables of the three axes, per axis [K][N]: the Chebyshev coefficients of
+// the centred factor with the transform folded in (D G W); and the far field's
+// scratch, in the same allocation.  Nothing after the first call.
 hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3], hipStream_t stream) {
     if (s->far_tab) return hipSuccess;
-    int64_t total = 0;
-    size_t work = 0;
-    std::vector<double2> nodes;
-    int64_t node_off[3];
+    // host values: the Chebyshev nodes, twiddles exp(-2 pi i j / N)
+    constexpr long double kPiL = 3.14159265358979323846264L;
+    std::vector<double2> host;
+    int64_t total = 0, build = 0, node_off[3];
+    FarWide fw{};
     for (int a = 0; a < 3; ++a) {
-        const int64_t N = p.n[a], K = s->K[a] = far_terms(far_axis(p, dxb, a).half);
+        const int b = face_axis_b(a), c = face_axis_c(a);
+        fw.ax[a] = far_axis(p, dxb, a);
+        fw.longest = std::max(fw.longest, fw.ax[a].N);
+        fw.pref[a] = dxb[b] * dxb[c] / (4 * kPi * p.n[b] * p.n[c]) / p.k0;
+        const int64_t N = p.n[a], K = s->K[a] = far_terms(fw.ax[a].half);
         s->far_off[a] = total;
         total += K * N;
-        work = std::max(work, (size_t)(2 * K * N + K * K + N * N) * sizeof(double2));
-        node_off[a] = (int64_t)nodes.size();
-        for (int64_t j = 0; j < K; ++j) {
-            const long double r = std::cos(3.14159265358979323846264L * (j + 0.5L) / K);
-            nodes.push_back(make_double2((double)r, (double)(r - (double)r)));
+        build = std::max(build, 2 * K * N + K * K + N * N);
+        for (int j = 0; j < N; ++j) {
+            const long double x = 2 * kPiL * j / N;
+            host.push_back(make_double2((double)std::cos(x), (double)-std::sin(x)));
         }
     }
-    work += nodes.size() * sizeof(double2);
+    for (int a = 0; a < 3; ++a) {
+        node_off[a] = (int64_t)host.size();
+        for (int64_t j = 0; j < s->K[a]; ++j) {
+            const long double r = std::cos(kPiL * (j + 0.5L) / s->K[a]);
+            host.push_back(make_double2((double)r, (double)(r - (double)r)));
+        }
+    }
     s->far_y = s->far_c = 0;
     for (int a = 0; a < 3; ++a) {
         const int b = face_axis_b(a), c = face_axis_c(a);
@@ -1313,57 +1324,37 @@ hipError_t far_tables(ProjectState* s, const pstd_problem& p, const double dxb[3
         s->far_y = std::max(s->far_y, (int64_t)4 * p.n[c] * s->K[b]);
         s->far_c = std::max(s->far_c, (int64_t)4 * s->K[c] * s->K[b]);
     }
-    FarWide& fw = s->wide;
-    for (int a = 0; a < 3; ++a) {
-        fw.ax[a] = far_axis(p, dxb, a);
-        fw.longest = std::max(fw.longest, fw.ax[a].N);
-        fw.pref[a] = dxb[face_axis_b(a)] * dxb[face_axis_c(a)] /
-                     (4 * kPi * p.n[face_axis_b(a)] * p.n[face_axis_c(a)]) / p.k0;
-    }
-    std::vector<double2> tw;
-    for (int a = 0; a < 3; ++a)
-        for (int j = 0; j < p.n[a]; ++j) {
-            const long double x = 2 * 3.14159265358979323846264L * j / p.n[a];
-            tw.push_back(make_double2((double)std::cos(x), (double)-std::sin(x)));
-        }
-    TRY(ensure(&s->work, &s->work_bytes, work));
-    double2 *tab = nullptr, *fwork = nullptr, *part = nullptr;
-    auto undo = [&](hipError_t e) {
-        (void)hipStreamSynchronize(stream);
-        (void)hipFree(tab);
-        (void)hipFree(fwork);
-        (void)hipFree(part);
-        return e;
-    };
-    hipError_t e;
-    if ((e = hipMalloc(&tab, (size_t)(total + tw.size()) * sizeof(double2))) ||
-        (e = hipMemcpy(tab + total, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice)) ||
-        (e = hipMalloc(&fwork, (size_t)(s->coef_off[3] + s->far_y + s->far_c + kWideGroups * wide_scratch(fw)) *
-                                   sizeof(double2))) ||
-        (e = hipMalloc(&part, (size_t)kFarPart * sizeof(double2))) ||
-        (e = hipStreamSynchronize(stream)) ||  // the scratch may be in use
-        (e = hipMemcpy(s->work, nodes.data(), nodes.size() * sizeof(double2), hipMemcpyHostToDevice)))
-        return undo(e);
-    const double2* node = s->work;
+    // (the tables are built in the scratch)
+    const int64_t work = std::max(build, s->coef_off[3] + s->far_y + s->far_c + kWideGroups * wide_scratch(fw));
+    double2* tab = nullptr;
+    hipError_t e = hipMalloc(&tab, (size_t)(total + (int64_t)host.size() + work + kFarPart) * sizeof(double2));
+    double2* vals = tab + total;
+    double2* scratch = vals + host.size();
+    if (!e) e = hipMemcpy(vals, host.data(), host.size() * sizeof(double2), hipMemcpyHostToDevice);
     for (int a = 0; a < 3 && !e; ++a) {
         const int N = p.n[a], K = s->K[a];
-        double2* G = s->work + nodes.size();
+        double2* G = scratch;
         double2* DG = G + (int64_t)K * N;
         double2* D = DG + (int64_t)K * N;
         double2* W = D + (int64_t)K * K;
-        hipLaunchKernelGGL(far_nodes_kernel, dim3(blocks_of((int64_t)K * N)), dim3(256), 0, stream, far_axis(p, dxb, a),
-                           K, node + node_off[a], G);
+        hipLaunchKernelGGL(far_nodes_kernel, dim3(blocks_of((int64_t)K * N)), dim3(256), 0, stream, fw.ax[a], K,
+                           vals + node_off[a], G);
         hipLaunchKernelGGL(far_dct_kernel, dim3(blocks_of((int64_t)K * K)), dim3(256), 0, stream, K, D);
         hipLaunchKernelGGL(dft_matrix_kernel, dim3(blocks_of((int64_t)N * N)), dim3(256), 0, stream, N, W);
         e = zgemm(K, N, K, ZOp{D, K}, ZOp{G, N}, DG, N, 0, 0, 1, 1, {}, stream);
         if (!e) e = zgemm(K, N, N, ZOp{DG, N}, ZOp{W, N}, tab + s->far_off[a], N, 0, 0, 1, 1, {}, stream);
     }
-    if (e) return undo(e);
-    s->far_work = fwork;
-    s->far_part = part;
-    s->far_tab = tab;
-    fw.tw = tab + total;
+    if (e) {
+        (void)hipStreamSynchronize(stream);
+        (void)hipFree(tab);
+        return e;
+    }
+    fw.tw = vals;
     fw.planes = s->phasors;
+    s->wide = fw;
+    s->far_tab = tab;
+    s->far_work = scratch;
+    s->far_part = scratch + work;
     return hipSuccess;
 }
 
@@ -1576,8 +1567,7 @@ hipError_t project_adjoint(ProjectState** pst, const pstd_problem& p, const doub
 
 void project_free(ProjectState* s) {
     if (!s) return;
-    void* ptrs[] = {s->phasors, s->work, s->part, s->low, s->flags, s->near_tab, s->econ, s->far_tab,
-                    s->far_work, s->far_part};
+    void* ptrs[] = {s->phasors, s->work, s->part, s->low, s->flags, s->near_tab, s->econ, s->far_tab};
     for (void* q : ptrs) (void)hipFree(q);
     delete s;
 }
