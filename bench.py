@@ -36,22 +36,22 @@ STEP_BYTES = 28  # whole step: read psi^{n-1}, psi^n, V; write psi^{n+1}
 # FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).  Valid only for the kernel sources whose
 # SHA-256 is TRAFFIC_SRC_SHA256; otherwise traffic is reported as null.  Key:
 # (N, N1, N2, pencils per workgroup, stage-B split M1, kernel as in PASS_BYTES).
-TRAFFIC_SRC_SHA256 = "606b11575101d9ed48abddd17a3197d5bf3d20dd547230fdf9d5da2f6f128f62"
+TRAFFIC_SRC_SHA256 = "016e29e946f05d08fd3c53ec65cb623337275c5872c3f20169b523aa3be3cb74"
 TRAFFIC_KIB = {  # (fetch, write) KiB per launch
-    (160, 8, 20, 16, 0, "xy"): (32789, 64000), (160, 8, 20, 16, 0, "z+"): (128293, 32000),
-    (160, 10, 16, 8, 0, "xy"): (33665, 64002), (160, 10, 16, 8, 0, "z+"): (128600, 32379),
-    (160, 10, 16, 16, 0, "xy"): (33944, 64000), (160, 10, 16, 16, 0, "z+"): (128272, 32000),
-    (160, 10, 16, 32, 0, "xy"): (34092, 64000), (160, 10, 16, 32, 0, "z+"): (128286, 32000),
-    (160, 16, 10, 16, 0, "xy"): (32841, 64000), (160, 16, 10, 16, 0, "z+"): (128358, 32000),
-    (160, 20, 8, 16, 0, "xy"): (32815, 64000), (160, 20, 8, 16, 0, "z+"): (128300, 32000),
-    (288, 12, 24, 8, 0, "x"): (192013, 186634), (288, 12, 24, 8, 0, "y"): (373762, 192662), (288, 12, 24, 8, 0, "z"): (709218, 187224),
-    (288, 12, 24, 8, 4, "x"): (192231, 186626), (288, 12, 24, 8, 4, "y"): (387760, 202006), (288, 12, 24, 8, 4, "z"): (762268, 188748),
-    (288, 12, 24, 16, 0, "x"): (189130, 186624), (288, 12, 24, 16, 0, "y"): (373468, 186624), (288, 12, 24, 16, 0, "z"): (560224, 186624),
-    (288, 16, 18, 16, 0, "x"): (187858, 186625), (288, 16, 18, 16, 0, "y"): (373471, 186624), (288, 16, 18, 16, 0, "z"): (560234, 186624),
-    (288, 16, 18, 32, 0, "x"): (188560, 186640), (288, 16, 18, 32, 0, "y"): (373551, 186624), (288, 16, 18, 32, 0, "z"): (560261, 186624),
-    (288, 18, 16, 16, 0, "x"): (188053, 186624), (288, 18, 16, 16, 0, "y"): (373493, 186624), (288, 18, 16, 16, 0, "z"): (560881, 186624),
-    (288, 24, 12, 8, 0, "x"): (188673, 186625), (288, 24, 12, 8, 0, "y"): (373506, 190634), (288, 24, 12, 8, 0, "z"): (637478, 186639),
-    (288, 24, 12, 16, 0, "x"): (187445, 186625), (288, 24, 12, 16, 0, "y"): (373465, 186624), (288, 24, 12, 16, 0, "z"): (561026, 186624),
+    (160, 8, 20, 16, 0, "xy"): (32791, 64000), (160, 8, 20, 16, 0, "z+"): (128280, 32000),
+    (160, 10, 16, 8, 0, "xy"): (33660, 64003), (160, 10, 16, 8, 0, "z+"): (128436, 32411),
+    (160, 10, 16, 16, 0, "xy"): (33907, 64000), (160, 10, 16, 16, 0, "z+"): (128271, 32000),
+    (160, 10, 16, 32, 0, "xy"): (33983, 64000), (160, 10, 16, 32, 0, "z+"): (128281, 32000),
+    (160, 16, 10, 16, 0, "xy"): (32856, 64000), (160, 16, 10, 16, 0, "z+"): (128361, 32000),
+    (160, 20, 8, 16, 0, "xy"): (32819, 64000), (160, 20, 8, 16, 0, "z+"): (128308, 32000),
+    (288, 12, 24, 8, 0, "x"): (192126, 186631), (288, 12, 24, 8, 0, "y"): (373736, 192797), (288, 12, 24, 8, 0, "z"): (708114, 187255),
+    (288, 12, 24, 8, 4, "x"): (192179, 186628), (288, 12, 24, 8, 4, "y"): (387663, 202134), (288, 12, 24, 8, 4, "z"): (763913, 188866),
+    (288, 12, 24, 16, 0, "x"): (189127, 186624), (288, 12, 24, 16, 0, "y"): (373467, 186624), (288, 12, 24, 16, 0, "z"): (560225, 186624),
+    (288, 16, 18, 16, 0, "x"): (187822, 186624), (288, 16, 18, 16, 0, "y"): (373471, 186624), (288, 16, 18, 16, 0, "z"): (560235, 186624),
+    (288, 16, 18, 32, 0, "x"): (188537, 186643), (288, 16, 18, 32, 0, "y"): (373548, 186624), (288, 16, 18, 32, 0, "z"): (560258, 186624),
+    (288, 18, 16, 16, 0, "x"): (188066, 186624), (288, 18, 16, 16, 0, "y"): (373493, 186624), (288, 18, 16, 16, 0, "z"): (560888, 186624),
+    (288, 24, 12, 8, 0, "x"): (188646, 186626), (288, 24, 12, 8, 0, "y"): (373487, 190567), (288, 24, 12, 8, 0, "z"): (637945, 186640),
+    (288, 24, 12, 16, 0, "x"): (187470, 186625), (288, 24, 12, 16, 0, "y"): (373471, 186624), (288, 24, 12, 16, 0, "z"): (561012, 186624),
 }
 KERNEL_SOURCES = ("paper_2403_04053_amd/csrc/pass_kernel.hpp", "paper_2403_04053_amd/csrc/pass_variants.hpp",
                   "paper_2403_04053_amd/csrc/dft.hpp", "paper_2403_04053_amd/csrc/internal.hpp")
@@ -60,14 +60,14 @@ KERNEL_SOURCES = ("paper_2403_04053_amd/csrc/pass_kernel.hpp", "paper_2403_04053
 # The shell DFT of the spherical surface (r = 5, 64 x 128 nodes) on the same
 # workload, per launch of a pair of steps, valid for the sphere sources whose
 # SHA-256 is SHELL_TRAFFIC_SRC_SHA256.
-SHELL_TRAFFIC_SRC_SHA256 = "a5d7df5852590cfea0700be3e86e8917e3838de7030a6d1064a326413461f754"
+SHELL_TRAFFIC_SRC_SHA256 = "df388c5c6c4297b9b25404fa84ca4039852cabb161529d7ce3bd3b94d163889c"
 SHELL_TRAFFIC_KIB = (11305, 5252)
 SHELL_SOURCES = ("paper_2403_04053_amd/csrc/sphere.hip",)
 
 # The same for the FDTD kernel on the 160^3 grid (key: grid edge), valid for
 # the sources whose SHA-256 is FDTD_TRAFFIC_SRC_SHA256.
-FDTD_TRAFFIC_SRC_SHA256 = "db0642faf74a8d94f142dd70c008941438d18c343f3121844564f3cf9f06b1f9"
-FDTD_TRAFFIC_KIB = {160: (108349, 32000)}
+FDTD_TRAFFIC_SRC_SHA256 = "79931a9d4a630c7ffe3ebf082a04e4861b191ccd74bf7339fb96bffb151a14e6"
+FDTD_TRAFFIC_KIB = {160: (107632, 32000)}
 FDTD_SOURCES = ("paper_2403_04053_amd/csrc/fdtd.hip", "paper_2403_04053_amd/csrc/dft.hpp",
                 "paper_2403_04053_amd/csrc/internal.hpp")
 
